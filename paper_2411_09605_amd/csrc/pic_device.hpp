@@ -38,9 +38,9 @@ namespace pic {
 // (more loads in flight against fewer waves per SIMD from the extra registers).
 template <int NV> constexpr int kUnrollA = 2;
 template <int NV> constexpr int kUnrollB = 2;
-// Minimum wavefronts per SIMD the particle passes are compiled for: 6 for 1D-1V (at most 80
-// VGPRs, so memory, LDS and ALU work of more wavefronts overlap); 1D-3V keeps its registers.
-template <int NV> constexpr int kWavesPerEU = NV == 1 ? 6 : 1;
+// Minimum wavefronts per SIMD the particle passes are compiled for: one 1024-thread
+// workgroup per CU is 4 per SIMD (at most 128 VGPRs); 1D-3V keeps its registers.
+template <int NV> constexpr int kWavesPerEU = NV == 1 ? 4 : 1;
 // Largest workgroup of the particle passes.
 template <int NV> constexpr int kMaxThreads = 1024;
 
@@ -57,6 +57,29 @@ __device__ __forceinline__ unsigned nthreads()
 {
     typedef const __attribute__((address_space(4))) unsigned int *kernarg_ptr;
     return ((kernarg_ptr)__builtin_amdgcn_implicitarg_ptr())[3] & 0xffffu;
+}
+
+// A run's scalars in constant memory: the first kernel argument of the plain passes, an entry
+// of the run table in the batched ones.
+typedef const __attribute__((address_space(4))) Run *RunPtr;
+
+__device__ __forceinline__ RunPtr kernarg_run()
+{
+    return (RunPtr)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
+// The run's scalars read (again) at this point, with scalar loads.  The passes read them once
+// for their prologue and once for the particle loop: values held from one to the other would
+// not fit the scalar registers beside the prologue's addresses, and the loop would fetch its
+// constants from spill lanes (150 of 670 vector instructions of a pass-B iteration).
+__device__ __forceinline__ Run reload(RunPtr p)
+{
+    asm volatile("" : "+s"(p));
+    struct Words {
+        int w[sizeof(Run) / 4];
+    };
+    typedef const __attribute__((address_space(4))) Words *words;
+    return __builtin_bit_cast(Run, *(words)p);
 }
 
 // Written by k_group_size_probe: nthreads() as read in one-workgroup launches of 64 and
@@ -173,10 +196,10 @@ template <int U> struct WaveBatches {
     {
         return s < np ? last - s : s;
     }
-    __device__ __forceinline__ void reset() const
+    __device__ __forceinline__ void reset(unsigned nt = nthreads()) const
     {
         if (threadIdx.x == 0)
-            *ctr = (int)(nthreads() >> 6);
+            *ctr = (int)(nt >> 6);
     }
     // first particle of this wavefront's first batch (the same in every lane)
     __device__ __forceinline__ int64_t first() const
@@ -323,19 +346,20 @@ __device__ __forceinline__ double gather_poly(const double *ct, const Cell<ORDER
         return fma(c.d, fma(c.d, k[2], k[1]), k[0]);
 }
 
-// Coefficients of every cell of a tile from its interior t[0..ng) (periodic).
+// Coefficients of every cell of a tile from its node values f(0..ng) (periodic).
 //   tent:      E(d) = E_0 + d (E_1 - E_0)
 //   quadratic: E(d) = (E_0 + E_2)/8 + 3 E_1/4 + d (E_2 - E_0)/2 + d^2 ((E_0 + E_2)/2 - E_1)
-template <int ORDER>
-__device__ __forceinline__ void coef_fill(double *ct, const double *t, int ng, int tw)
+template <int ORDER, typename F>
+__device__ __forceinline__ void coef_fill(double *ct, F &&f, int ng, int tw, unsigned nt)
 {
-    for (int s = threadIdx.x; s < tw - ORDER; s += nthreads()) {
-        const double e0 = t[wrap_node(s - kGhost, ng)], e1 = t[wrap_node(s - kGhost + 1, ng)];
+    for (int s = threadIdx.x; s < tw - ORDER; s += nt) {
+        const int i0 = wrap_node(s - kGhost, ng), i1 = i0 + 1 == ng ? 0 : i0 + 1;
+        const double e0 = f(i0), e1 = f(i1);
         if constexpr (ORDER == 1) {
             ct[2 * s] = e0;
             ct[2 * s + 1] = e1 - e0;
         } else {
-            const double e2 = t[wrap_node(s - kGhost + 2, ng)];
+            const double e2 = f(i1 + 1 == ng ? 0 : i1 + 1);
             ct[3 * s] = 0.125 * (e0 + e2) + 0.75 * e1;
             ct[3 * s + 1] = 0.5 * (e2 - e0);
             ct[3 * s + 2] = 0.5 * (e0 + e2) - e1;
@@ -343,20 +367,24 @@ __device__ __forceinline__ void coef_fill(double *ct, const double *t, int ng, i
     }
 }
 
-
 // Add a workgroup's ghost-padded LDS current tile (ncomp components) into the global
 // current (hardware FP64 atomics); ghost slots go to their periodic nodes, zero entries
 // (common when the particles are cell-sorted) are skipped.
 __device__ __forceinline__ void tile_flush(const double *tile, double *J, int ncomp, int ng,
                                            int tw)
 {
-    for (int idx = threadIdx.x; idx < ncomp * tw; idx += nthreads()) {
-        const double val = tile[idx];
-        if (val != 0.0) {
-            const int c = idx / tw, j = idx % tw;
-            unsafeAtomicAdd(&J[c * ng + wrap_node(j - kGhost, ng)], val);
+    for (int c = 0; c < ncomp; ++c)
+        for (int j = threadIdx.x; j < tw; j += nthreads()) {
+            const double val = tile[c * tw + j];
+            if (val != 0.0)
+                unsafeAtomicAdd(&J[c * ng + wrap_node(j - kGhost, ng)], val);
         }
-    }
+}
+
+__device__ __forceinline__ double read_lane(double v, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
 
 // Deposit accumulator of one thread for NC current components (tile stride tw).
@@ -405,11 +433,21 @@ template <int ORDER, int NC> struct Depo<ORDER, NC, 0> {
                                          int which = 0)
     {
         side = side_tile;
-        scale = st->fx_scale[which];
-        inv = st->fx_inv[which];
+        // through vector loads (an index the compiler takes to differ by lane): a scalar
+        // load would be waited for at once, before the loads and the clearing around it
+        unsigned k = (unsigned)which;
+        asm("" : "+v"(k));
+        scale = st->fx_scale[k];
+        inv = st->fx_inv[k];
         lim = r.fx_lim;
         det = r.det;
         over = 0;
+    }
+    // Before the first add: the scales (the same in every lane) into scalar registers.
+    __device__ __forceinline__ void settle()
+    {
+        scale = read_lane(scale, 0);
+        inv = read_lane(inv, 0);
     }
     __device__ __forceinline__ void add(double *jt, int tw, int ng, const Stencil<ORDER> &s,
                                         const double (&q)[NC], bool = true, bool = true)
@@ -468,19 +506,19 @@ template <int ORDER, int NC> struct Depo<ORDER, NC, 0> {
             }
             return;
         }
-        for (int idx = threadIdx.x; idx < ncomp * tw; idx += nthreads()) {
-            const double val = value(jt, idx);
-            if (val != 0.0) {
-                const int c = idx / tw, j = idx % tw;
-                unsafeAtomicAdd(&J[c * ng + wrap_node(j - kGhost, ng)], val);
+        for (int c = 0; c < ncomp; ++c)
+            for (int j = threadIdx.x; j < tw; j += nthreads()) {
+                const double val = value(jt, c * tw + j);
+                if (val != 0.0)
+                    unsafeAtomicAdd(&J[c * ng + wrap_node(j - kGhost, ng)], val);
             }
-        }
     }
 };
 
 template <int ORDER, int NC> struct Depo<ORDER, NC, 3> {
     int over = 0;
     __device__ __forceinline__ void init(double *, const Run &, const DevState *, int = 0) {}
+    __device__ __forceinline__ void settle() {}
     __device__ __forceinline__ void add(double *jt, int tw, int ng, const Stencil<ORDER> &s,
                                         const double (&q)[NC], bool = true, bool = true)
     {
@@ -506,6 +544,7 @@ template <int ORDER, int NC> struct Depo<ORDER, NC, 1> {
     bool live;
     int over = 0;
     double acc[NC][W];
+    __device__ __forceinline__ void settle() {}
     __device__ __forceinline__ void clear()
     {
 #pragma unroll
@@ -601,6 +640,7 @@ template <int ORDER, int NC> struct Depo<ORDER, NC, 2> {
     bool live;
     int over = 0;
     double acc[NC][W];
+    __device__ __forceinline__ void settle() {}
     __device__ __forceinline__ void clear()
     {
 #pragma unroll
@@ -787,12 +827,6 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-__device__ __forceinline__ double read_lane(double v, int lane)
-{
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
-                            __builtin_amdgcn_readlane(__double2loint(v), lane));
-}
-
 // Sum (max) over the 64 lanes of a wavefront, all lanes active; every lane gets the same
 // value.  Within each row of 16 lanes, DPP butterflies (quad permutations, half-row and row
 // mirrors) leave the row's sum in all of its lanes (each addition pairs the same two
@@ -859,6 +893,46 @@ __device__ __forceinline__ void block_reduce(double (&v)[N], double *red)
     lds_barrier();
 }
 
+// A block reduction in two halves around a barrier that the caller has anyway:
+// wave_partials leaves each wavefront's value k in red; after the barrier wave_total(red, k,
+// nw) combines the nw wavefronts' values, in every lane of any wavefront that asks (all
+// lanes active).  The lanes read the values side by side and combine them within rows of 16
+// (DPP), a fixed order; reading them one after the other, as block_reduce does, is a chain of
+// nw LDS round trips (0.7 us for 16 wavefronts).
+template <unsigned MAXMASK, int N>
+__device__ __forceinline__ void wave_partials(const double (&v)[N], double *red)
+{
+    static_assert(N >= 1 && N * 16 <= kRedSize, "reduction too wide");
+    const int wid = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const double t = (MAXMASK >> k) & 1u ? wave_max(v[k]) : wave_sum(v[k]);
+        if ((threadIdx.x & 63) == 0)
+            red[k * 16 + wid] = t;
+    }
+}
+
+template <bool MAX = false>
+__device__ __forceinline__ double wave_total(const double *red, int k, unsigned nw)
+{
+    const unsigned i = threadIdx.x & 15;
+    double v = red[k * 16 + (i < nw ? i : 0)];
+    if (!MAX && i >= nw)
+        v = 0.0;
+    if constexpr (MAX) {
+        v = fmax(v, dpp_mov<0xB1>(v));
+        v = fmax(v, dpp_mov<0x4E>(v));
+        v = fmax(v, dpp_mov<0x141>(v));
+        v = fmax(v, dpp_mov<0x140>(v));
+    } else {
+        v += dpp_mov<0xB1>(v);
+        v += dpp_mov<0x4E>(v);
+        v += dpp_mov<0x141>(v);
+        v += dpp_mov<0x140>(v);
+    }
+    return v;
+}
+
 __device__ __forceinline__ double block_sum(double v, double *red)
 {
     double a[1] = {v};
@@ -913,16 +987,19 @@ __device__ __forceinline__ void rep_zero(double *J, int n, int nrep, int rs)
             J[(size_t)k * rs + i] = 0.0;
 }
 
-// Zero part `part` of `nparts` of every replica of the first n values of J (the parts
-// together cover them once), so that all workgroups of a launch share the clearing.
-__device__ __forceinline__ void rep_zero_part(double *J, int n, int nrep, int rs, int64_t part,
-                                              int64_t nparts)
+// Zero share `part` of `nparts` >= nrep of every replica of the first n values of J (the
+// shares together cover them once), so that all workgroups of a launch share the clearing:
+// share p takes a slice of replica p mod nrep.
+__device__ __forceinline__ void rep_zero_part(double *J, int n, int nrep, int rs, int part,
+                                              int nparts, unsigned nt)
 {
-    const int64_t tot = (int64_t)nrep * n;
-    const int64_t per = (tot + nparts - 1) / nparts;
-    const int64_t e1 = min(tot, (part + 1) * per);
-    for (int64_t e = part * per + threadIdx.x; e < e1; e += nthreads())
-        J[(e / n) * rs + e % n] = 0.0;
+    const unsigned k = (unsigned)part % (unsigned)nrep, j = (unsigned)part / (unsigned)nrep;
+    const unsigned slices = ((unsigned)nparts - k + nrep - 1) / (unsigned)nrep;
+    const unsigned per = ((unsigned)n + slices - 1) / slices;
+    const unsigned e1 = min((unsigned)n, (j + 1) * per);
+    double *Jk = J + (size_t)k * rs;
+    for (unsigned e = j * per + threadIdx.x; e < e1; e += nt)
+        Jk[e] = 0.0;
 }
 
 // The replica a workgroup adds into.
@@ -945,23 +1022,26 @@ template <typename D> __device__ __forceinline__ void flag_over(const D &dep, co
         atomicOr(&wk.st->flag_a, 1);
 }
 
-__device__ __forceinline__ void tile_load(double *dst, const double *src, int n)
+__device__ __forceinline__ void tile_load(double *dst, const double *src, int n,
+                                          unsigned nt = nthreads())
 {
-    for (int i = threadIdx.x; i < n; i += nthreads())
+    for (int i = threadIdx.x; i < n; i += nt)
         dst[i] = src[i];
 }
 
-__device__ __forceinline__ void tile_zero(double *dst, int n)
+__device__ __forceinline__ void tile_zero(double *dst, int n,
+                                          unsigned nt = nthreads())
 {
-    for (int i = threadIdx.x; i < n; i += nthreads())
+    for (int i = threadIdx.x; i < n; i += nt)
         dst[i] = 0.0;
 }
 
 // Fill the ghost slots of ncomp tile components from their periodic images (the
 // interior must be written and visible).
-__device__ __forceinline__ void ghost_fill(double *tile, int ncomp, int ng, int tw)
+__device__ __forceinline__ void ghost_fill(double *tile, int ncomp, int ng, int tw,
+                                          unsigned nt = nthreads())
 {
-    for (int idx = threadIdx.x; idx < ncomp * 2 * kGhost; idx += nthreads()) {
+    for (int idx = threadIdx.x; idx < ncomp * 2 * kGhost; idx += nt) {
         const int c = idx / (2 * kGhost), j = idx % (2 * kGhost);
         const int slot = j < kGhost ? j : ng + j;
         tile[c * tw + slot] = tile[c * tw + wrap_node(slot - kGhost, ng) + kGhost];
@@ -970,10 +1050,11 @@ __device__ __forceinline__ void ghost_fill(double *tile, int ncomp, int ng, int 
 
 // Interiors of the ghost-padded E [3][tw] and B [2][tw] tiles from a field block
 // E [3][ng] | B [2][ng] (Work::ps or Work::pf); the caller fills the ghosts.
-__device__ __forceinline__ void psatd_tiles(const Run &r, const double *src, double *et, double *bt)
+__device__ __forceinline__ void psatd_tiles(const Run &r, const double *src, double *et, double *bt,
+                                            unsigned nt)
 {
     const int ng = r.ng, tw = r.tw;
-    for (int idx = threadIdx.x; idx < 5 * ng; idx += nthreads()) {
+    for (int idx = threadIdx.x; idx < 5 * ng; idx += nt) {
         const int c = idx / ng, i = idx - c * ng;
         double *dst = c < 3 ? et + c * tw : bt + (c - 3) * tw;
         dst[kGhost + i] = src[idx];
@@ -1004,50 +1085,32 @@ __device__ __forceinline__ double lf_bhalf(const Run &r, const double *E, const 
 }
 
 // EMEC(LF)'s magnetic energy of the state (E^n, B^{n-1/2}) (section 4.1):
-// W_B^n = c^2/2 h sum B^{n+1/2} . B^{n-1/2}.  Summed by the first wavefront in an order
-// fixed by N_g alone (the other wavefronts add exact zeros), so that every writer of a
-// record (a pass's lead, the end-of-call launch, initialisation) gets the same bits.
-// Every thread gets the result.
-__device__ __forceinline__ double lf_magnetic_energy(const Run &r, const double *E, const double *B,
-                                                     double *red)
+// W_B^n = c^2/2 h sum B^{n+1/2} . B^{n-1/2}.  Computed by one wavefront (all lanes active)
+// in an order fixed by N_g alone, so that every writer of a record (a pass's lead, the
+// end-of-call launch, initialisation) gets the same bits.
+__device__ __forceinline__ double lf_magnetic_energy(const Run &r, const double *E, const double *B)
 {
     const int ng = r.ng;
     double s = 0.0;
-    if (threadIdx.x < 64)
-        for (int idx = threadIdx.x; idx < 2 * ng; idx += 64) {
-            const int c = idx >= ng ? 1 : 0, i = idx - c * ng;
-            s = fma(lf_bhalf(r, E, B, c, i), B[idx], s);
-        }
-    return 0.5 * r.c2 * r.h * block_sum(s, red);
+    for (int idx = threadIdx.x & 63; idx < 2 * ng; idx += 64) {
+        const int c = idx >= ng ? 1 : 0, i = idx - c * ng;
+        s = fma(lf_bhalf(r, E, B, c, i), B[idx], s);
+    }
+    return 0.5 * r.c2 * r.h * wave_sum(s);
 }
 
-// Predictor fields into the interiors of the LDS tiles es [ne][tw], bs [2][tw] from E^n,
-// B^n and j^{n,*} (the caller fills the ghosts):
-//   ESEC2: E* = E - dt/2 (j - mean j)                        (eq. (good_translation))
+// Electromagnetic predictor fields into the interiors of the LDS tiles es [3][tw], bs [2][tw]
+// from E^n, B^n and j^{n,*} (the caller fills the ghosts; the electrostatic passes build
+// theirs from NodeLoad):
 //   EM   : E* = E + dt/2 (c^2 curl B - j), B* = B - dt/2 curl E   (eq. (EMbasic))
 //   EMEC(LF): B^{n+1/2} = B - dt curl E into bs, E* = E + dt/2 (c^2 curl B^{n+1/2} - j)
 //          (eq. (EMleapfrog); the workgroup synchronises between the two)
-//   ESEC1: E* = E  (v* uses E^n, eq. (naivetranslation))
 // In 1D: (curl B)_y = -D-B_z, (curl B)_z = D-B_y, (curl E)_y = -D+E_z, (curl E)_z = D+E_y.
 __device__ __forceinline__ void predictor_fields(const Run &r, const double *E, const double *B,
-                                 const double *J, double *es, double *bs, double *red, int nrep)
+                                 const double *J, double *es, double *bs, int nrep)
 {
     const int ng = r.ng, tw = r.tw, rs = 3 * ng;
     double *e0 = es + kGhost, *b0 = bs + kGhost;
-    if (r.scheme == 1) {
-        for (int i = threadIdx.x; i < ng; i += nthreads())
-            e0[i] = E[i];
-        return;
-    }
-    if (r.scheme == 0) {
-        // the summed current goes through the tile (each thread rereads its own entries)
-        for (int i = threadIdx.x; i < ng; i += nthreads())
-            e0[i] = rep_sum(J, i, nrep, rs);
-        const double mean = block_mean(e0, ng, red);
-        for (int i = threadIdx.x; i < ng; i += nthreads())
-            e0[i] = E[i] - r.hdt * (e0[i] - mean);
-        return;
-    }
     const double *Ex = E, *Ey = E + ng, *Ez = E + 2 * ng;
     const double *By = B, *Bz = B + ng;
     if (r.scheme == kLeapfrog) {
@@ -1076,35 +1139,21 @@ __device__ __forceinline__ void predictor_fields(const Run &r, const double *E, 
     }
 }
 
-// Field update from the centred current J (global): new fields into e1 [ne][ng] and
-// b1 [2][ng] (LDS), averaged fields into the interiors of the tiles eb [ne][tw],
-// bb [2][tw] (the caller fills the ghosts).  Electromagnetic single runs take these from
-// the field launch (k_em_fields) instead; the batched form solves them here.
-//   ES: E^{n+1} = E^n - dt (j - mean j)                    (eq. (ampere) in 1D)
-//   EM (a = dt/2, s = a^2 c^2, L_h = D-D+), eq. (EMbasic) with Crank-Nicolson:
+// Electromagnetic field update (EMEC(LI)) from the centred current J (global): new fields
+// into e1 [3][ng] and b1 [2][ng] (LDS), averaged fields into the interiors of the tiles eb
+// [3][tw], bb [2][tw] (the caller fills the ghosts).  Single runs take these from the field
+// launch (k_em_fields) instead; the batched form solves them here.
+//   a = dt/2, s = a^2 c^2, L_h = D-D+, eq. (EMbasic) with Crank-Nicolson:
 //     (I - s L_h) E_y' = (I + s L_h) E_y - dt c^2 D-B_z - dt j_y,  B_z' = B_z - a D+(E_y + E_y')
 //     (I - s L_h) E_z' = (I + s L_h) E_z + dt c^2 D-B_y - dt j_z,  B_y' = B_y + a D+(E_z + E_z')
 //     E_x' = E_x - dt j_x
 //   The circulant system is solved with the first row g of its inverse.
-// scratch: EM only, 8 N_g doubles of LDS (E^n, B^n, right-hand sides, g).
+// scratch: 8 N_g doubles of LDS (E^n, B^n, right-hand sides, g).
 __device__ __forceinline__ void field_update(const Run &r, const Work &wk, const double *E, const double *B,
                              const double *J, double *e1, double *b1, double *eb, double *bb,
-                             double *scratch, double *red, int nrep)
+                             double *scratch, int nrep)
 {
     const int ng = r.ng, tw = r.tw, rs = 3 * ng;
-    if (r.scheme != 2) {
-        // the summed current goes through e1 (each thread rereads its own entries)
-        for (int i = threadIdx.x; i < ng; i += nthreads())
-            e1[i] = rep_sum(J, i, nrep, rs);
-        const double mean = block_mean(e1, ng, red);
-        for (int i = threadIdx.x; i < ng; i += nthreads()) {
-            const double e0 = E[i];
-            const double en = e0 - r.dt * (e1[i] - mean);
-            e1[i] = en;
-            eb[kGhost + i] = 0.5 * (e0 + en);
-        }
-        return;
-    }
     double *E0 = scratch;            // [3][ng]
     double *B0 = E0 + 3 * ng;        // [2][ng]
     double *R = B0 + 2 * ng;         // [2][ng]
@@ -1177,88 +1226,75 @@ __device__ __forceinline__ void lf_full_fields(const Run &r, const double *E, co
     }
 }
 
-// ESEC2 electrostatic predictor field E* of pass A into the interior of es, exactly as
-// predictor_fields computes it, with one round of loads: the replicas of j^{n,*} and E^n
-// together (E^n waits in `stash`, ng doubles of LDS that the caller overwrites later).
-// Split in two so that the caller can issue its first particle loads in between: load
-// completions are counted in order, so loads issued before these would be waited for too.
-__device__ __forceinline__ double esec2_predictor_load(const Run &r, const double *E,
-                                                       const double *J1, double *es,
-                                                       double *stash, int nrep)
-{
-    const int ng = r.ng, rs = 3 * ng;
-    double *e0 = es + kGhost;
-    double m = 0.0;
-    for (int i = threadIdx.x; i < ng; i += nthreads()) {
-        const double en0 = E[i];
-        const double a = rep_sum(J1, i, nrep, rs);
-        e0[i] = a;
-        stash[i] = en0;
-        m += a;
+// What an electrostatic pass builds its fields from, one node per thread and round: E^n and
+// the replicas of the predictor current (J1) and, in pass B, of the centred current (J2);
+// null: none (ESEC1 has no predictor current).  issue() starts the loads, commit() sums
+// the replicas in order and leaves the three values of the node in LDS.  The passes issue the
+// first round, then their first particle loads (completions are counted in order, so loads
+// issued before these would be waited for too) and the clearing of their tiles, and commit
+// after that, so the clearing is done while the loads are under way.
+// (All kMaxRep replicas are read without a branch; those past nrep repeat the last one and
+// count as zero.)
+template <bool TWO> struct NodeLoad {
+    double e, a[kMaxRep], b[TWO ? kMaxRep : 1];
+    __device__ __forceinline__ void issue(const Run &r, const double *E, const double *J1,
+                                          const double *J2, int node)
+    {
+        const unsigned i = (unsigned)min(node, r.ng - 1);
+        const unsigned rs = 3u * (unsigned)r.ng;
+        const double *A = J1 ? J1 : E;
+        const int na = J1 ? r.nrep : 1;
+        e = E[i];
+#pragma unroll
+        for (int k = 0; k < kMaxRep; ++k) {
+            a[k] = (A + (size_t)((unsigned)min(k, na - 1) * rs))[i];
+            if constexpr (TWO)
+                b[k] = (J2 + (size_t)((unsigned)min(k, r.nrep - 1) * rs))[i];
+        }
+        live = J1 ? r.nrep : 0;
     }
-    return m;
-}
-
-__device__ __forceinline__ void esec2_predictor_finish(const Run &r, double *es,
-                                                       const double *stash, double *red, double part)
-{
-    const int ng = r.ng;
-    double *e0 = es + kGhost;
-    double m[1] = {part};
-    block_reduce<0u>(m, red);
-    const double mean = m[0] / ng;
-    for (int i = threadIdx.x; i < ng; i += nthreads())
-        e0[i] = stash[i] - r.hdt * (e0[i] - mean);
-}
-
-// ESEC2 electrostatic fields of pass B: the predictor field E* into the interior of es
-// (exactly as predictor_fields computes it), E^{n+1} into e1 and the average into the
-// interior of eb (exactly as field_update computes them).  One round of loads (the
-// replicas of j^{n,*} and of j^{*,n+1/2}, and E^n, which waits in eb) and one block
-// reduction for both means; split in two like esec2_predictor.
-struct Sums2 {
-    double a, b;
+    int live;             // replicas of J1 that count
+    __device__ __forceinline__ void commit(const Run &r, int i, double *re, double *ra, double *rb,
+                                           double &sa, double &sb, double *save) const
+    {
+        if (i >= r.ng)
+            return;
+        double ja = live > 0 ? a[0] : 0.0;
+#pragma unroll
+        for (int k = 1; k < kMaxRep; ++k)
+            ja += k < live ? a[k] : 0.0;
+        re[i] = e;
+        ra[i] = ja;
+        sa += ja;
+        if constexpr (TWO) {
+            double jb = b[0];
+#pragma unroll
+            for (int k = 1; k < kMaxRep; ++k)
+                jb += k < r.nrep ? b[k] : 0.0;
+            rb[i] = jb;
+            sb += jb;
+            if (save) {
+                save[i] = e;
+                save[r.ng + i] = ja;
+                save[2 * r.ng + i] = jb;
+            }
+        }
+    }
 };
 
-__device__ __forceinline__ Sums2 esec2_fields_load(const Run &r, const double *E, const double *J1,
-                                                   const double *J2, double *es, double *e1,
-                                                   double *eb, int nrep, double *save)
+// The rounds after the first (grids with more nodes than the workgroup has threads), two
+// nodes in flight per thread.
+template <bool TWO>
+__device__ __forceinline__ void node_rounds(const Run &r, const double *E, const double *J1,
+                                            const double *J2, double *re, double *ra, double *rb,
+                                            double &sa, double &sb, double *save, int nt)
 {
-    const int ng = r.ng, rs = 3 * ng;
-    double *e0 = es + kGhost, *ebi = eb + kGhost;
-    Sums2 m = {0.0, 0.0};
-    for (int i = threadIdx.x; i < ng; i += nthreads()) {
-        const double en0 = E[i];
-        const double a = rep_sum(J1, i, nrep, rs);
-        const double b = rep_sum(J2, i, nrep, rs);
-        e0[i] = a;
-        ebi[i] = en0;
-        e1[i] = b;
-        if (save) {
-            save[i] = en0;
-            save[ng + i] = a;
-            save[2 * ng + i] = b;
-        }
-        m.a += a;
-        m.b += b;
-    }
-    return m;
-}
-
-__device__ __forceinline__ void esec2_fields_finish(const Run &r, double *es, double *e1,
-                                                    double *eb, double *red, Sums2 part)
-{
-    const int ng = r.ng;
-    double *e0 = es + kGhost, *ebi = eb + kGhost;
-    double m[2] = {part.a, part.b};
-    block_reduce<0u>(m, red);
-    const double mean1 = m[0] / ng, mean2 = m[1] / ng;
-    for (int i = threadIdx.x; i < ng; i += nthreads()) {
-        const double en0 = ebi[i];
-        e0[i] = en0 - r.hdt * (e0[i] - mean1);
-        const double en = en0 - r.dt * (e1[i] - mean2);
-        e1[i] = en;
-        ebi[i] = 0.5 * (en0 + en);
+    for (int i = threadIdx.x + nt; i < r.ng; i += 2 * nt) {
+        NodeLoad<TWO> p, q;
+        p.issue(r, E, J1, J2, i);
+        q.issue(r, E, J1, J2, i + nt);
+        p.commit(r, i, re, ra, rb, sa, sb, save);
+        q.commit(r, i + nt, re, ra, rb, sa, sb, save);
     }
 }
 
@@ -1279,67 +1315,99 @@ __device__ __forceinline__ void field_energies(const Run &r, const double *E, co
     *wb = em ? 0.5 * r.c2 * r.h * block_sum(sb, red) : 0.0;
 }
 
-// Write the record of `step` from the pass-B scalars of every workgroup (summed in a
-// fixed order) and the field energies in st; run by one workgroup.
+// Write the record of `step` from the pass-B scalars of every workgroup and the field
+// energies in st.  One wavefront (all lanes active) writes it, without a barrier, so in a
+// pass the lead workgroup's other wavefronts go on with its particles meanwhile: the record
+// is a chain of three memory round trips (2.5 us at 256 workgroups), which used to sit in
+// front of the lead's particles (pass A of Landau 1e5 x 64: 7.2 us on the lead, 5.9 on the
+// others).  Lane l takes workgroups l, l + 64, ... in turn and the lanes are summed in a fixed
+// order, so every writer of a record gets the same bits.
 // The standard scheme (Run::scheme == kStandard) has its fields at half steps: its record
 // of step n >= 1 is TE at (n - 1/2) dt, the mean of the kinetic energies of steps n - 1
 // (slot 4, written by the same pass) and n plus the field energy of E^{n-1/2}.
-
-__device__ __forceinline__ void write_record(const Run &r, const Work &wk, int64_t step, double *red)
+__device__ __forceinline__ void write_record(const Run &r, const Work &wk, int64_t step)
 {
     const bool half = r.scheme == kStandard && step > 0;
+    const int lane = threadIdx.x & 63;
+    DevState *st = wk.st;
+    const double we = st->we, wb = st->wb, te_start = st->te0;
+    const int64_t fb_before = step == 0 ? 0 : st->fb_total;
+    const int32_t sticky = step == 0 ? 0 : st->nonfinite_sticky;
     double ke = 0.0, fb = 0.0, gd = 0.0, nf = 0.0;
-    // The kinetic energy is summed by the first wavefront alone (lane l takes workgroups
-    // l, l + 64, ... in turn, then the fixed wavefront and workgroup reductions, where the
-    // other wavefronts add exact zeros), so the sum does not depend on the size of the
-    // workgroup writing the record: a pass and the end-of-call launch write the same
-    // record.  The other values are exact (integer sums below 2^53, maxima).
-    if (threadIdx.x < 64)
-        for (int b = threadIdx.x; b < r.nblocks; b += 64)
-            ke += half ? 0.5 * (wk.spart[b * kNS + 0] + wk.spart[b * kNS + 4]) : wk.spart[b * kNS + 0];
-    for (int b = threadIdx.x; b < r.nblocks; b += nthreads()) {
-        fb += wk.spart[b * kNS + 1];
-        gd = fmax(gd, wk.spart[b * kNS + 2]);
-        nf = fmax(nf, wk.spart[b * kNS + 3]);
+#pragma unroll 4
+    for (int b = lane; b < r.nblocks; b += 64) {
+        const double *sp = wk.spart + (size_t)b * kNS;
+        ke += half ? 0.5 * (sp[0] + sp[4]) : sp[0];
+        fb += sp[1];
+        gd = fmax(gd, sp[2]);
+        nf = fmax(nf, sp[3]);
     }
-    ke = block_sum(ke, red);
-    fb = block_sum(fb, red);
-    gd = block_max(gd, red);
-    nf = block_max(nf, red);
-    if (threadIdx.x == 0) {
-        DevState *st = wk.st;
-        if (st->flag_a) {
+    ke = wave_sum(ke);
+    fb = wave_sum(fb);
+    gd = wave_max(gd);
+    nf = wave_max(nf);
+    if (lane == 0) {
+        // (exchanged: workgroups of this pass may set it for the next record meanwhile)
+        if (atomicExch(&st->flag_a, 0))
             nf = 1.0;
-            st->flag_a = 0;
-        }
-        if (step == 0) {
-            st->fb_total = 0;
-            st->nonfinite_sticky = 0;
-        }
-        const double te = ke + st->we + st->wb;
-        if (step == 0)
-            st->te0 = te;
-        st->fb_total += (int64_t)fb;
-        st->nonfinite_sticky |= (nf != 0.0);
+        const double te = ke + we + wb, te0 = step == 0 ? te : te_start;
+        const int64_t fb_total = fb_before + (int64_t)fb;
+        st->te0 = te0;
+        st->fb_total = fb_total;
+        st->nonfinite_sticky = sticky | (nf != 0.0);
         DevRecord rec;
         rec.step = step;
         rec.time = ((double)step - (half ? 0.5 : 0.0)) * r.dt;
         rec.kinetic = ke;
-        rec.field_e = st->we;
-        rec.field_b = st->wb;
+        rec.field_e = we;
+        rec.field_b = wb;
         rec.total = te;
-        rec.rel_energy_err = fabs(te - st->te0) / st->te0;
+        rec.rel_energy_err = fabs(te - te0) / te0;
         rec.max_gamma_dev = gd;
         rec.fallbacks = (int64_t)fb;
-        rec.fallbacks_total = st->fb_total;
+        rec.fallbacks_total = fb_total;
         rec.nonfinite = nf != 0.0;
         rec.pad = 0;
-        wk.rec[step % r.rec_cap] = rec;
+        wk.rec[step < ((int64_t)1 << 31) ? (int64_t)((uint32_t)step % (uint32_t)r.rec_cap) : step % r.rec_cap] = rec;
         st->recorded = step;
     }
 }
 
+// The wavefront of a workgroup that writes records and energies: its last one.
+__device__ __forceinline__ bool record_wave(unsigned nt = nthreads())
+{
+    return (unsigned)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == (nt >> 6) - 1;
+}
+
+// h/2 sum_i f(i) over n values, by one wavefront (all lanes active).
+template <typename F> __device__ __forceinline__ double wave_energy(double half_h, int n, F &&f)
+{
+    double s = 0.0;
+    for (int i = threadIdx.x & 63; i < n; i += 64)
+        s += f(i);
+    return half_h * wave_sum(s);
+}
+
 // --------------------------------------------------------------- particle kernels
+// The double buffers of a run with those of parity par at index 0 (see pass_a_body): the
+// passes then index them with constants, which also keeps a batched run's descriptor in
+// registers rather than in scratch memory.
+__host__ __device__ inline Work by_parity(Work w, int par)
+{
+    if (par) {
+        const double *t[4] = {w.Ef[0], w.Bf[0], w.J1[0], w.J2[0]};
+        w.Ef[0] = w.Ef[1];
+        w.Bf[0] = w.Bf[1];
+        w.J1[0] = w.J1[1];
+        w.J2[0] = w.J2[1];
+        w.Ef[1] = const_cast<double *>(t[0]);
+        w.Bf[1] = const_cast<double *>(t[1]);
+        w.J1[1] = const_cast<double *>(t[2]);
+        w.J2[1] = const_cast<double *>(t[3]);
+    }
+    return w;
+}
+
 template <int NV, bool EM> struct TileSizes {
     static constexpr int ne = EM ? 3 : 1;      // E components gathered
     static constexpr int nb = EM ? 2 : 0;      // B components gathered
@@ -1424,81 +1492,94 @@ __device__ __forceinline__ Half<ORDER, NV, EM> half_step(const Run &r, double x,
     return o;
 }
 
-// Pass A of step n (par = n & 1).
-// LDS: jt[ncur][tw] | es[ne][tw] | bs[nb][tw]
-// pass_a_body processes particles [p0, p1) of one run; `lead` marks the one workgroup
-// (per run and launch) that also clears the other predictor current and writes the record.
+// Pass A of step n.  The passes take the run's arrays with those of the step's parity at
+// index 0 (Work's double buffers turned by the caller, by_parity), so their addresses come with the
+// kernel arguments instead of from a second, dependent read of them.
+// LDS: EM: jt[ncur][tw] | es[ne][tw] | bs[nb][tw] | side[ncur][tw]; ES: jt[tw] | es[tw]
+//      (j^{n,*}) | side[tw] | eraw[tw] (E^n) | coefficients of E*
+// pass_a_body processes particles [p0, p1) of one run, its workgroup `slot`; `lead` marks
+// the one workgroup (per run and launch) that also writes the record.
 template <int ORDER, int NV, bool EM, int DEP, int U = kUnrollA<NV>>
-__device__ __forceinline__ void pass_a_body(const Run &r, const Work &wk, int par, int64_t step,
+__device__ __forceinline__ void pass_a_body(const Run &r0, RunPtr rp, const Work &wk, int64_t step,
                                             const double *__restrict__ X,
                                             const double *__restrict__ V, int64_t p0,
-                                            int64_t p1, bool lead, double *smem, double *red,
-                                            int *wctr)
+                                            int64_t p1, bool lead, int slot, double *smem,
+                                            double *red, int *wctr)
 {
+    const Run &r = r0;
     using T = TileSizes<NV, EM>;
     const int ng = r.ng, tw = r.tw;
-    const unsigned lane = threadIdx.x & 63;
+    const unsigned lane = threadIdx.x & 63, nt = nthreads();
     double *jt = smem;
     double *es = jt + T::ncur * tw;
     double *bs = es + T::ne * tw;
     double *side = bs + T::nb * tw;       // [ncur][tw] FP64 side tile of the deposit
-    double *ct = smem + coef_offset((2 * T::ncur + T::ne + T::nb) * tw);   // ES: coefficients
+    double *eraw = side + T::ncur * tw;   // ES: E^n (es: j^{n,*})
+    double *ct = smem + coef_offset((2 * T::ncur + T::ne + T::nb + 1) * tw);   // ES: coefficients
+    Depo<ORDER, T::ncur, DEP> dep;
     // pass A walks the state from its end, pass B from its start (see WaveBatches)
     WaveBatches<U> wb(p0, wctr, r.interleave, r.nblocks, r.det, r.np, true);
     PBatch<U, NV> cur, nxt;
     int64_t bcur = wb.first();
-    wb.reset();
-    if (!EM && r.scheme == 0) {
-        const double part = esec2_predictor_load(r, wk.Ef[par], wk.J1[par], es, ct, r.nrep);
-        load_batch(cur, X, V, r.vstride, bcur, p1);
-        esec2_predictor_finish(r, es, ct, red, part);
-    } else if (EM && r.scheme == kPsatd) {
-        // E*, B* come from the field launch before this pass
-        psatd_tiles(r, wk.ps, es, bs);
+    wb.reset(nt);
+    NodeLoad<false> nodes;
+    // ESEC1 gathers E^n itself: no predictor current
+    const double *j1 = EM || r.scheme != 0 ? nullptr : wk.J1[0];
+    if constexpr (!EM) {
+        nodes.issue(r, wk.Ef[0], j1, nullptr, threadIdx.x);
+        dep.init(side, r, wk.st);
+        __builtin_amdgcn_sched_barrier(0);
         load_batch(cur, X, V, r.vstride, bcur, p1);
     } else {
-        predictor_fields(r, wk.Ef[par], EM ? wk.Bf[par] : nullptr, wk.J1[par], es, bs, red, r.nrep);
-        load_batch(cur, X, V, r.vstride, bcur, p1);
+        dep.init(side, r, wk.st);
     }
-    tile_zero(jt, T::ncur * tw);
-    tile_zero(side, T::ncur * tw);
+    tile_zero(jt, T::ncur * tw, nt);
+    tile_zero(side, T::ncur * tw, nt);
     // the currents of the next step accumulate into the other buffers (nothing reads them
     // in this pass): every workgroup clears its share
-    {
-        const int64_t part = p0 / r.chunk, nparts = r.nblocks;
-        if (r.scheme != 1)
-            rep_zero_part(wk.J1[par ^ 1], T::ncur * ng, r.nrep, 3 * ng, part, nparts);
-        rep_zero_part(wk.J2[par ^ 1], T::ncur * ng, r.nrep, 3 * ng, part, nparts);
+    if (r.scheme != 1)
+        rep_zero_part(wk.J1[1], T::ncur * ng, r.nrep, 3 * ng, slot, r.nblocks, nt);
+    rep_zero_part(wk.J2[1], T::ncur * ng, r.nrep, 3 * ng, slot, r.nblocks, nt);
+    if constexpr (EM) {
+        if (r.scheme == kPsatd)
+            psatd_tiles(r, wk.ps, es, bs, nt);    // E*, B* come from the field launch before
+        else
+            predictor_fields(r, wk.Ef[0], wk.Bf[0], wk.J1[0], es, bs, r.nrep);
+        load_batch(cur, X, V, r.vstride, bcur, p1);
+        lds_barrier();
+        ghost_fill(es, T::ne, ng, tw, nt);
+        ghost_fill(bs, T::nb, ng, tw, nt);
+    } else {
+        double m[1] = {0.0}, unused = 0.0;
+        nodes.commit(r, threadIdx.x, eraw, es, nullptr, m[0], unused, nullptr);
+        node_rounds<false>(r, wk.Ef[0], j1, nullptr, eraw, es, nullptr, m[0], unused, nullptr, nt);
+        wave_partials<0u>(m, red);
+        lds_barrier();
+        const double mean = wave_total(red, 0, nt >> 6) * r.inv_ng;
+        coef_fill<ORDER>(ct, [&](int i) { return eraw[i] - r.hdt * (es[i] - mean); }, ng, tw, nt);
     }
+    lds_barrier();
     // the record of the state this step starts from, if not written yet
-    if (lead && step > wk.st->recorded) {
+    if (lead && record_wave(nt) && step > wk.st->recorded) {
         if (EM && r.scheme == kLeapfrog) {
-            const double wbl = lf_magnetic_energy(r, wk.Ef[par], wk.Bf[par], red);
-            if (threadIdx.x == 0)
+            const double wbl = lf_magnetic_energy(r, wk.Ef[0], wk.Bf[0]);
+            if (lane == 0)
                 wk.st->wb = wbl;
         }
-        write_record(r, wk, step, red);
+        write_record(r, wk, step);
     }
-    lds_barrier();
-    if constexpr (EM) {
-        ghost_fill(es, T::ne, ng, tw);
-        ghost_fill(bs, T::nb, ng, tw);
-    } else {
-        coef_fill<ORDER>(ct, es + kGhost, ng, tw);
-    }
-    lds_barrier();
     const double *eg = EM ? es : ct;     // what half_step gathers E from
 
-    Depo<ORDER, T::ncur, DEP> dep;
-    dep.init(side, r, wk.st);
+    const Run q = reload(rp);
+    dep.settle();
     // whole wavefronts run the loop (DEP = 2 needs them in its deposit); particles past the
     // end are masked with `valid`
     while (bcur < p1) {
         const int64_t bnxt = wb.claim();
         const unsigned nval = (unsigned)min(p1 - bcur, (int64_t)(64 * U));
         double w[U];
-        load_weights(w, r.w, r.wu, bcur, p1);
-        load_batch(nxt, X, V, r.vstride, bnxt, p1);   // the last one is discarded
+        load_weights(w, q.w, q.wu, bcur, p1);
+        load_batch(nxt, X, V, q.vstride, bnxt, p1);   // the last one is discarded
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const bool valid = lane + 64u * u < nval;
@@ -1506,17 +1587,17 @@ __device__ __forceinline__ void pass_a_body(const Run &r, const Work &wk, int pa
                 if (!valid)
                     break;
             }
-            const Half<ORDER, NV, EM> hs = half_step<ORDER, NV, EM>(r, cur.x[u], cur.v[u], eg, bs);
-            const double q = valid ? w[u] * r.qs : 0.0;
+            const Half<ORDER, NV, EM> hs = half_step<ORDER, NV, EM>(q, cur.x[u], cur.v[u], eg, bs);
+            const double qw = valid ? w[u] * q.qs : 0.0;
             double qv[T::ncur];
 #pragma unroll
             for (int c = 0; c < T::ncur; ++c)
-                qv[c] = q * hs.vs[c];
+                qv[c] = qw * hs.vs[c];
             bool done = false;
             if constexpr (!EM && ORDER == 1 && DEP != 2) {
-                if (r.cc) {
+                if (q.cc) {
                     // exact charge conservation: through the pieces of the path x^n -> x^{n+1}
-                    cc_pieces(r, cur.x[u], hs.x1, [&](double base, double t, double f) {
+                    cc_pieces(q, cur.x[u], hs.x1, [&](double base, double t, double f) {
                         double qf[T::ncur];
 #pragma unroll
                         for (int c = 0; c < T::ncur; ++c)
@@ -1527,7 +1608,7 @@ __device__ __forceinline__ void pass_a_body(const Run &r, const Work &wk, int pa
                 }
             }
             if (!done)
-                dep.add(jt, tw, ng, stencil<ORDER>(hs.xh * r.inv_h), qv, valid, u == 0);
+                dep.add(jt, tw, ng, stencil<ORDER>(hs.xh * q.inv_h), qv, valid, u == 0);
         }
         cur = nxt;
         bcur = bnxt;
@@ -1535,12 +1616,12 @@ __device__ __forceinline__ void pass_a_body(const Run &r, const Work &wk, int pa
     dep.finish(jt, tw, ng);
     flag_over(dep, wk);
     lds_barrier();
-    dep.flush_tile(jt, dep_target(r, wk, wk.J2[par]), T::ncur, ng, tw);
+    dep.flush_tile(jt, dep_target(q, wk, wk.J2[0]), T::ncur, ng, tw);
 }
 
 template <int ORDER, int NV, bool EM, int DEP>
 __global__ __launch_bounds__(kMaxThreads<NV>) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<NV>)))
-void k_pass_a(Run r, Work wk, int par, int64_t step,
+void k_pass_a(Run r, Work wk, int64_t step,
                                                  const double *__restrict__ X,
                                                  const double *__restrict__ V)
 {
@@ -1548,32 +1629,53 @@ void k_pass_a(Run r, Work wk, int par, int64_t step,
     __shared__ double red[kRedSize];
     __shared__ int wctr;
     const int64_t p0 = (int64_t)blockIdx.x * r.chunk;
-    // the lead (which also writes the record) is the last workgroup, whose chunk is the
-    // smallest when N_p is not a multiple of it, so its extra work does not lengthen the pass
-    pass_a_body<ORDER, NV, EM, DEP>(r, wk, par, step, X, V, p0,
+    // the lead (one of whose wavefronts also writes the record) is the last workgroup, whose
+    // chunk is the smallest when N_p is not a multiple of it
+    pass_a_body<ORDER, NV, EM, DEP>(r, kernarg_run(), wk, step, X, V, p0,
                                     r.interleave ? r.np : min(r.np, p0 + r.chunk),
-                                    (int)blockIdx.x == r.nblocks - 1, smem, red, &wctr);
+                                    (int)blockIdx.x == r.nblocks - 1, blockIdx.x, smem, red,
+                                    &wctr);
 }
 
-// Pass B of step n (par = n & 1): new fields, second gather, Gamma, state write and
+// A workgroup's scalars from the wavefronts' partials in red (after the barrier): kinetic
+// energy (halved here) and fallbacks are sums, max |Gamma - 1| and the non-finite flag
+// maxima.  Written by the record wavefront.
+__device__ __forceinline__ void write_scalars(double *sp, const double *red, unsigned nt)
+{
+    if (record_wave(nt)) {
+        const unsigned nw = nt >> 6;
+        const double ke = 0.5 * wave_total(red, 0, nw), fb = wave_total(red, 1, nw);
+        const double gd = wave_total<true>(red, 2, nw), nf = wave_total<true>(red, 3, nw);
+        if ((threadIdx.x & 63) == 0) {
+            sp[0] = ke;
+            sp[1] = fb;
+            sp[2] = gd;
+            sp[3] = nf;
+        }
+    }
+}
+
+// Pass B of step n: new fields, second gather, Gamma, state write and
 // (PRED) the next step's predictor deposit.
 // LDS: jt[ncur][tw] | es[ne][tw] | bs[nb][tw] | eb[ne][tw] | bb[nb][tw] | e1[ne][ng] |
-//      b1[nb][ng] | EM scratch[8 ng]
+//      b1[nb][ng] | EM scratch[8 ng] | side[ncur][tw]; ES: es, eb, e1 hold j^{n,*}, E^n,
+//      j^{*,n+1/2}, and the coefficients of E* and E-bar follow side
 // pass_b_body processes particles [p0, p1) of one run and leaves its scalars in
 // spart[slot]; `lead` marks the workgroup that publishes the new fields of the run.
 template <int ORDER, int NV, bool EM, bool PRED, int DEP, int U = kUnrollB<NV>>
-__device__ __forceinline__ void pass_b_body(const Run &r, const Work &wk, int par, const double *X,
+__device__ __forceinline__ void pass_b_body(const Run &r0, RunPtr rp, const Work &wk, const double *X,
                                             const double *V, double *Xo, double *Vo,
                                             int64_t p0, int64_t p1, bool lead, int slot,
                                             double *smem, double *red, int *wctr)
 {
+    const Run &r = r0;
     using T = TileSizes<NV, EM>;
     const int ng = r.ng, tw = r.tw;
-    const unsigned lane = threadIdx.x & 63;
+    const unsigned lane = threadIdx.x & 63, nt = nthreads();
     WaveBatches<U> wb(p0, wctr, r.interleave, r.nblocks, r.det);
     PBatch<U, NV> cur, nxt;
     int64_t bcur = wb.first();
-    wb.reset();
+    wb.reset(nt);
     double *jt = smem;
     double *es = jt + T::ncur * tw;
     double *bs = es + T::ne * tw;
@@ -1586,94 +1688,120 @@ __device__ __forceinline__ void pass_b_body(const Run &r, const Work &wk, int pa
     // ES: coefficient tiles of E* and E-bar
     double *cts = smem + coef_offset((2 * T::ncur + 2 * T::ne + 2 * T::nb) * tw + (T::ne + T::nb + (EM ? 8 : 0)) * ng);
     double *ctb = cts + (ORDER + 1) * tw;
-    const double *En = wk.Ef[par];
-    const double *Bn = EM ? wk.Bf[par] : nullptr;
-    // the first particle batch is issued after the field loads (see esec2_predictor)
-    if (!EM && r.scheme == 0) {
-        const Sums2 part = esec2_fields_load(r, En, wk.J1[par], wk.J2[par], es, e1, eb, r.nrep,
-                                             lead ? wk.grid_save : nullptr);
+    const double *En = wk.Ef[0];
+    const double *Bn = EM ? wk.Bf[0] : nullptr;
+    Depo<ORDER, T::ncur, DEP> dep;
+    NodeLoad<true> nodes;
+    const double *j1 = EM || r.scheme != 0 ? nullptr : wk.J1[0];
+    if constexpr (!EM) {
+        nodes.issue(r, En, j1, wk.J2[0], threadIdx.x);
+        dep.init(side, r, wk.st);
+        __builtin_amdgcn_sched_barrier(0);
         load_batch(cur, X, V, r.vstride, bcur, p1);
-        esec2_fields_finish(r, es, e1, eb, red, part);
-    } else if (EM && r.em_fields) {
-        // the fields v-dagger gathers come from the field launch before this pass, which
-        // has also published E^{n+1}, B^{n+1} (the lead reads those back for their
-        // energies); E*, B* from the predictor launch (PSATD) or, for the local LI
-        // predictor, as in pass A
-        if (r.scheme == kPsatd)
-            psatd_tiles(r, wk.ps, es, bs);
-        else
-            predictor_fields(r, En, Bn, wk.J1[par], es, bs, red, r.nrep);
-        psatd_tiles(r, wk.pf, eb, bb);
-        if (lead) {
-            tile_load(e1, wk.Ef[par ^ 1], 3 * ng);
-            tile_load(b1, wk.Bf[par ^ 1], 2 * ng);
-        }
-        load_batch(cur, X, V, r.vstride, bcur, p1);
-    } else if (EM && r.scheme == kLeapfrog) {
-        predictor_fields(r, En, Bn, wk.J1[par], es, bs, red, r.nrep);
-        load_batch(cur, X, V, r.vstride, bcur, p1);
-        lf_full_fields(r, En, wk.J2[par], bs, e1, b1, eb, bb, r.nrep);
     } else {
-        predictor_fields(r, En, Bn, wk.J1[par], es, bs, red, r.nrep);
-        load_batch(cur, X, V, r.vstride, bcur, p1);
-        field_update(r, wk, En, Bn, wk.J2[par], e1, b1, eb, bb, scratch, red, r.nrep);
+        dep.init(side, r, wk.st);
     }
     if constexpr (PRED) {
-        tile_zero(jt, T::ncur * tw);
-        tile_zero(side, T::ncur * tw);
+        tile_zero(jt, T::ncur * tw, nt);
+        tile_zero(side, T::ncur * tw, nt);
     }
-    lds_barrier();
     if constexpr (EM) {
-        ghost_fill(es, T::ne, ng, tw);
-        ghost_fill(eb, T::ne, ng, tw);
-        ghost_fill(bs, T::nb, ng, tw);
-        ghost_fill(bb, T::nb, ng, tw);
-    } else {
-        coef_fill<ORDER>(cts, es + kGhost, ng, tw);
-        coef_fill<ORDER>(ctb, eb + kGhost, ng, tw);
-    }
-    const double *eg = EM ? es : cts;    // what half_step gathers E* from
-    if (lead) {
-        // publish E^{n+1} (B^{n+1}) and their energies (pass A clears the next currents)
-        if (!(EM && r.em_fields)) {
-            for (int i = threadIdx.x; i < T::ne * ng; i += nthreads())
-                wk.Ef[par ^ 1][i] = e1[i];
-            if constexpr (EM)
-                for (int i = threadIdx.x; i < 2 * ng; i += nthreads())
-                    wk.Bf[par ^ 1][i] = b1[i];
+        if (r.em_fields) {
+            // the fields v-dagger gathers come from the field launch before this pass, which
+            // has also published E^{n+1}, B^{n+1} (the lead reads those back for their
+            // energies); E*, B* from the predictor launch (PSATD) or, for the local LI
+            // predictor, as in pass A
+            if (r.scheme == kPsatd)
+                psatd_tiles(r, wk.ps, es, bs, nt);
+            else
+                predictor_fields(r, En, Bn, wk.J1[0], es, bs, r.nrep);
+            psatd_tiles(r, wk.pf, eb, bb, nt);
+            if (lead) {
+                tile_load(e1, wk.Ef[1], 3 * ng, nt);
+                tile_load(b1, wk.Bf[1], 2 * ng, nt);
+            }
+            load_batch(cur, X, V, r.vstride, bcur, p1);
+        } else if (r.scheme == kLeapfrog) {
+            predictor_fields(r, En, Bn, wk.J1[0], es, bs, r.nrep);
+            load_batch(cur, X, V, r.vstride, bcur, p1);
+            lf_full_fields(r, En, wk.J2[0], bs, e1, b1, eb, bb, r.nrep);
+        } else {
+            predictor_fields(r, En, Bn, wk.J1[0], es, bs, r.nrep);
+            load_batch(cur, X, V, r.vstride, bcur, p1);
+            field_update(r, wk, En, Bn, wk.J2[0], e1, b1, eb, bb, scratch, r.nrep);
         }
-        if constexpr (!EM) {
-            if (wk.grid_save) {
-                // the fields this step gathers, for the adjoint's reverse passes
-                double *sv = wk.grid_save + 3 * ng;
-                for (int i = threadIdx.x; i < ng; i += nthreads()) {
-                    sv[i] = es[kGhost + i];
-                    sv[ng + i] = eb[kGhost + i];
-                    sv[2 * ng + i] = e1[i];
+        lds_barrier();
+        ghost_fill(es, T::ne, ng, tw, nt);
+        ghost_fill(eb, T::ne, ng, tw, nt);
+        ghost_fill(bs, T::nb, ng, tw, nt);
+        ghost_fill(bb, T::nb, ng, tw, nt);
+        if (lead) {
+            // publish E^{n+1}, B^{n+1} and their energies (pass A clears the next currents)
+            if (!r.em_fields) {
+                for (int i = threadIdx.x; i < T::ne * ng; i += nt)
+                    wk.Ef[1][i] = e1[i];
+                for (int i = threadIdx.x; i < 2 * ng; i += nt)
+                    wk.Bf[1][i] = b1[i];
+            }
+            if (record_wave(nt)) {
+                const double we = wave_energy(0.5 * r.h, 3 * ng, [&](int i) { return e1[i] * e1[i]; });
+                const double wb = wave_energy(0.5 * r.c2 * r.h, 2 * ng, [&](int i) { return b1[i] * b1[i]; });
+                if (lane == 0) {
+                    wk.st->we = we;
+                    // EMEC(LF)'s W_B needs B^{n+3/2}: the writer of the next record computes it
+                    if (r.scheme != kLeapfrog)
+                        wk.st->wb = wb;
                 }
             }
         }
-        double we, wb;
-        field_energies(r, e1, b1, &we, &wb, red);
-        if (threadIdx.x == 0) {
-            wk.st->we = we;
-            // EMEC(LF)'s W_B needs B^{n+3/2}: the writer of the next record computes it
-            if (r.scheme != kLeapfrog)
-                wk.st->wb = wb;
+    } else {
+        // E* = E^n - dt/2 (j^{n,*} - mean) (eq. (good_translation); ESEC1: E^n) and
+        // E^{n+1} = E^n - dt (j^{*,n+1/2} - mean) (eq. (ampere) in 1D), from the node values
+        double *save = lead ? wk.grid_save : nullptr;
+        double m[2] = {0.0, 0.0};
+        nodes.commit(r, threadIdx.x, eb, es, e1, m[0], m[1], save);
+        node_rounds<true>(r, En, j1, wk.J2[0], eb, es, e1, m[0], m[1], save, nt);
+        wave_partials<0u>(m, red);
+        lds_barrier();
+        const double mean1 = wave_total(red, 0, nt >> 6) * r.inv_ng, mean2 = wave_total(red, 1, nt >> 6) * r.inv_ng;
+        auto star = [&](int i) { return eb[i] - r.hdt * (es[i] - mean1); };
+        auto next = [&](int i) { return eb[i] - r.dt * (e1[i] - mean2); };
+        auto bar = [&](int i) { return 0.5 * (eb[i] + next(i)); };
+        coef_fill<ORDER>(cts, star, ng, tw, nt);
+        coef_fill<ORDER>(ctb, bar, ng, tw, nt);
+        if (lead) {
+            // publish E^{n+1} and its energy (pass A clears the next currents)
+            for (int i = threadIdx.x; i < ng; i += nt)
+                wk.Ef[1][i] = next(i);
+            if (save)
+                // the fields this step gathers, for the adjoint's reverse passes
+                for (int i = threadIdx.x; i < ng; i += nt) {
+                    save[3 * ng + i] = star(i);
+                    save[4 * ng + i] = bar(i);
+                    save[5 * ng + i] = next(i);
+                }
+            if (record_wave(nt)) {
+                const double we = wave_energy(0.5 * r.h, ng, [&](int i) { return next(i) * next(i); });
+                if (lane == 0) {
+                    wk.st->we = we;
+                    wk.st->wb = 0.0;
+                }
+            }
         }
     }
+    const double *eg = EM ? es : cts;    // what half_step gathers E* from
     lds_barrier();
 
-    Depo<ORDER, T::ncur, DEP> dep;
-    dep.init(side, r, wk.st);
     double ke = 0.0, gdev = 0.0;
     int fb = 0, nonfinite = 0;
+    const Run q = reload(rp);
+    dep.settle();
     while (bcur < p1) {
         const int64_t bnxt = wb.claim();
         const unsigned nval = (unsigned)min(p1 - bcur, (int64_t)(64 * U));
         double w[U];
-        load_weights(w, r.w, r.wu, bcur, p1);
-        load_batch(nxt, X, V, r.vstride, bnxt, p1);   // the last one is discarded
+        load_weights(w, q.w, q.wu, bcur, p1);
+        load_batch(nxt, X, V, q.vstride, bnxt, p1);   // the last one is discarded
         double *Xob = Xo + bcur;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -1684,44 +1812,44 @@ __device__ __forceinline__ void pass_b_body(const Run &r, const Work &wk, int pa
                     break;
             }
             const double *v = cur.v[u];
-            const Half<ORDER, NV, EM> hs = half_step<ORDER, NV, EM>(r, cur.x[u], v, eg, bs);
+            const Half<ORDER, NV, EM> hs = half_step<ORDER, NV, EM>(q, cur.x[u], v, eg, bs);
             double vd[NV];
             if constexpr (NV == 1) {
                 double eb1;
                 if constexpr (ORDER == 1)
-                    eb1 = r.cc ? cc_gather(r, ctb, cur.x[u], hs.x1)
-                               : gather_poly<ORDER>(ctb, cell_of<ORDER>(hs.xh * r.inv_h, ng));
+                    eb1 = q.cc ? cc_gather(q, ctb, cur.x[u], hs.x1)
+                               : gather_poly<ORDER>(ctb, cell_of<ORDER>(hs.xh * q.inv_h, ng));
                 else
-                    eb1 = gather_poly<ORDER>(ctb, cell_of<ORDER>(hs.xh * r.inv_h, ng));
-                vd[0] = fma(r.dt, eb1, v[0]);
+                    eb1 = gather_poly<ORDER>(ctb, cell_of<ORDER>(hs.xh * q.inv_h, ng));
+                vd[0] = fma(q.dt, eb1, v[0]);
             } else {
                 double e[3], b[3];
-                b[0] = r.bext[0];
+                b[0] = q.bext[0];
                 if constexpr (EM) {
-                    const Stencil<ORDER> s = stencil<ORDER>(hs.xh * r.inv_h);
+                    const Stencil<ORDER> s = stencil<ORDER>(hs.xh * q.inv_h);
                     const Slots<ORDER> n = slots_of<ORDER>(s, ng);
                     e[0] = gather1<ORDER>(eb, s, n);
                     e[1] = gather1<ORDER>(eb + tw, s, n);
                     e[2] = gather1<ORDER>(eb + 2 * tw, s, n);
-                    const Stencil<ORDER> sh = stencil<ORDER>(hs.xh * r.inv_h - 0.5);
+                    const Stencil<ORDER> sh = stencil<ORDER>(hs.xh * q.inv_h - 0.5);
                     const Slots<ORDER> nh = slots_of<ORDER>(sh, ng);
-                    b[1] = r.bext[1] + gather1<ORDER>(bb, sh, nh);
-                    b[2] = r.bext[2] + gather1<ORDER>(bb + tw, sh, nh);
+                    b[1] = q.bext[1] + gather1<ORDER>(bb, sh, nh);
+                    b[2] = q.bext[2] + gather1<ORDER>(bb + tw, sh, nh);
                 } else {
                     if constexpr (ORDER == 1)
-                        e[0] = r.cc ? cc_gather(r, ctb, cur.x[u], hs.x1)
-                                    : gather_poly<ORDER>(ctb, cell_of<ORDER>(hs.xh * r.inv_h, ng));
+                        e[0] = q.cc ? cc_gather(q, ctb, cur.x[u], hs.x1)
+                                    : gather_poly<ORDER>(ctb, cell_of<ORDER>(hs.xh * q.inv_h, ng));
                     else
-                        e[0] = gather_poly<ORDER>(ctb, cell_of<ORDER>(hs.xh * r.inv_h, ng));
+                        e[0] = gather_poly<ORDER>(ctb, cell_of<ORDER>(hs.xh * q.inv_h, ng));
                     e[1] = 0.0;
                     e[2] = 0.0;
-                    b[1] = r.bext[1];
-                    b[2] = r.bext[2];
+                    b[1] = q.bext[1];
+                    b[2] = q.bext[2];
                 }
                 // v-dagger = v^n + dt (E-bar + v* x B-bar)   (eq. (good_translation), (EMbasic))
-                vd[0] = v[0] + r.dt * (e[0] + (hs.vs[1] * b[2] - hs.vs[2] * b[1]));
-                vd[1] = v[1] + r.dt * (e[1] + (hs.vs[2] * b[0] - hs.vs[0] * b[2]));
-                vd[2] = v[2] + r.dt * (e[2] + (hs.vs[0] * b[1] - hs.vs[1] * b[0]));
+                vd[0] = v[0] + q.dt * (e[0] + (hs.vs[1] * b[2] - hs.vs[2] * b[1]));
+                vd[1] = v[1] + q.dt * (e[1] + (hs.vs[2] * b[0] - hs.vs[0] * b[2]));
+                vd[2] = v[2] + q.dt * (e[2] + (hs.vs[0] * b[1] - hs.vs[1] * b[0]));
             }
             // Gamma (eq. (opt_solution)); an imaginary or undefined root falls back to 1.
             // num2 = 2 num = sum (2 v* - (v-dagger + v)) . (v-dagger - v)
@@ -1741,7 +1869,7 @@ __device__ __forceinline__ void pass_b_body(const Run &r, const Work &wk, int pa
                 vn[c] = g * vd[c];
                 v2 = fma(vn[c], vn[c], v2);
             }
-            const double xw = wrap_pos(hs.x1, r.L);
+            const double xw = wrap_pos(hs.x1, q.L);
             const double wp = valid ? w[u] : 0.0;
             if (valid) {
                 // the new state is written through to memory (system-scope relaxed stores):
@@ -1749,7 +1877,7 @@ __device__ __forceinline__ void pass_b_body(const Run &r, const Work &wk, int pa
                 // XCD would be written back at the end of the kernel
 #pragma unroll
                 for (int c = 0; c < NV; ++c)
-                    __hip_atomic_store(&(Vo + c * r.vstride + bcur)[o], vn[c], __ATOMIC_RELAXED,
+                    __hip_atomic_store(&(Vo + c * q.vstride + bcur)[o], vn[c], __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_SYSTEM);
                 __hip_atomic_store(&Xob[o], xw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
                 fb += fbp;
@@ -1759,12 +1887,12 @@ __device__ __forceinline__ void pass_b_body(const Run &r, const Work &wk, int pa
                     nonfinite = 1;
             }
             if constexpr (PRED) {
-                const double q = wp * r.qs;
+                const double qw = wp * q.qs;
                 double qv[T::ncur];
 #pragma unroll
                 for (int c = 0; c < T::ncur; ++c)
-                    qv[c] = q * vn[c];
-                dep.add(jt, tw, ng, stencil<ORDER>(fma(r.hdt, vn[0], xw) * r.inv_h - r.xshift), qv, valid,
+                    qv[c] = qw * vn[c];
+                dep.add(jt, tw, ng, stencil<ORDER>(fma(q.hdt, vn[0], xw) * q.inv_h - q.xshift), qv, valid,
                         u == 0);
             }
         }
@@ -1776,30 +1904,24 @@ __device__ __forceinline__ void pass_b_body(const Run &r, const Work &wk, int pa
         nonfinite |= dep.over;
     }
     // kinetic energy and fallbacks (sums), max |Gamma - 1| and the non-finite flag (maxima)
-    double sc[4] = {ke, (double)fb, gdev, (double)nonfinite};
-    block_reduce<0xcu>(sc, red);
-    if (threadIdx.x == 0) {
-        wk.spart[slot * kNS + 0] = 0.5 * sc[0];
-        wk.spart[slot * kNS + 1] = sc[1];
-        wk.spart[slot * kNS + 2] = sc[2];
-        wk.spart[slot * kNS + 3] = sc[3];
-    }
-    if constexpr (PRED) {
-        lds_barrier();
-        dep.flush_tile(jt, dep_target(r, wk, wk.J1[par ^ 1]), T::ncur, ng, tw);
-    }
+    const double sc[4] = {ke, (double)fb, gdev, (double)nonfinite};
+    wave_partials<0xcu>(sc, red);
+    lds_barrier();
+    if constexpr (PRED)
+        dep.flush_tile(jt, dep_target(q, wk, wk.J1[1]), T::ncur, ng, tw);
+    write_scalars(wk.spart + (size_t)slot * kNS, red, nt);
 }
 
 template <int ORDER, int NV, bool EM, bool PRED, int DEP>
 __global__ __launch_bounds__(kMaxThreads<NV>) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<NV>)))
-void k_pass_b(Run r, Work wk, int par, const double *X,
+void k_pass_b(Run r, Work wk, const double *X,
                                                  const double *V, double *Xo, double *Vo)
 {
     extern __shared__ double smem[];
     __shared__ double red[kRedSize];
     __shared__ int wctr;
     const int64_t p0 = (int64_t)blockIdx.x * r.chunk;
-    pass_b_body<ORDER, NV, EM, PRED, DEP>(r, wk, par, X, V, Xo, Vo, p0,
+    pass_b_body<ORDER, NV, EM, PRED, DEP>(r, kernarg_run(), wk, X, V, Xo, Vo, p0,
                                           r.interleave ? r.np : min(r.np, p0 + r.chunk),
                                           (int)blockIdx.x == r.nblocks - 1, blockIdx.x, smem,
                                           red, &wctr);
@@ -1821,22 +1943,23 @@ void k_pass_b(Run r, Work wk, int par, const double *X,
 // into.  The per-workgroup scalars alternate between two arrays as well: this pass's lead
 // writes the record of step n from the scalars of the previous pass (wk.spart) while
 // the other workgroups write theirs for step n + 1 (spw).
-// LDS: jt[ncur][tw] | es[tw] | eb[tw] | e1[ng] | side[ncur][tw] | three coefficient tiles
-//      (E^n, E-bar, E^{n+1}), ES only.
+// LDS: jt[tw] | es[tw] (E^n) | eb[tw] (unused) | e1[ng] (j^{n+1/2}) | side[tw] | three
+//      coefficient tiles (E^n, E-bar, E^{n+1}).
 template <int ORDER, int NV, int DEP, int U = kUnrollB<NV>>
-__device__ __forceinline__ void esec1_body(const Run &r, const Work &wk, int par, int64_t step,
+__device__ __forceinline__ void esec1_body(const Run &r0, RunPtr rp, const Work &wk, int64_t step,
                                            const double *X, const double *V, double *Xo,
                                            double *Vo, const double *Jr, double *Jd, double *Jc,
                                            double *spw, int64_t p0, int64_t p1, bool lead,
                                            int slot, double *smem, double *red, int *wctr)
 {
+    const Run &r = r0;
     const int ng = r.ng, tw = r.tw;
-    const unsigned lane = threadIdx.x & 63;
+    const unsigned lane = threadIdx.x & 63, nt = nthreads();
     // one pass per step: alternate directions (see WaveBatches)
     WaveBatches<U> wb(p0, wctr, r.interleave, r.nblocks, r.det, r.np, (step & 1) != 0);
     PBatch<U, NV> cur, nxt;
     int64_t bcur = wb.first();
-    wb.reset();
+    wb.reset(nt);
     double *jt = smem;
     double *es = jt + tw;
     double *eb = es + tw;
@@ -1845,48 +1968,53 @@ __device__ __forceinline__ void esec1_body(const Run &r, const Work &wk, int par
     double *ctn = smem + coef_offset(4 * tw + ng);     // E^n
     double *ctb = ctn + (ORDER + 1) * tw;               // E-bar
     double *ct1 = ctb + (ORDER + 1) * tw;               // E^{n+1}
-    const double *En = wk.Ef[par];
-    // fields: E^n into es, E^{n+1} into e1, E-bar into eb (field_update, as in pass B)
-    for (int i = threadIdx.x; i < ng; i += nthreads())
-        es[kGhost + i] = En[i];
+    const double *En = wk.Ef[0];
+    Depo<ORDER, 1, DEP> dep;
+    // node values: E^n into es, j^{n+1/2} into e1 (see pass_b_body)
+    NodeLoad<false> nodes;
+    nodes.issue(r, En, Jr, nullptr, threadIdx.x);
+    dep.init(side, r, wk.st);
+    __builtin_amdgcn_sched_barrier(0);
     load_batch(cur, X, V, r.vstride, bcur, p1);
-    field_update(r, wk, En, nullptr, Jr, e1, nullptr, eb, nullptr, nullptr, red, r.nrep);
-    tile_zero(jt, tw);
-    tile_zero(side, tw);
-    {
-        const int64_t part = p0 / r.chunk, nparts = r.nblocks;
-        rep_zero_part(Jc, ng, r.nrep, 3 * ng, part, nparts);
-    }
+    tile_zero(jt, tw, nt);
+    tile_zero(side, tw, nt);
+    rep_zero_part(Jc, ng, r.nrep, 3 * ng, slot, r.nblocks, nt);
+    double m[1] = {0.0}, unused = 0.0;
+    nodes.commit(r, threadIdx.x, es, e1, nullptr, m[0], unused, nullptr);
+    node_rounds<false>(r, En, Jr, nullptr, es, e1, nullptr, m[0], unused, nullptr, nt);
+    wave_partials<0u>(m, red);
     lds_barrier();
-    coef_fill<ORDER>(ctn, es + kGhost, ng, tw);
-    coef_fill<ORDER>(ctb, eb + kGhost, ng, tw);
-    coef_fill<ORDER>(ct1, e1, ng, tw);
-    if (lead) {
+    const double mean = wave_total(red, 0, nt >> 6) * r.inv_ng;
+    auto next = [&](int i) { return es[i] - r.dt * (e1[i] - mean); };     // E^{n+1}
+    coef_fill<ORDER>(ctn, [&](int i) { return es[i]; }, ng, tw, nt);
+    coef_fill<ORDER>(ctb, [&](int i) { return 0.5 * (es[i] + next(i)); }, ng, tw, nt);
+    coef_fill<ORDER>(ct1, next, ng, tw, nt);
+    if (lead)
+        for (int i = threadIdx.x; i < ng; i += nt)
+            wk.Ef[1][i] = next(i);
+    lds_barrier();
+    if (lead && record_wave(nt)) {
         // the record of step n (its kinetic energy from the previous pass's scalars, its
-        // field energy from st->we), then E^{n+1} and its energy for step n + 1
+        // field energy from st->we), then the energy of E^{n+1} for step n + 1
         if (step > wk.st->recorded)
-            write_record(r, wk, step, red);
-        for (int i = threadIdx.x; i < ng; i += nthreads())
-            wk.Ef[par ^ 1][i] = e1[i];
-        double we, wbv;
-        field_energies(r, e1, nullptr, &we, &wbv, red);
-        if (threadIdx.x == 0) {
+            write_record(r, wk, step);
+        const double we = wave_energy(0.5 * r.h, ng, [&](int i) { return next(i) * next(i); });
+        if (lane == 0) {
             wk.st->we = we;
             wk.st->wb = 0.0;
         }
     }
-    lds_barrier();
 
-    Depo<ORDER, 1, DEP> dep;
-    dep.init(side, r, wk.st);
     double ke = 0.0, gdev = 0.0;
     int fb = 0, nonfinite = 0;
+    const Run q = reload(rp);
+    dep.settle();
     while (bcur < p1) {
         const int64_t bnxt = wb.claim();
         const unsigned nval = (unsigned)min(p1 - bcur, (int64_t)(64 * U));
         double w[U];
-        load_weights(w, r.w, r.wu, bcur, p1);
-        load_batch(nxt, X, V, r.vstride, bnxt, p1);   // the last one is discarded
+        load_weights(w, q.w, q.wu, bcur, p1);
+        load_batch(nxt, X, V, q.vstride, bnxt, p1);   // the last one is discarded
         double *Xob = Xo + bcur;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -1897,16 +2025,16 @@ __device__ __forceinline__ void esec1_body(const Run &r, const Work &wk, int par
                     break;
             }
             const double *v = cur.v[u];
-            const Half<ORDER, NV, false> hs = half_step<ORDER, NV, false>(r, cur.x[u], v, ctn, nullptr);
+            const Half<ORDER, NV, false> hs = half_step<ORDER, NV, false>(q, cur.x[u], v, ctn, nullptr);
             double vd[NV];
-            const double eh = gather_poly<ORDER>(ctb, cell_of<ORDER>(hs.xh * r.inv_h, ng));
+            const double eh = gather_poly<ORDER>(ctb, cell_of<ORDER>(hs.xh * q.inv_h, ng));
             if constexpr (NV == 1) {
-                vd[0] = fma(r.dt, eh, v[0]);
+                vd[0] = fma(q.dt, eh, v[0]);
             } else {
-                const double *b = r.bext;
-                vd[0] = v[0] + r.dt * (eh + (hs.vs[1] * b[2] - hs.vs[2] * b[1]));
-                vd[1] = v[1] + r.dt * (hs.vs[2] * b[0] - hs.vs[0] * b[2]);
-                vd[2] = v[2] + r.dt * (hs.vs[0] * b[1] - hs.vs[1] * b[0]);
+                const double *b = q.bext;
+                vd[0] = v[0] + q.dt * (eh + (hs.vs[1] * b[2] - hs.vs[2] * b[1]));
+                vd[1] = v[1] + q.dt * (hs.vs[2] * b[0] - hs.vs[0] * b[2]);
+                vd[2] = v[2] + q.dt * (hs.vs[0] * b[1] - hs.vs[1] * b[0]);
             }
             double num2 = 0.0, den = 0.0;
 #pragma unroll
@@ -1924,12 +2052,12 @@ __device__ __forceinline__ void esec1_body(const Run &r, const Work &wk, int par
                 vn[c] = g * vd[c];
                 v2 = fma(vn[c], vn[c], v2);
             }
-            const double xw = wrap_pos(hs.x1, r.L);
+            const double xw = wrap_pos(hs.x1, q.L);
             const double wp = valid ? w[u] : 0.0;
             if (valid) {
 #pragma unroll
                 for (int c = 0; c < NV; ++c)
-                    __hip_atomic_store(&(Vo + c * r.vstride + bcur)[o], vn[c], __ATOMIC_RELAXED,
+                    __hip_atomic_store(&(Vo + c * q.vstride + bcur)[o], vn[c], __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_SYSTEM);
                 __hip_atomic_store(&Xob[o], xw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
                 fb += fbp;
@@ -1939,37 +2067,32 @@ __device__ __forceinline__ void esec1_body(const Run &r, const Work &wk, int par
                     nonfinite = 1;
             }
             // step n + 1: v* from E^{n+1} at x*_{n+1}, and the centred deposit j^{n+3/2}
-            const Half<ORDER, NV, false> h1 = half_step<ORDER, NV, false>(r, xw, vn, ct1, nullptr);
-            const double q[1] = {wp * r.qs * h1.vs[0]};
-            dep.add(jt, tw, ng, stencil<ORDER>(h1.xh * r.inv_h), q, valid, u == 0);
+            const Half<ORDER, NV, false> h1 = half_step<ORDER, NV, false>(q, xw, vn, ct1, nullptr);
+            const double qd[1] = {wp * q.qs * h1.vs[0]};
+            dep.add(jt, tw, ng, stencil<ORDER>(h1.xh * q.inv_h), qd, valid, u == 0);
         }
         cur = nxt;
         bcur = bnxt;
     }
     dep.finish(jt, tw, ng);
     nonfinite |= dep.over;
-    double sc[4] = {ke, (double)fb, gdev, (double)nonfinite};
-    block_reduce<0xcu>(sc, red);
-    if (threadIdx.x == 0) {
-        spw[slot * kNS + 0] = 0.5 * sc[0];
-        spw[slot * kNS + 1] = sc[1];
-        spw[slot * kNS + 2] = sc[2];
-        spw[slot * kNS + 3] = sc[3];
-    }
+    const double sc[4] = {ke, (double)fb, gdev, (double)nonfinite};
+    wave_partials<0xcu>(sc, red);
     lds_barrier();
-    dep.flush_tile(jt, dep_target(r, wk, Jd), 1, ng, tw);
+    dep.flush_tile(jt, dep_target(q, wk, Jd), 1, ng, tw);
+    write_scalars(spw + (size_t)slot * kNS, red, nt);
 }
 
 template <int ORDER, int NV, int DEP>
 __global__ __launch_bounds__(kMaxThreads<NV>) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<NV>)))
-void k_esec1(Run r, Work wk, int par, int64_t step, const double *X, const double *V, double *Xo,
+void k_esec1(Run r, Work wk, int64_t step, const double *X, const double *V, double *Xo,
              double *Vo, const double *Jr, double *Jd, double *Jc, double *spw)
 {
     extern __shared__ double smem[];
     __shared__ double red[kRedSize];
     __shared__ int wctr;
     const int64_t p0 = (int64_t)blockIdx.x * r.chunk;
-    esec1_body<ORDER, NV, DEP>(r, wk, par, step, X, V, Xo, Vo, Jr, Jd, Jc, spw, p0,
+    esec1_body<ORDER, NV, DEP>(r, kernarg_run(), wk, step, X, V, Xo, Vo, Jr, Jd, Jc, spw, p0,
                                r.interleave ? r.np : min(r.np, p0 + r.chunk),
                                (int)blockIdx.x == r.nblocks - 1, blockIdx.x, smem, red, &wctr);
 }
@@ -2082,57 +2205,60 @@ __global__ __launch_bounds__(1024) void k_std_prime(Run r, Work wk, const double
 // state, the kinetic energies before and after, and the density at x*_{n+1}.
 // LDS: jt[tw] | es[tw] | side[tw] | coefficient tile of E^{n+1/2}.
 template <int ORDER, int NV, int DEP, int U = kUnrollB<NV>>
-__device__ __forceinline__ void std_pass_body(const Run &r, const Work &wk, int par, int64_t step,
+__device__ __forceinline__ void std_pass_body(const Run &r0, RunPtr rp, const Work &wk, int64_t step,
                                               const double *X, const double *V, double *Xo,
                                               double *Vo, double *Jd, double *Jc, double *spw,
                                               int64_t p0, int64_t p1, bool lead, int slot,
-                                              double *smem, double *red, int *wctr)
+                                              double *smem, double *red, double *red0, int *wctr)
 {
+    const Run &r = r0;
     const int ng = r.ng, tw = r.tw;
-    const unsigned lane = threadIdx.x & 63;
+    const unsigned lane = threadIdx.x & 63, nt = nthreads();
     // one pass per step: alternate directions (see WaveBatches)
     WaveBatches<U> wb(p0, wctr, r.interleave, r.nblocks, r.det, r.np, (step & 1) != 0);
     PBatch<U, NV> cur, nxt;
     int64_t bcur = wb.first();
-    wb.reset();
+    wb.reset(nt);
     double *jt = smem;
     double *es = jt + tw;
     double *side = es + tw;
     double *ct = smem + coef_offset(3 * tw);
-    const double *Eh = wk.Ef[par];
-    for (int i = threadIdx.x; i < ng; i += nthreads())
-        es[kGhost + i] = Eh[i];
+    const double *Eh = wk.Ef[0];
+    Depo<ORDER, 1, DEP> dep;
+    const double eh0 = Eh[min((int)threadIdx.x, ng - 1)];
+    dep.init(side, r, wk.st, 1);
+    __builtin_amdgcn_sched_barrier(0);
     load_batch(cur, X, V, r.vstride, bcur, p1);
-    tile_zero(jt, tw);
-    tile_zero(side, tw);
-    {
-        const int64_t part = p0 / r.chunk, nparts = r.nblocks;
-        rep_zero_part(Jc, ng, r.nrep, 3 * ng, part, nparts);
-    }
+    tile_zero(jt, tw, nt);
+    tile_zero(side, tw, nt);
+    rep_zero_part(Jc, ng, r.nrep, 3 * ng, slot, r.nblocks, nt);
+    if ((int)threadIdx.x < ng)
+        es[threadIdx.x] = eh0;
+    for (int i = threadIdx.x + nt; i < ng; i += nt)
+        es[i] = Eh[i];
     lds_barrier();
-    coef_fill<ORDER>(ct, es + kGhost, ng, tw);
-    if (lead) {
+    coef_fill<ORDER>(ct, [&](int i) { return es[i]; }, ng, tw, nt);
+    lds_barrier();
+    if (lead && record_wave(nt)) {
         if (step > wk.st->recorded)
-            write_record(r, wk, step, red);
-        double we, wbv;
-        field_energies(r, es + kGhost, nullptr, &we, &wbv, red);
-        if (threadIdx.x == 0) {
+            write_record(r, wk, step);
+        const double we = wave_energy(0.5 * r.h, ng, [&](int i) { return es[i] * es[i]; });
+        if (lane == 0) {
             wk.st->we = we;
             wk.st->wb = 0.0;
         }
     }
-    lds_barrier();
 
-    Depo<ORDER, 1, DEP> dep;
-    dep.init(side, r, wk.st, 1);
     double ke1 = 0.0, ke0 = 0.0;
     int nonfinite = 0;
+    const Run q = reload(rp);
+    dep.settle();
     while (bcur < p1) {
         const int64_t bnxt = wb.claim();
         const unsigned nval = (unsigned)min(p1 - bcur, (int64_t)(64 * U));
         double w[U];
-        load_weights(w, r.w, r.wu, bcur, p1);
-        load_batch(nxt, X, V, r.vstride, bnxt, p1);   // the last one is discarded
+        load_weights(w, q.w, q.wu, bcur, p1);
+        load_batch(nxt, X, V, q.vstride, bnxt, p1);   // the last one is discarded
         double *Xob = Xo + bcur;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -2143,23 +2269,23 @@ __device__ __forceinline__ void std_pass_body(const Run &r, const Work &wk, int 
                     break;
             }
             const double *v = cur.v[u];
-            const double xs = fma(r.hdt, v[0], cur.x[u]);
-            const double ep = gather_poly<ORDER>(ct, cell_of<ORDER>(xs * r.inv_h, ng));
+            const double xs = fma(q.hdt, v[0], cur.x[u]);
+            const double ep = gather_poly<ORDER>(ct, cell_of<ORDER>(xs * q.inv_h, ng));
             double vn[NV];
             if constexpr (NV == 1) {
-                vn[0] = fma(r.dt, ep, v[0]);
+                vn[0] = fma(q.dt, ep, v[0]);
             } else {
                 // v^{n+1/2} = u + v^{n+1/2} x t, u = v^n + dt/2 E, t = dt/2 B; v^{n+1} = 2 v^{n+1/2} - v^n
-                const double uu[3] = {fma(r.hdt, ep, v[0]), v[1], v[2]};
-                const double tt[3] = {r.hdt * r.bext[0], r.hdt * r.bext[1], r.hdt * r.bext[2]};
+                const double uu[3] = {fma(q.hdt, ep, v[0]), v[1], v[2]};
+                const double tt[3] = {q.hdt * q.bext[0], q.hdt * q.bext[1], q.hdt * q.bext[2]};
                 double vh[3];
                 rotate_half(uu, tt, vh);
 #pragma unroll
                 for (int c = 0; c < 3; ++c)
                     vn[c] = fma(2.0, vh[c], -v[c]);
             }
-            const double x1 = fma(r.hdt, vn[0], xs);
-            const double xw = wrap_pos(x1, r.L);
+            const double x1 = fma(q.hdt, vn[0], xs);
+            const double xw = wrap_pos(x1, q.L);
             const double wp = valid ? w[u] : 0.0;
             double v2 = 0.0, v20 = 0.0;
 #pragma unroll
@@ -2170,7 +2296,7 @@ __device__ __forceinline__ void std_pass_body(const Run &r, const Work &wk, int 
             if (valid) {
 #pragma unroll
                 for (int c = 0; c < NV; ++c)
-                    __hip_atomic_store(&(Vo + c * r.vstride + bcur)[o], vn[c], __ATOMIC_RELAXED,
+                    __hip_atomic_store(&(Vo + c * q.vstride + bcur)[o], vn[c], __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_SYSTEM);
                 __hip_atomic_store(&Xob[o], xw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
                 ke1 = fma(wp, v2, ke1);
@@ -2179,52 +2305,56 @@ __device__ __forceinline__ void std_pass_body(const Run &r, const Work &wk, int 
                     nonfinite = 1;
             }
             // the density of step n + 1 at x*_{n+1}
-            const double q[1] = {wp * r.qs};
-            dep.add(jt, tw, ng, stencil<ORDER>(fma(r.hdt, vn[0], xw) * r.inv_h), q, valid, u == 0);
+            const double qd[1] = {wp * q.qs};
+            dep.add(jt, tw, ng, stencil<ORDER>(fma(q.hdt, vn[0], xw) * q.inv_h), qd, valid, u == 0);
         }
         cur = nxt;
         bcur = bnxt;
     }
     dep.finish(jt, tw, ng);
     nonfinite |= dep.over;
-    double sc[3] = {ke1, ke0, (double)nonfinite};
-    block_reduce<4u>(sc, red);
-    if (threadIdx.x == 0) {
-        spw[slot * kNS + 0] = 0.5 * sc[0];
-        spw[slot * kNS + 1] = 0.0;
-        spw[slot * kNS + 2] = 0.0;
-        spw[slot * kNS + 3] = sc[2];
-        spw[slot * kNS + 4] = 0.5 * sc[1];
-    }
+    // slots: kinetic energy after, no fallbacks, no Gamma, non-finite; kinetic energy before
+    const double sc[4] = {ke1, 0.0, 0.0, (double)nonfinite};
+    wave_partials<0xcu>(sc, red);
+    const double ke0w = wave_sum(ke0);
+    if (lane == 0)
+        red0[threadIdx.x >> 6] = ke0w;
     lds_barrier();
-    dep.flush_tile(jt, dep_target(r, wk, Jd), 1, ng, tw);
+    dep.flush_tile(jt, dep_target(q, wk, Jd), 1, ng, tw);
+    write_scalars(spw + (size_t)slot * kNS, red, nt);
+    if (record_wave(nt)) {
+        const double k0 = 0.5 * wave_total(red0, 0, nt >> 6);
+        if (lane == 0)
+            spw[(size_t)slot * kNS + 4] = k0;
+    }
 }
 
 template <int ORDER, int NV, int DEP>
 __global__ __launch_bounds__(kMaxThreads<NV>) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<NV>)))
-void k_std_pass(Run r, Work wk, int par, int64_t step, const double *X, const double *V, double *Xo,
+void k_std_pass(Run r, Work wk, int64_t step, const double *X, const double *V, double *Xo,
                 double *Vo, double *Jd, double *Jc, double *spw)
 {
     extern __shared__ double smem[];
-    __shared__ double red[kRedSize];
+    __shared__ double red[kRedSize], red0[16];
     __shared__ int wctr;
     const int64_t p0 = (int64_t)blockIdx.x * r.chunk;
-    std_pass_body<ORDER, NV, DEP>(r, wk, par, step, X, V, Xo, Vo, Jd, Jc, spw, p0,
+    std_pass_body<ORDER, NV, DEP>(r, kernarg_run(), wk, step, X, V, Xo, Vo, Jd, Jc, spw, p0,
                                   r.interleave ? r.np : min(r.np, p0 + r.chunk),
-                                  (int)blockIdx.x == r.nblocks - 1, blockIdx.x, smem, red, &wctr);
+                                  (int)blockIdx.x == r.nblocks - 1, blockIdx.x, smem, red, red0,
+                                  &wctr);
 }
 
 // End of a pic_step call (one workgroup): the record of the newest state and a copy of
 // the newest fields into the caller's arrays.
-__device__ void finish_body(const Run &r, const Work &wk, int par, int64_t step, double *red)
+__device__ void finish_body(const Run &r, const Work &wk, int par, int64_t step)
 {
-    if (step > wk.st->recorded) {
+    if (record_wave() && step > wk.st->recorded) {
         if (r.scheme == kLeapfrog) {
-            const double wbl = lf_magnetic_energy(r, wk.Ef[par], wk.Bf[par], red);
-            if (threadIdx.x == 0)
+            const double wbl = lf_magnetic_energy(r, wk.Ef[par], wk.Bf[par]);
+            if ((threadIdx.x & 63) == 0)
                 wk.st->wb = wbl;
         }
-        write_record(r, wk, step, red);
+        write_record(r, wk, step);
     }
     for (int i = threadIdx.x; i < 3 * r.ng; i += nthreads())
         wk.E[i] = wk.Ef[par][i];
@@ -2235,8 +2365,7 @@ __device__ void finish_body(const Run &r, const Work &wk, int par, int64_t step,
 
 __global__ __launch_bounds__(1024) void k_finish(Run r, Work wk, int par, int64_t step)
 {
-    __shared__ double red[kRedSize];
-    finish_body(r, wk, par, step, red);
+    finish_body(r, wk, par, step);
 }
 
 // Copy of the newest record into a caller's device pic_diag (one thread).
@@ -2811,12 +2940,12 @@ __global__ __launch_bounds__(256) void k_em_rows(Run r, Work wk)
 // LDS: e | B (signed) | j | the three rows [6][N] | partial sums [kPsatdSeg][kPsatdOut].
 constexpr int kPsatdOut = 32, kPsatdSeg = 8;
 
-__global__ __launch_bounds__(256) void k_em_fields(Run r, Work wk, int par, int full)
+__global__ __launch_bounds__(256) void k_em_fields(Run r, Work wk, int full)
 {
     extern __shared__ double sm[];
     const int ng = r.ng, rs = 3 * ng, q = blockIdx.y;
     const int p = full ? q / 3 : q >> 1, o = full ? q % 3 : q & 1;
-    const double *E = wk.Ef[par], *B = wk.Bf[par], *J = full ? wk.J2[par] : wk.J1[par];
+    const double *E = wk.Ef[0], *B = wk.Bf[0], *J = full ? wk.J2[0] : wk.J1[0];
     const int bc = p == 0 ? 1 : 0;       // pair 0: B_z, pair 1: B_y (taken as -B_y)
     const double sg = p == 0 ? 1.0 : -1.0;
     double *e = sm, *b = sm + ng, *jj = sm + 2 * ng, *k0 = sm + 3 * ng, *k1 = sm + 4 * ng,
@@ -2866,10 +2995,10 @@ __global__ __launch_bounds__(256) void k_em_fields(Run r, Work wk, int par, int 
         else
             wk.ps[(3 + bc) * ng + i] = sg * acc;
     } else if (o == 0) {
-        wk.Ef[par ^ 1][(1 + p) * ng + i] = acc;
+        wk.Ef[1][(1 + p) * ng + i] = acc;
     } else if (o == 1) {
         const double bn = sg * acc;
-        wk.Bf[par ^ 1][bc * ng + i] = bn;
+        wk.Bf[1][bc * ng + i] = bn;
         wk.pf[(3 + bc) * ng + i] = 0.5 * (B[bc * ng + i] + bn);
     } else {
         wk.pf[(1 + p) * ng + i] = acc;
@@ -2877,7 +3006,7 @@ __global__ __launch_bounds__(256) void k_em_fields(Run r, Work wk, int par, int 
     if (q == 0) {
         const double ex = E[i], jx = rep_sum(J, i, r.nrep, rs);
         if (full) {
-            wk.Ef[par ^ 1][i] = ex - r.dt * jx;
+            wk.Ef[1][i] = ex - r.dt * jx;
             wk.pf[i] = ex - r.hdt * jx;
         } else {
             wk.ps[i] = ex - r.hdt * jx;
@@ -2897,8 +3026,8 @@ __device__ void init_finish_body(const Run &r, const Work &wk, double *red)
             wk.Bf[0][i] = wk.B[i];
     double we, wb;
     field_energies(r, wk.E, wk.B, &we, &wb, red);
-    if (r.scheme == kLeapfrog)
-        wb = lf_magnetic_energy(r, wk.E, wk.B, red);
+    if (r.scheme == kLeapfrog && threadIdx.x < 64)
+        wb = lf_magnetic_energy(r, wk.E, wk.B);
     if (threadIdx.x == 0) {
         wk.st->we = we;
         wk.st->wb = wb;
@@ -2907,7 +3036,8 @@ __device__ void init_finish_body(const Run &r, const Work &wk, double *red)
     // the charge scratch must be zero before the first centred deposit
     rep_zero(wk.J2[0], 3 * ng, r.nrep, 3 * ng);
     __syncthreads();
-    write_record(r, wk, 0, red);
+    if (threadIdx.x < 64)
+        write_record(r, wk, 0);
 }
 
 __global__ __launch_bounds__(1024) void k_init_finish(Run r, Work wk)
@@ -2978,6 +3108,9 @@ constexpr int kBatchMaxThreads = 512;
 // usually larger than the Infinity Cache and streams from HBM, whose longer latency wants
 // more loads in flight than the plain passes (U = 2).
 template <int NV> constexpr int kBatchUnroll = NV == 1 ? 4 : 2;
+// Wavefronts per SIMD the batched passes are compiled for: two 512-thread workgroups per CU
+// (at most 128 VGPRs), so that one's prologue and flush overlap the other's particles.
+constexpr int kBatchWavesPerEU = 4;
 
 struct Batch {
     const BatchRun *runs;
@@ -2987,27 +3120,8 @@ struct Batch {
     int64_t *stepc;        // steps completed (device counter)
 };
 
-// The per-step arrays of a run with those of parity par at index 0: the pass bodies then
-// index them with constants (par = 0), which keeps the copied descriptor in registers
-// rather than in scratch memory.
-__device__ __forceinline__ Work by_parity(Work w, int par)
-{
-    if (par) {
-        const double *t[4] = {w.Ef[0], w.Bf[0], w.J1[0], w.J2[0]};
-        w.Ef[0] = w.Ef[1];
-        w.Bf[0] = w.Bf[1];
-        w.J1[0] = w.J1[1];
-        w.J2[0] = w.J2[1];
-        w.Ef[1] = const_cast<double *>(t[0]);
-        w.Bf[1] = const_cast<double *>(t[1]);
-        w.J1[1] = const_cast<double *>(t[2]);
-        w.J2[1] = const_cast<double *>(t[3]);
-    }
-    return w;
-}
-
 template <int ORDER, int NV, bool EM, int DEP>
-__global__ __launch_bounds__(kBatchMaxThreads) void k_batch_pass_a(Batch b)
+__global__ __launch_bounds__(kBatchMaxThreads) __attribute__((amdgpu_waves_per_eu(kBatchWavesPerEU))) void k_batch_pass_a(Batch b)
 {
     extern __shared__ double smem[];
     __shared__ double red[kRedSize];
@@ -3019,15 +3133,15 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batch_pass_a(Batch b)
         const BatchRun br = uniform_load(b.runs + item.run);
         const Run &r = br.r;
         const Work wk = by_parity(br.wk, par);
-        pass_a_body<ORDER, NV, EM, DEP, kBatchUnroll<NV>>(r, wk, 0, step, b.X + br.poff,
+        pass_a_body<ORDER, NV, EM, DEP, kBatchUnroll<NV>>(r, (RunPtr)&b.runs[item.run].r, wk, step, b.X + br.poff,
                                                           b.V + br.poff, item.p0, item.p1,
-                                                          item.slot == 0, smem, red, &wctr);
+                                                          item.slot == 0, item.slot, smem, red, &wctr);
         lds_barrier();
     }
 }
 
 template <int ORDER, int NV, bool EM, bool PRED, int DEP>
-__global__ __launch_bounds__(kBatchMaxThreads) void k_batch_pass_b(Batch b)
+__global__ __launch_bounds__(kBatchMaxThreads) __attribute__((amdgpu_waves_per_eu(kBatchWavesPerEU))) void k_batch_pass_b(Batch b)
 {
     extern __shared__ double smem[];
     __shared__ double red[kRedSize];
@@ -3039,7 +3153,7 @@ __global__ __launch_bounds__(kBatchMaxThreads) void k_batch_pass_b(Batch b)
         const Run &r = br.r;
         const Work wk = by_parity(br.wk, par);
         pass_b_body<ORDER, NV, EM, PRED, DEP, kBatchUnroll<NV>>(
-            r, wk, 0, b.X + br.poff, b.V + br.poff, b.X + br.poff, b.V + br.poff, item.p0,
+            r, (RunPtr)&b.runs[item.run].r, wk, b.X + br.poff, b.V + br.poff, b.X + br.poff, b.V + br.poff, item.p0,
             item.p1, item.slot == 0, item.slot, smem, red, &wctr);
         lds_barrier();
     }
@@ -3055,12 +3169,11 @@ __global__ void k_batch_tick(Batch b)
 // One workgroup per run: newest record and fields into the caller's arrays.
 __global__ __launch_bounds__(1024) void k_batch_finish(Batch b)
 {
-    __shared__ double red[kRedSize];
     const int64_t step = *b.stepc;
     const BatchRun &br = b.runs[blockIdx.x];
     const Run r = uniform_copy(br.r);
     const Work wk = uniform_copy(br.wk);
-    finish_body(r, wk, (int)(step & 1), step, red);
+    finish_body(r, wk, (int)(step & 1), step);
 }
 
 template <int NV>

@@ -107,9 +107,9 @@ size_t tile_width(const pic_params *p) { return (size_t)p->n_cells + 2 * kGhost;
 size_t lds_pass_a_of(bool em, int order, size_t ng)
 {
     const size_t tw = ng + 2 * kGhost;
-    // EM: jt[3] | es[3] | bs[2] | side[3];  ES: jt | es | side | coefficients[order + 1]
+    // EM: jt[3] | es[3] | bs[2] | side[3];  ES: jt | es | side | eraw | coefficients[order + 1]
     return em ? (3 + 3 + 2 + 3) * tw * 8
-              : ((size_t)pic::coef_offset((int)(3 * tw)) + (order + 1) * tw) * 8;
+              : ((size_t)pic::coef_offset((int)(4 * tw)) + (order + 1) * tw) * 8;
 }
 
 size_t lds_pass_b_of(bool em, int order, size_t ng)

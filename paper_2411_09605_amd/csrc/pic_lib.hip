@@ -68,15 +68,15 @@ void launch_pass(pic_ctx *c, K kernel, uint32_t lds, A... args)
 template <int ORDER, int NV, bool EM, int DEP>
 void launch_a(pic_ctx *c, int par, int64_t step, const double *X, const double *V)
 {
-    launch_pass(c, k_pass_a<ORDER, NV, EM, DEP>, (uint32_t)lds_pass_a(&c->p), c->run, c->wk, par,
-                step, X, V);
+    launch_pass(c, k_pass_a<ORDER, NV, EM, DEP>, (uint32_t)lds_pass_a(&c->p), c->run,
+                by_parity(c->wk, par), step, X, V);
 }
 
 template <int ORDER, int NV, bool EM, bool PRED, int DEP>
 void launch_b(pic_ctx *c, int par, const double *X, const double *V)
 {
-    launch_pass(c, k_pass_b<ORDER, NV, EM, PRED, DEP>, (uint32_t)lds_pass_b(&c->p), c->run, c->wk,
-                par, X, V, c->b.x, c->b.v);
+    launch_pass(c, k_pass_b<ORDER, NV, EM, PRED, DEP>, (uint32_t)lds_pass_b(&c->p), c->run,
+                by_parity(c->wk, par), X, V, c->b.x, c->b.v);
 }
 
 template <int ORDER, int NV, bool EM>
@@ -128,10 +128,10 @@ template <int ORDER, int NV, int DEP>
 void launch_std_pass(pic_ctx *c, int64_t n, const double *X, const double *V)
 {
     const int par = (int)(n & 1);
-    Work wk = c->wk;
+    Work wk = by_parity(c->wk, par);
     wk.spart = spart_of(c, n);
     launch_pass(c, k_std_pass<ORDER, NV, DEP>,
-                (uint32_t)lds_std_pass_of(ORDER, (size_t)c->p.n_cells), c->run, wk, par, n, X, V,
+                (uint32_t)lds_std_pass_of(ORDER, (size_t)c->p.n_cells), c->run, wk, n, X, V,
                 c->b.x, c->b.v, c->wk.J2[par ^ 1], c->wk.J2[par], spart_of(c, n + 1));
 }
 
@@ -154,16 +154,16 @@ void launch_em_fields(pic_ctx *c, int par, int full)
     const int ng = c->p.n_cells;
     hipLaunchKernelGGL(k_em_fields, dim3((unsigned)((ng + kPsatdOut - 1) / kPsatdOut), full ? 6u : 4u),
                        dim3(kPsatdOut * kPsatdSeg), (uint32_t)lds_psatd_of((size_t)ng), c->stream,
-                       c->run, c->wk, par, full);
+                       c->run, by_parity(c->wk, par), full);
 }
 
 template <int ORDER, int NV, int DEP>
 void launch_esec1(pic_ctx *c, int64_t n, const double *X, const double *V)
 {
-    Work wk = c->wk;
+    Work wk = by_parity(c->wk, (int)(n & 1));
     wk.spart = spart_of(c, n);
     launch_pass(c, k_esec1<ORDER, NV, DEP>,
-                (uint32_t)lds_esec1_of(ORDER, (size_t)c->p.n_cells), c->run, wk, (int)(n & 1), n, X, V,
+                (uint32_t)lds_esec1_of(ORDER, (size_t)c->p.n_cells), c->run, wk, n, X, V,
                 c->b.x, c->b.v, (const double *)esec1_current(c, n), esec1_current(c, n + 1),
                 esec1_current(c, n + 2), spart_of(c, n + 1));
 }
@@ -298,6 +298,7 @@ void bind_run_work(const pic_params *p, const pic_buffers *b, const Layout &L, c
     r.L = p->length;
     r.h = p->length / p->n_cells;
     r.inv_h = p->n_cells / p->length;
+    r.inv_ng = 1.0 / p->n_cells;
     r.dt = p->dt;
     r.hdt = 0.5 * p->dt;
     r.c2 = p->c * p->c;
@@ -1337,6 +1338,7 @@ int pic_batch_init(const pic_batch_params *p, const pic_batch_buffers *b, void *
         R.L = q.length;
         R.h = q.length / q.n_cells;
         R.inv_h = q.n_cells / q.length;
+        R.inv_ng = 1.0 / q.n_cells;
         R.dt = q.dt;
         R.hdt = 0.5 * q.dt;
         R.c2 = q.c * q.c;
@@ -1649,7 +1651,7 @@ template <int ORDER>
 void adj_pass_a(pic_adj *c, int par, int64_t step, const double *X, const double *V)
 {
     hipLaunchKernelGGL((k_pass_a<ORDER, 1, false, 0>), dim3(c->run.nblocks), dim3(c->threads),
-                       lds_pass_a(&c->q), c->stream, c->run, c->wk, par, step, X, V);
+                       lds_pass_a(&c->q), c->stream, c->run, by_parity(c->wk, par), step, X, V);
 }
 
 // save: null, or where the lead workgroup copies the step's grids, E^n | j^{n,*} |
@@ -1659,10 +1661,10 @@ template <int ORDER>
 void adj_pass_b(pic_adj *c, int par, const double *X, const double *V, double *Xo, double *Vo,
                 double *save = nullptr)
 {
-    Work wk = c->wk;
+    Work wk = by_parity(c->wk, par);
     wk.grid_save = save;
     hipLaunchKernelGGL((k_pass_b<ORDER, 1, false, true, 0>), dim3(c->run.nblocks), dim3(c->threads),
-                       lds_pass_b(&c->q), c->stream, c->run, wk, par, X, V, Xo, Vo);
+                       lds_pass_b(&c->q), c->stream, c->run, wk, X, V, Xo, Vo);
 }
 
 // Recompute of step n of the forward run from its state (X, V) into (Xo, Vo) in one
@@ -1676,14 +1678,14 @@ void adj_recompute(pic_adj *c, hipStream_t stream, int par, const double *g, con
 {
     Run r = c->run;
     r.nrep = 1;
-    Work wk = c->wk;
+    Work wk = by_parity(c->wk, par);
     const int ng = c->p.n_cells;
-    wk.Ef[par] = const_cast<double *>(g);
-    wk.J1[par] = const_cast<double *>(g) + ng;
-    wk.J2[par] = const_cast<double *>(g) + 2 * ng;
+    wk.Ef[0] = const_cast<double *>(g);
+    wk.J1[0] = const_cast<double *>(g) + ng;
+    wk.J2[0] = const_cast<double *>(g) + 2 * ng;
     wk.grid_save = nullptr;
     hipLaunchKernelGGL((k_pass_b<ORDER, 1, false, false, 0>), dim3(c->run.nblocks), dim3(c->threads),
-                       lds_pass_b(&c->q), stream, r, wk, par, X, V, Xo, Vo);
+                       lds_pass_b(&c->q), stream, r, wk, X, V, Xo, Vo);
 }
 
 template <int ORDER>
