@@ -36,8 +36,8 @@ namespace pic {
 
 // Particles whose loads each thread issues together before computing on them, per pass
 // (more loads in flight against fewer waves per SIMD from the extra registers).
-template <int NV> constexpr int kUnrollA = 2;
-template <int NV> constexpr int kUnrollB = 2;
+template <int NV> constexpr int kUnrollA = NV == 1 ? 2 : 1;
+template <int NV> constexpr int kUnrollB = NV == 1 ? 2 : 1;
 // Minimum wavefronts per SIMD the particle passes are compiled for: one 1024-thread
 // workgroup per CU is 4 per SIMD (at most 128 VGPRs); 1D-3V keeps its registers.
 template <int NV> constexpr int kWavesPerEU = NV == 1 ? 4 : 1;
@@ -213,9 +213,13 @@ template <int U> struct WaveBatches {
             k += (int)(nthreads() >> 6);
             return order(origin + (int64_t)k * step);
         }
+        // (an address the compiler takes to differ by lane keeps it from wrapping the one
+        // lane's atomic in a wavefront-wide sum)
         int kc = 0;
+        unsigned zero = 0;
+        asm("" : "+v"(zero));
         if ((threadIdx.x & 63) == 0)
-            kc = atomicAdd(ctr, 1);
+            kc = atomicAdd(ctr + zero, 1);
         return order(origin + (int64_t)__builtin_amdgcn_readlane(kc, 0) * step);
     }
 };
@@ -325,21 +329,135 @@ template <int ORDER> struct Cell {
     double d;
 };
 
-template <int ORDER> __device__ __forceinline__ Cell<ORDER> cell_of(double xi, int ng)
+// The particle loops treat the U particles of a lane together, stage by stage, so that their
+// dependent chains overlap (a pass on few particles has one wavefront per SIMD and nothing
+// else to issue) and the rare cases (a stencil beyond the ghost band, a wrap, a large
+// correction) cost one test per stage: a branch the whole wavefront takes or not.
+
+// Slots of the first nodes of stencils that start at node first[u] (see Slots).
+template <int ORDER, int U>
+__device__ __forceinline__ void slot_bases(int (&b)[U], const int (&first)[U], int ng)
 {
-    const double f = floor(ORDER == 2 ? xi + 0.5 : xi);
-    Cell<ORDER> c;
-    c.d = xi - f;
+    const unsigned lim = (unsigned)(ng + 2 * kGhost - ORDER - 1);
+    bool out = false;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        b[u] = (int)((unsigned)first[u] + kGhost);
+        out |= (unsigned)b[u] > lim;
+    }
+    if (__any(out)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if ((unsigned)b[u] > lim)
+                b[u] = wrap_node(first[u], ng) + kGhost;
+    }
+}
+
+// Where a particle sits on the grid: its node (the nearest one for the quadratic shape, the
+// lower one for the tent) and the offset from it, both of the coordinate s scale - shift.
+// Adding 1.5 2^52 rounds to the nearest integer and leaves it in the sum's low bits, so
+// neither the coordinate itself nor a conversion is needed.  (A tie may round to either node;
+// the spline's two pieces agree there.  The low bits of a coordinate beyond 2^31, or of one that
+// is not finite, are some integer, which slot_bases puts inside the tile.)
+constexpr double kRoundMagic = 6755399441055744.0;   // 1.5 * 2^52
+struct Pos {
+    int i;
+    double d;
+};
+
+template <int ORDER> __device__ __forceinline__ Pos locate(double s, double scale, double shift)
+{
+    Pos p;
+    if constexpr (ORDER == 2) {
+        const double t = fma(s, scale, kRoundMagic);   // (shift is 0: half-node grids use tents)
+        p.i = __double2loint(t);
+        p.d = fma(s, scale, -(t - kRoundMagic));
+    } else {
+        const double xi = fma(s, scale, -shift), f = floor(xi);
+        p.i = __double2loint(f + kRoundMagic);
+        p.d = xi - f;
+    }
+    return p;
+}
+
+// The same particle on the half nodes (i + 1/2).
+template <int ORDER> __device__ __forceinline__ Pos half_node(const Pos &p)
+{
+    Pos o;
+    if constexpr (ORDER == 2) {
+        // nearest half node: i or i - 1 by the sign of the offset
+        o.d = p.d - __builtin_copysign(0.5, p.d);
+        o.i = p.i + (__double2hiint(p.d) >> 31);
+    } else {
+        const bool low = p.d < 0.5;
+        o.d = low ? p.d + 0.5 : p.d - 0.5;
+        o.i = low ? p.i - 1 : p.i;
+    }
+    return o;
+}
+
+// The stencil of a particle (the weights of stencil<ORDER> from its offset).
+template <int ORDER> __device__ __forceinline__ Stencil<ORDER> stencil_at(const Pos &p)
+{
     Stencil<ORDER> s;
-    s.first = (int)f - (ORDER == 2 ? 1 : 0);
-    c.base = slots_of<ORDER>(s, ng).n[0];
-    return c;
+    if constexpr (ORDER == 2) {
+        const double hd = 0.5 * p.d, t = fma(hd, p.d, 0.125);
+        s.first = p.i - 1;
+        s.w[0] = t - hd;
+        s.w[1] = fma(-p.d, p.d, 0.75);
+        s.w[2] = t + hd;
+    } else {
+        s.first = p.i;
+        s.w[0] = 1.0 - p.d;
+        s.w[1] = p.d;
+    }
+    return s;
+}
+
+template <int ORDER, int U>
+__device__ __forceinline__ void cells_at(Cell<ORDER> (&c)[U], const Pos (&p)[U], int ng)
+{
+    int first[U], b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        c[u].d = p[u].d;
+        first[u] = p[u].i - (ORDER == 2 ? 1 : 0);
+    }
+    slot_bases<ORDER, U>(b, first, ng);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        c[u].base = b[u];
+}
+
+// Stencils of the particles and the slots of their first nodes.
+template <int ORDER, int U>
+__device__ __forceinline__ void stencils_at(Stencil<ORDER> (&st)[U], int (&b)[U], const Pos (&p)[U],
+                                            int ng)
+{
+    int first[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        st[u] = stencil_at<ORDER>(p[u]);
+        first[u] = st[u].first;
+    }
+    slot_bases<ORDER, U>(b, first, ng);
+}
+
+template <int ORDER>
+__device__ __forceinline__ double gather_at(const double *tile, const Stencil<ORDER> &s, int base)
+{
+    double acc = 0.0;
+#pragma unroll
+    for (int k = 0; k <= ORDER; ++k)
+        acc = fma(tile[base + k], s.w[k], acc);
+    return acc;
 }
 
 template <int ORDER>
 __device__ __forceinline__ double gather_poly(const double *ct, const Cell<ORDER> &c)
 {
-    const double *k = ct + (ORDER + 1) * c.base;
+    // (base is a slot number: the 24-bit product runs at full rate, the 64-bit one does not)
+    const double *k = ct + __umul24((unsigned)c.base, ORDER + 1);
     if constexpr (ORDER == 1)
         return fma(c.d, k[1], k[0]);
     else
@@ -419,10 +537,13 @@ template <int ORDER, int NC, int DEP> struct Depo;
 constexpr double kFxMagic = 6755399441055744.0;   // 1.5 * 2^52
 constexpr int kFxCoarse = 12;
 
-__device__ __forceinline__ long long fx_round(double v)
+// The integer that v + kFxMagic (rounded) holds.
+__device__ __forceinline__ long long fx_round_of(double sum)
 {
-    return __double_as_longlong(v + kFxMagic) - __double_as_longlong(kFxMagic);
+    return __double_as_longlong(sum) - __double_as_longlong(kFxMagic);
 }
+
+__device__ __forceinline__ long long fx_round(double v) { return fx_round_of(v + kFxMagic); }
 
 template <int ORDER, int NC> struct Depo<ORDER, NC, 0> {
     double *side;
@@ -480,6 +601,42 @@ template <int ORDER, int NC> struct Depo<ORDER, NC, 0> {
                 }
             }
         }
+    }
+    // The contributions of a lane's U particles: straight to the tile unless one of the
+    // wavefront's is out of range.
+    template <int U>
+    __device__ __forceinline__ void add_all(double *jt, int tw, int ng, const Pos (&p)[U],
+                                            const double (&q)[U][NC], const bool (&valid)[U])
+    {
+        Stencil<ORDER> st[U];
+        int b[U];
+        stencils_at<ORDER, U>(st, b, p, ng);
+        double qs[U][NC];
+        bool out = false;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                qs[u][c] = q[u][c] * scale;
+                out |= !(fabs(qs[u][c]) < lim);     // (lanes past the end carry no weight)
+            }
+        if (__any(out)) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (valid[u])
+                    add(jt, tw, ng, st[u], q[u]);
+            return;
+        }
+        unsigned long long *ti = reinterpret_cast<unsigned long long *>(jt);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (valid[u])
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+#pragma unroll
+                    for (int k = 0; k <= ORDER; ++k)
+                        atomicAdd(&ti[c * tw + b[u] + k],
+                                  (unsigned long long)fx_round_of(fma(qs[u][c], st[u].w[k], kFxMagic)));
     }
     __device__ __forceinline__ void finish(double *, int, int) {}
     // Tile slot `idx` as a double: the integer sum times 2^-S plus the side tile.
@@ -730,6 +887,22 @@ template <int ORDER, int NC> struct Depo<ORDER, NC, 2> {
     __device__ __forceinline__ void finish(double *jt, int tw, int ng) { flush(jt, tw, ng); }
 };
 
+// A lane's U particles into any kind of accumulator (Depo<., ., 2> wants every lane).
+template <int ORDER, int NC, int DEP, int U>
+__device__ __forceinline__ void deposit_all(Depo<ORDER, NC, DEP> &dep, double *jt, int tw, int ng,
+                                            const Pos (&p)[U], const double (&q)[U][NC],
+                                            const bool (&valid)[U])
+{
+    if constexpr (DEP == 0) {
+        dep.template add_all<U>(jt, tw, ng, p, q, valid);
+    } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (DEP == 2 || valid[u])
+                dep.add(jt, tw, ng, stencil_at<ORDER>(p[u]), q[u], valid[u], u == 0);
+    }
+}
+
 // Periodic position in [0, L).  A particle moves less than a period per step, so one
 // conditional add or subtract almost always suffices; otherwise x - L floor(x / L),
 // with rounding that lands on L mapped to 0.
@@ -749,6 +922,34 @@ __device__ __forceinline__ double wrap_pos(double x, double L)
     return x;
 }
 
+// The passes' periodic positions: x1 - L floor(x1 / L) in one rounding, which is x1, x1 + L
+// or x1 - L for a particle that moved less than a period; what lands outside [0, L) by the
+// rounding of x1 / L (or is not finite) goes through wrap_pos.
+template <int U>
+__device__ __forceinline__ void wrap_all(double (&xw)[U], const double (&x1)[U], const Run &r)
+{
+    bool out = false;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        xw[u] = fma(-r.L, floor(x1[u] * r.inv_L), x1[u]);
+        out |= !(xw[u] >= 0.0 && xw[u] < r.L);
+    }
+    if (__any(out)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (!(xw[u] >= 0.0 && xw[u] < r.L))
+                xw[u] = wrap_pos(x1[u], r.L);
+    }
+}
+
+__device__ __forceinline__ double wrap_one(double x1, const Run &r)
+{
+    const double in[1] = {x1};
+    double xw[1];
+    wrap_all<1>(xw, in, r);
+    return xw[0];
+}
+
 // Exact charge conservation (section 3.5; Run::cc; tent shapes): the centred current and
 // v-dagger's field go through the pieces of the particle's path x0 -> x1 (x0 wrapped, as
 // stored; x1 unwrapped) between the half nodes, where the tent has its kinks.  In
@@ -766,10 +967,9 @@ __device__ __forceinline__ void cc_pieces(const Run &r, double x0, double x1, F 
 {
     const double ua = x0 * r.inv_h - 0.5;
     const double base = floor(ua);
-    const double xw = wrap_pos(x1, r.L);
-    // whole periods between x1 and xw (x1 - xw is a multiple of L up to rounding, so the
-    // reciprocal of L, inv_h / N_g, serves)
-    const double m = rint((x1 - xw) * (r.inv_h / (double)r.ng));
+    const double xw = wrap_one(x1, r);
+    // whole periods between x1 and xw (x1 - xw is a multiple of L up to rounding)
+    const double m = rint((x1 - xw) * r.inv_L);
     const double ta = ua - base;
     const double tb = (xw * r.inv_h - 0.5) + (m * (double)r.ng - base);
     const double lo = fmin(ta, tb), hi = fmax(ta, tb), len = hi - lo;
@@ -1414,32 +1614,64 @@ template <int NV, bool EM> struct TileSizes {
     static constexpr int ncur = EM ? 3 : 1;    // current components deposited
 };
 
-// The particle's half-step quantities, computed identically in both passes.
-template <int ORDER, int NV, bool EM> struct Half {
-    double vs[NV];       // v*
-    double x1;           // x^{n+1} (unwrapped)
-    double xh;           // x^{n+1/2}
-};
-
 // Gamma = sqrt(r), r = 1 + rho, rho = num2 / den with num2 = 2 num (eq. (opt_solution));
 // r < 0 or a non-finite r (e.g. den = 0) takes the fallback Gamma = 1 and is counted.
-// Because Gamma - 1 is tiny for almost every particle (O(dt^4) for ESEC2), the common
-// case |rho| < 1e-4 evaluates rho with the hardware reciprocal refined by one Newton step
-// (relative error about 2^-46, so below 1e-18 in Gamma) and sqrt(1 + rho) by its Taylor
-// series through rho^4 (truncation below 3e-22); any other rho is evaluated with an IEEE
-// division and square root.
-__device__ __forceinline__ double gamma_factor(double num2, double den, int &fallbacks)
+// Gamma - 1 is tiny for almost every particle (O(dt^4) for ESEC2): |rho| < 1e-4 evaluates
+// rho with the hardware reciprocal refined by one Newton step (relative error about 2^-46,
+// so below 1e-18 in Gamma) and sqrt(1 + rho) by its Taylor series through rho^4 (truncation
+// below 3e-22).  A wavefront that holds any other rho (slow particles: half of the
+// wavefronts of a thermal plasma) takes the square root of r = 1 + num2 / den as well, with
+// the quotient and the root corrected to their last bit by one more Newton step each
+// (methods of Goldschmidt and Markstein); a den below the range of the reciprocal's steps
+// divides instead.
+template <int NV, int U>
+__device__ __forceinline__ void gamma_all(double (&g)[U], const double (&vs)[U][NV],
+                                          const double (&vd)[U][NV], const double (&v)[U][NV],
+                                          const bool (&valid)[U], int &fallbacks)
 {
-    double rc = __builtin_amdgcn_rcp(den);
-    rc = fma(rc, fma(-den, rc, 1.0), rc);
-    const double rho = num2 * rc;
-    if (fabs(rho) < 1e-4)
-        return fma(rho, fma(rho, fma(rho, fma(rho, -0.0390625, 0.0625), -0.125), 0.5), 1.0);
-    const double rr = 1.0 + num2 / den;
-    if (rr >= 0.0 && isfinite(rr))
-        return sqrt(rr);
-    ++fallbacks;
-    return 1.0;
+    // num2 = 2 num = sum (2 v* - (v-dagger + v)) . (v-dagger - v)
+    double num2[U], den[U], rc[U], rho[U];
+    bool large[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        num2[u] = 0.0;
+        den[u] = 0.0;
+#pragma unroll
+        for (int c = 0; c < NV; ++c) {
+            const double a2 = fma(2.0, vs[u][c], -(vd[u][c] + v[u][c]));
+            num2[u] = fma(a2, vd[u][c] - v[u][c], num2[u]);
+            den[u] = fma(vd[u][c], vd[u][c], den[u]);
+        }
+        const double y = __builtin_amdgcn_rcp(den[u]);
+        rc[u] = fma(y, fma(-den[u], y, 1.0), y);
+        rho[u] = num2[u] * rc[u];
+        large[u] = !(fabs(rho[u]) < 1e-4);
+        g[u] = fma(rho[u], fma(rho[u], fma(rho[u], fma(rho[u], -0.0390625, 0.0625), -0.125), 0.5), 1.0);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (__any(large[u])) {
+            const double y = fma(rc[u], fma(-den[u], rc[u], 1.0), rc[u]);
+            double quo = num2[u] * y;
+            quo = fma(fma(-quo, den[u], num2[u]), y, quo);
+            if (__any(large[u] && den[u] < 1e-280)) {
+                asm volatile("");      // (not to be computed beside the usual quotient)
+                quo = den[u] < 1e-280 ? num2[u] / den[u] : quo;
+            }
+            const double rr = 1.0 + quo;
+            const double s = __builtin_amdgcn_rsq(rr);
+            double root = rr * s, half = 0.5 * s;
+            const double e = fma(-half, root, 0.5);
+            root = fma(root, e, root);
+            half = fma(half, e, half);
+            root = fma(fma(-root, root, rr), half, root);
+            root = rr > 0.0 ? root : 0.0;
+            const bool ok = rr >= 0.0 && isfinite(rr);
+            if (large[u]) {
+                g[u] = ok ? root : 1.0;
+                fallbacks += (!ok && valid[u]) ? 1 : 0;
+            }
+        }
 }
 
 // v* solves v* = u + v* x t with u = v^n + dt/2 E**, t = dt/2 B** (eq. (good_translation)
@@ -1454,42 +1686,103 @@ __device__ __forceinline__ void rotate_half(const double u[3], const double t[3]
     o[2] = (u[2] + (u[0] * t[1] - u[1] * t[0]) + ut * t[2]) * inv;
 }
 
+// v* and x^{n+1} (unwrapped) of a lane's particles, computed identically in both passes.
 // tiles: EM: es[3][tw] predictor E, bs[2][tw] predictor B, ghost-padded; ES: es is the
 // coefficient tile of E_x (coef_fill)
-template <int ORDER, int NV, bool EM>
-__device__ __forceinline__ Half<ORDER, NV, EM> half_step(const Run &r, double x, const double v[NV],
-                                                        const double *es, const double *bs)
+template <int ORDER, int NV, bool EM, int U>
+__device__ __forceinline__ void half_steps(const Run &r, const double (&x)[U], const double (&v)[U][NV],
+                                           const double *es, const double *bs, double (&vs)[U][NV],
+                                           double (&x1)[U])
 {
-    Half<ORDER, NV, EM> o;
-    const double xs = fma(r.hdt, v[0], x);
-    if constexpr (NV == 1) {
-        o.vs[0] = fma(r.hdt, gather_poly<ORDER>(es, cell_of<ORDER>(xs * r.inv_h - r.xshift, r.ng)), v[0]);
-    } else {
-        double u[3], t[3];
-        if constexpr (EM) {
-            const Stencil<ORDER> s = stencil<ORDER>(xs * r.inv_h);
-            const Slots<ORDER> n = slots_of<ORDER>(s, r.ng);
-            u[0] = fma(r.hdt, gather1<ORDER>(es, s, n), v[0]);
-            u[1] = fma(r.hdt, gather1<ORDER>(es + r.tw, s, n), v[1]);
-            u[2] = fma(r.hdt, gather1<ORDER>(es + 2 * r.tw, s, n), v[2]);
-            const Stencil<ORDER> sh = stencil<ORDER>(xs * r.inv_h - 0.5);
-            const Slots<ORDER> nh = slots_of<ORDER>(sh, r.ng);
+    Pos p[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        p[u] = locate<ORDER>(fma(r.hdt, v[u][0], x[u]), r.inv_h, r.xshift);     // x*
+    if constexpr (EM) {
+        Stencil<ORDER> s[U], sh[U];
+        int n[U], nh[U];
+        stencils_at<ORDER, U>(s, n, p, r.ng);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            p[u] = half_node<ORDER>(p[u]);
+        stencils_at<ORDER, U>(sh, nh, p, r.ng);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            double a[3], t[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                a[c] = fma(r.hdt, gather_at<ORDER>(es + c * r.tw, s[u], n[u]), v[u][c]);
             t[0] = r.hdt * r.bext[0];
-            t[1] = r.hdt * (r.bext[1] + gather1<ORDER>(bs, sh, nh));
-            t[2] = r.hdt * (r.bext[2] + gather1<ORDER>(bs + r.tw, sh, nh));
-        } else {
-            u[0] = fma(r.hdt, gather_poly<ORDER>(es, cell_of<ORDER>(xs * r.inv_h - r.xshift, r.ng)), v[0]);
-            u[1] = v[1];
-            u[2] = v[2];
-            t[0] = r.hdt * r.bext[0];
-            t[1] = r.hdt * r.bext[1];
-            t[2] = r.hdt * r.bext[2];
+            t[1] = r.hdt * (r.bext[1] + gather_at<ORDER>(bs, sh[u], nh[u]));
+            t[2] = r.hdt * (r.bext[2] + gather_at<ORDER>(bs + r.tw, sh[u], nh[u]));
+            rotate_half(a, t, vs[u]);
         }
-        rotate_half(u, t, o.vs);
+    } else {
+        Cell<ORDER> c[U];
+        cells_at<ORDER, U>(c, p, r.ng);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const double a0 = fma(r.hdt, gather_poly<ORDER>(es, c[u]), v[u][0]);
+            if constexpr (NV == 1) {
+                vs[u][0] = a0;
+            } else {
+                const double a[3] = {a0, v[u][1], v[u][2]};
+                const double t[3] = {r.hdt * r.bext[0], r.hdt * r.bext[1], r.hdt * r.bext[2]};
+                rotate_half(a, t, vs[u]);
+            }
+        }
     }
-    o.x1 = fma(r.dt, o.vs[0], x);
-    o.xh = 0.5 * (x + o.x1);
-    return o;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        x1[u] = fma(r.dt, vs[u][0], x[u]);
+}
+
+// x^{n+1/2} = (x^n + x^{n+1}) / 2 on the nodes (hinv_h = 1 / 2h).
+template <int ORDER, int U>
+__device__ __forceinline__ void mid_points(Pos (&p)[U], const double (&x)[U], const double (&x1)[U],
+                                           const Run &r)
+{
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        p[u] = locate<ORDER>(x[u] + x1[u], r.hinv_h, 0.0);
+}
+
+// v-dagger of an electrostatic particle from E-bar at x^{n+1/2} (eq. (good_translation)).
+template <int NV>
+__device__ __forceinline__ void dagger_es(double (&vd)[NV], const double (&v)[NV], const double (&vs)[NV],
+                                          double e, const Run &r)
+{
+    if constexpr (NV == 1) {
+        vd[0] = fma(r.dt, e, v[0]);
+    } else {
+        const double *b = r.bext;
+        vd[0] = v[0] + r.dt * (e + (vs[1] * b[2] - vs[2] * b[1]));
+        vd[1] = v[1] + r.dt * (vs[2] * b[0] - vs[0] * b[2]);
+        vd[2] = v[2] + r.dt * (vs[0] * b[1] - vs[1] * b[0]);
+    }
+}
+
+// A lane's new state of a pass that starts at particle b0 of its batch, and its scalars.
+// The state is written through to memory (system-scope relaxed stores): nothing in the
+// pass reads it back, and lines left dirty in the L2 of each XCD would be written back at
+// the end of the kernel.  A non-finite state makes the kinetic energy non-finite, which is
+// where the passes look for one.
+template <int NV, int U>
+__device__ __forceinline__ void store_all(const double (&xw)[U], const double (&vn)[U][NV],
+                                          const bool (&valid)[U], double *Xo, double *Vo, int64_t b0,
+                                          int64_t vstride)
+{
+    const unsigned lane = threadIdx.x & 63;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (valid[u]) {
+            const unsigned o = lane + 64u * u;
+#pragma unroll
+            for (int c = 0; c < NV; ++c)
+                __hip_atomic_store(&(Vo + c * vstride + b0)[o], vn[u][c], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(&(Xo + b0)[o], xw[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
 }
 
 // Pass A of step n.  The passes take the run's arrays with those of the step's parity at
@@ -1580,35 +1873,44 @@ __device__ __forceinline__ void pass_a_body(const Run &r0, RunPtr rp, const Work
         double w[U];
         load_weights(w, q.w, q.wu, bcur, p1);
         load_batch(nxt, X, V, q.vstride, bnxt, p1);   // the last one is discarded
+        bool valid[U];
+        // lanes past the end repeat the last particle, without weight
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const bool valid = lane + 64u * u < nval;
-            if constexpr (DEP != 2) {
-                if (!valid)
-                    break;
-            }
-            const Half<ORDER, NV, EM> hs = half_step<ORDER, NV, EM>(q, cur.x[u], cur.v[u], eg, bs);
-            const double qw = valid ? w[u] * q.qs : 0.0;
-            double qv[T::ncur];
+            valid[u] = lane + 64u * u < nval;
+            w[u] = valid[u] ? w[u] : 0.0;
+        }
+        double vs[U][NV], x1[U];
+        half_steps<ORDER, NV, EM, U>(q, cur.x, cur.v, eg, bs, vs, x1);
+        double qv[U][T::ncur];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const double qw = w[u] * q.qs;
 #pragma unroll
             for (int c = 0; c < T::ncur; ++c)
-                qv[c] = qw * hs.vs[c];
-            bool done = false;
-            if constexpr (!EM && ORDER == 1 && DEP != 2) {
-                if (q.cc) {
-                    // exact charge conservation: through the pieces of the path x^n -> x^{n+1}
-                    cc_pieces(q, cur.x[u], hs.x1, [&](double base, double t, double f) {
-                        double qf[T::ncur];
+                qv[u][c] = qw * vs[u][c];
+        }
+        bool done = false;
+        if constexpr (!EM && ORDER == 1 && DEP != 2) {
+            if (q.cc) {
+                // exact charge conservation: through the pieces of the path x^n -> x^{n+1}
 #pragma unroll
-                        for (int c = 0; c < T::ncur; ++c)
-                            qf[c] = qv[c] * f;
-                        dep.add(jt, tw, ng, cc_stencil(base, t), qf, valid, false);
-                    });
-                    done = true;
-                }
+                for (int u = 0; u < U; ++u)
+                    if (valid[u])
+                        cc_pieces(q, cur.x[u], x1[u], [&](double base, double t, double f) {
+                            double qf[T::ncur];
+#pragma unroll
+                            for (int c = 0; c < T::ncur; ++c)
+                                qf[c] = qv[u][c] * f;
+                            dep.add(jt, tw, ng, cc_stencil(base, t), qf, true, false);
+                        });
+                done = true;
             }
-            if (!done)
-                dep.add(jt, tw, ng, stencil<ORDER>(hs.xh * q.inv_h), qv, valid, u == 0);
+        }
+        if (!done) {
+            Pos pos[U];
+            mid_points<ORDER, U>(pos, cur.x, x1, q);
+            deposit_all<ORDER, T::ncur, DEP, U>(dep, jt, tw, ng, pos, qv, valid);
         }
         cur = nxt;
         bcur = bnxt;
@@ -1793,7 +2095,7 @@ __device__ __forceinline__ void pass_b_body(const Run &r0, RunPtr rp, const Work
     lds_barrier();
 
     double ke = 0.0, gdev = 0.0;
-    int fb = 0, nonfinite = 0;
+    int fb = 0;
     const Run q = reload(rp);
     dep.settle();
     while (bcur < p1) {
@@ -1802,103 +2104,94 @@ __device__ __forceinline__ void pass_b_body(const Run &r0, RunPtr rp, const Work
         double w[U];
         load_weights(w, q.w, q.wu, bcur, p1);
         load_batch(nxt, X, V, q.vstride, bnxt, p1);   // the last one is discarded
-        double *Xob = Xo + bcur;
+        bool valid[U];
+        // lanes past the end repeat the last particle, without weight
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const unsigned o = lane + 64u * u;
-            const bool valid = o < nval;
-            if constexpr (DEP != 2) {
-                if (!valid)
-                    break;
-            }
-            const double *v = cur.v[u];
-            const Half<ORDER, NV, EM> hs = half_step<ORDER, NV, EM>(q, cur.x[u], v, eg, bs);
-            double vd[NV];
-            if constexpr (NV == 1) {
-                double eb1;
-                if constexpr (ORDER == 1)
-                    eb1 = q.cc ? cc_gather(q, ctb, cur.x[u], hs.x1)
-                               : gather_poly<ORDER>(ctb, cell_of<ORDER>(hs.xh * q.inv_h, ng));
-                else
-                    eb1 = gather_poly<ORDER>(ctb, cell_of<ORDER>(hs.xh * q.inv_h, ng));
-                vd[0] = fma(q.dt, eb1, v[0]);
-            } else {
-                double e[3], b[3];
-                b[0] = q.bext[0];
-                if constexpr (EM) {
-                    const Stencil<ORDER> s = stencil<ORDER>(hs.xh * q.inv_h);
-                    const Slots<ORDER> n = slots_of<ORDER>(s, ng);
-                    e[0] = gather1<ORDER>(eb, s, n);
-                    e[1] = gather1<ORDER>(eb + tw, s, n);
-                    e[2] = gather1<ORDER>(eb + 2 * tw, s, n);
-                    const Stencil<ORDER> sh = stencil<ORDER>(hs.xh * q.inv_h - 0.5);
-                    const Slots<ORDER> nh = slots_of<ORDER>(sh, ng);
-                    b[1] = q.bext[1] + gather1<ORDER>(bb, sh, nh);
-                    b[2] = q.bext[2] + gather1<ORDER>(bb + tw, sh, nh);
-                } else {
-                    if constexpr (ORDER == 1)
-                        e[0] = q.cc ? cc_gather(q, ctb, cur.x[u], hs.x1)
-                                    : gather_poly<ORDER>(ctb, cell_of<ORDER>(hs.xh * q.inv_h, ng));
-                    else
-                        e[0] = gather_poly<ORDER>(ctb, cell_of<ORDER>(hs.xh * q.inv_h, ng));
-                    e[1] = 0.0;
-                    e[2] = 0.0;
-                    b[1] = q.bext[1];
-                    b[2] = q.bext[2];
-                }
+            valid[u] = lane + 64u * u < nval;
+            w[u] = valid[u] ? w[u] : 0.0;
+        }
+        double vs[U][NV], x1[U], vd[U][NV];
+        Pos pos[U];
+        half_steps<ORDER, NV, EM, U>(q, cur.x, cur.v, eg, bs, vs, x1);
+        mid_points<ORDER, U>(pos, cur.x, x1, q);
+        if constexpr (EM) {
+            Stencil<ORDER> s[U], sh[U];
+            int n[U], nh[U];
+            stencils_at<ORDER, U>(s, n, pos, ng);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                pos[u] = half_node<ORDER>(pos[u]);
+            stencils_at<ORDER, U>(sh, nh, pos, ng);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
                 // v-dagger = v^n + dt (E-bar + v* x B-bar)   (eq. (good_translation), (EMbasic))
-                vd[0] = v[0] + q.dt * (e[0] + (hs.vs[1] * b[2] - hs.vs[2] * b[1]));
-                vd[1] = v[1] + q.dt * (e[1] + (hs.vs[2] * b[0] - hs.vs[0] * b[2]));
-                vd[2] = v[2] + q.dt * (e[2] + (hs.vs[0] * b[1] - hs.vs[1] * b[0]));
+                const double e[3] = {gather_at<ORDER>(eb, s[u], n[u]), gather_at<ORDER>(eb + tw, s[u], n[u]),
+                                     gather_at<ORDER>(eb + 2 * tw, s[u], n[u])};
+                const double b[3] = {q.bext[0], q.bext[1] + gather_at<ORDER>(bb, sh[u], nh[u]),
+                                     q.bext[2] + gather_at<ORDER>(bb + tw, sh[u], nh[u])};
+                const double *v = cur.v[u], *a = vs[u];
+                vd[u][0] = v[0] + q.dt * (e[0] + (a[1] * b[2] - a[2] * b[1]));
+                vd[u][1] = v[1] + q.dt * (e[1] + (a[2] * b[0] - a[0] * b[2]));
+                vd[u][2] = v[2] + q.dt * (e[2] + (a[0] * b[1] - a[1] * b[0]));
             }
-            // Gamma (eq. (opt_solution)); an imaginary or undefined root falls back to 1.
-            // num2 = 2 num = sum (2 v* - (v-dagger + v)) . (v-dagger - v)
-            double num2 = 0.0, den = 0.0;
+        } else {
+            double e[U];
+            bool done = false;
+            if constexpr (ORDER == 1) {
+                if (q.cc) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        e[u] = cc_gather(q, ctb, cur.x[u], x1[u]);
+                    done = true;
+                }
+            }
+            if (!done) {
+                Cell<ORDER> c[U];
+                cells_at<ORDER, U>(c, pos, ng);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    e[u] = gather_poly<ORDER>(ctb, c[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                dagger_es<NV>(vd[u], cur.v[u], vs[u], e[u], q);
+        }
+        // Gamma (eq. (opt_solution)); an imaginary or undefined root falls back to 1
+        double g[U], vn[U][NV], xw[U], v2[U];
+        gamma_all<NV, U>(g, vs, vd, cur.v, valid, fb);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            v2[u] = 0.0;
 #pragma unroll
             for (int c = 0; c < NV; ++c) {
-                const double a2 = fma(2.0, hs.vs[c], -(vd[c] + v[c]));
-                num2 = fma(a2, vd[c] - v[c], num2);
-                den = fma(vd[c], vd[c], den);
+                vn[u][c] = g[u] * vd[u][c];
+                v2[u] = fma(vn[u][c], vn[u][c], v2[u]);
             }
-            int fbp = 0;
-            const double g = gamma_factor(num2, den, fbp);
-            double vn[NV];
-            double v2 = 0.0;
+        }
+        wrap_all<U>(xw, x1, q);
+        store_all<NV, U>(xw, vn, valid, Xo, Vo, bcur, q.vstride);
 #pragma unroll
-            for (int c = 0; c < NV; ++c) {
-                vn[c] = g * vd[c];
-                v2 = fma(vn[c], vn[c], v2);
-            }
-            const double xw = wrap_pos(hs.x1, q.L);
-            const double wp = valid ? w[u] : 0.0;
-            if (valid) {
-                // the new state is written through to memory (system-scope relaxed stores):
-                // nothing in this pass reads it back, and lines left dirty in the L2 of each
-                // XCD would be written back at the end of the kernel
+        for (int u = 0; u < U; ++u) {
+            gdev = fmax(gdev, fabs(g[u] - 1.0));
+            ke = fma(w[u], v2[u], ke);
+        }
+        if constexpr (PRED) {
+            double qv[U][T::ncur];
 #pragma unroll
-                for (int c = 0; c < NV; ++c)
-                    __hip_atomic_store(&(Vo + c * q.vstride + bcur)[o], vn[c], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_SYSTEM);
-                __hip_atomic_store(&Xob[o], xw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                fb += fbp;
-                gdev = fmax(gdev, fabs(g - 1.0));
-                ke = fma(wp, v2, ke);
-                if (!isfinite(v2) || !isfinite(hs.x1))
-                    nonfinite = 1;
-            }
-            if constexpr (PRED) {
-                const double qw = wp * q.qs;
-                double qv[T::ncur];
+            for (int u = 0; u < U; ++u) {
+                const double qw = w[u] * q.qs;
 #pragma unroll
                 for (int c = 0; c < T::ncur; ++c)
-                    qv[c] = qw * vn[c];
-                dep.add(jt, tw, ng, stencil<ORDER>(fma(q.hdt, vn[0], xw) * q.inv_h - q.xshift), qv, valid,
-                        u == 0);
+                    qv[u][c] = qw * vn[u][c];
+                pos[u] = locate<ORDER>(fma(q.hdt, vn[u][0], xw[u]), q.inv_h, q.xshift);
             }
+            deposit_all<ORDER, T::ncur, DEP, U>(dep, jt, tw, ng, pos, qv, valid);
         }
         cur = nxt;
         bcur = bnxt;
     }
+    int nonfinite = isfinite(ke) ? 0 : 1;
     if constexpr (PRED) {
         dep.finish(jt, tw, ng);
         nonfinite |= dep.over;
@@ -2006,7 +2299,7 @@ __device__ __forceinline__ void esec1_body(const Run &r0, RunPtr rp, const Work 
     }
 
     double ke = 0.0, gdev = 0.0;
-    int fb = 0, nonfinite = 0;
+    int fb = 0;
     const Run q = reload(rp);
     dep.settle();
     while (bcur < p1) {
@@ -2015,67 +2308,53 @@ __device__ __forceinline__ void esec1_body(const Run &r0, RunPtr rp, const Work 
         double w[U];
         load_weights(w, q.w, q.wu, bcur, p1);
         load_batch(nxt, X, V, q.vstride, bnxt, p1);   // the last one is discarded
-        double *Xob = Xo + bcur;
+        bool valid[U];
+        // lanes past the end repeat the last particle, without weight
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const unsigned o = lane + 64u * u;
-            const bool valid = o < nval;
-            if constexpr (DEP != 2) {
-                if (!valid)
-                    break;
-            }
-            const double *v = cur.v[u];
-            const Half<ORDER, NV, false> hs = half_step<ORDER, NV, false>(q, cur.x[u], v, ctn, nullptr);
-            double vd[NV];
-            const double eh = gather_poly<ORDER>(ctb, cell_of<ORDER>(hs.xh * q.inv_h, ng));
-            if constexpr (NV == 1) {
-                vd[0] = fma(q.dt, eh, v[0]);
-            } else {
-                const double *b = q.bext;
-                vd[0] = v[0] + q.dt * (eh + (hs.vs[1] * b[2] - hs.vs[2] * b[1]));
-                vd[1] = v[1] + q.dt * (hs.vs[2] * b[0] - hs.vs[0] * b[2]);
-                vd[2] = v[2] + q.dt * (hs.vs[0] * b[1] - hs.vs[1] * b[0]);
-            }
-            double num2 = 0.0, den = 0.0;
-#pragma unroll
-            for (int c = 0; c < NV; ++c) {
-                const double a2 = fma(2.0, hs.vs[c], -(vd[c] + v[c]));
-                num2 = fma(a2, vd[c] - v[c], num2);
-                den = fma(vd[c], vd[c], den);
-            }
-            int fbp = 0;
-            const double g = gamma_factor(num2, den, fbp);
-            double vn[NV];
-            double v2 = 0.0;
-#pragma unroll
-            for (int c = 0; c < NV; ++c) {
-                vn[c] = g * vd[c];
-                v2 = fma(vn[c], vn[c], v2);
-            }
-            const double xw = wrap_pos(hs.x1, q.L);
-            const double wp = valid ? w[u] : 0.0;
-            if (valid) {
-#pragma unroll
-                for (int c = 0; c < NV; ++c)
-                    __hip_atomic_store(&(Vo + c * q.vstride + bcur)[o], vn[c], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_SYSTEM);
-                __hip_atomic_store(&Xob[o], xw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                fb += fbp;
-                gdev = fmax(gdev, fabs(g - 1.0));
-                ke = fma(wp, v2, ke);
-                if (!isfinite(v2) || !isfinite(hs.x1))
-                    nonfinite = 1;
-            }
-            // step n + 1: v* from E^{n+1} at x*_{n+1}, and the centred deposit j^{n+3/2}
-            const Half<ORDER, NV, false> h1 = half_step<ORDER, NV, false>(q, xw, vn, ct1, nullptr);
-            const double qd[1] = {wp * q.qs * h1.vs[0]};
-            dep.add(jt, tw, ng, stencil<ORDER>(h1.xh * q.inv_h), qd, valid, u == 0);
+            valid[u] = lane + 64u * u < nval;
+            w[u] = valid[u] ? w[u] : 0.0;
         }
+        double vs[U][NV], x1[U], vd[U][NV];
+        Pos pos[U];
+        half_steps<ORDER, NV, false, U>(q, cur.x, cur.v, ctn, nullptr, vs, x1);
+        mid_points<ORDER, U>(pos, cur.x, x1, q);
+        Cell<ORDER> c[U];
+        cells_at<ORDER, U>(c, pos, ng);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            dagger_es<NV>(vd[u], cur.v[u], vs[u], gather_poly<ORDER>(ctb, c[u]), q);
+        double g[U], vn[U][NV], xw[U], v2[U];
+        gamma_all<NV, U>(g, vs, vd, cur.v, valid, fb);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            v2[u] = 0.0;
+#pragma unroll
+            for (int c = 0; c < NV; ++c) {
+                vn[u][c] = g[u] * vd[u][c];
+                v2[u] = fma(vn[u][c], vn[u][c], v2[u]);
+            }
+        }
+        wrap_all<U>(xw, x1, q);
+        store_all<NV, U>(xw, vn, valid, Xo, Vo, bcur, q.vstride);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            gdev = fmax(gdev, fabs(g[u] - 1.0));
+            ke = fma(w[u], v2[u], ke);
+        }
+        // step n + 1: v* from E^{n+1} at x*_{n+1}, and the centred deposit j^{n+3/2}
+        double va[U][NV], xa[U], qv[U][1];
+        half_steps<ORDER, NV, false, U>(q, xw, vn, ct1, nullptr, va, xa);
+        mid_points<ORDER, U>(pos, xw, xa, q);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            qv[u][0] = (w[u] * q.qs) * va[u][0];
+        deposit_all<ORDER, 1, DEP, U>(dep, jt, tw, ng, pos, qv, valid);
         cur = nxt;
         bcur = bnxt;
     }
     dep.finish(jt, tw, ng);
-    nonfinite |= dep.over;
+    const int nonfinite = isfinite(ke) ? dep.over : 1;
     const double sc[4] = {ke, (double)fb, gdev, (double)nonfinite};
     wave_partials<0xcu>(sc, red);
     lds_barrier();
@@ -2250,7 +2529,6 @@ __device__ __forceinline__ void std_pass_body(const Run &r0, RunPtr rp, const Wo
     }
 
     double ke1 = 0.0, ke0 = 0.0;
-    int nonfinite = 0;
     const Run q = reload(rp);
     dep.settle();
     while (bcur < p1) {
@@ -2259,60 +2537,63 @@ __device__ __forceinline__ void std_pass_body(const Run &r0, RunPtr rp, const Wo
         double w[U];
         load_weights(w, q.w, q.wu, bcur, p1);
         load_batch(nxt, X, V, q.vstride, bnxt, p1);   // the last one is discarded
-        double *Xob = Xo + bcur;
+        bool valid[U];
+        // lanes past the end repeat the last particle, without weight
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const unsigned o = lane + 64u * u;
-            const bool valid = o < nval;
-            if constexpr (DEP != 2) {
-                if (!valid)
-                    break;
-            }
-            const double *v = cur.v[u];
-            const double xs = fma(q.hdt, v[0], cur.x[u]);
-            const double ep = gather_poly<ORDER>(ct, cell_of<ORDER>(xs * q.inv_h, ng));
-            double vn[NV];
-            if constexpr (NV == 1) {
-                vn[0] = fma(q.dt, ep, v[0]);
-            } else {
-                // v^{n+1/2} = u + v^{n+1/2} x t, u = v^n + dt/2 E, t = dt/2 B; v^{n+1} = 2 v^{n+1/2} - v^n
-                const double uu[3] = {fma(q.hdt, ep, v[0]), v[1], v[2]};
-                const double tt[3] = {q.hdt * q.bext[0], q.hdt * q.bext[1], q.hdt * q.bext[2]};
-                double vh[3];
-                rotate_half(uu, tt, vh);
+            valid[u] = lane + 64u * u < nval;
+            w[u] = valid[u] ? w[u] : 0.0;
+        }
+        double xs[U], vn[U][NV], x1[U], xw[U];
+        Pos pos[U];
 #pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    vn[c] = fma(2.0, vh[c], -v[c]);
+        for (int u = 0; u < U; ++u) {
+            xs[u] = fma(q.hdt, cur.v[u][0], cur.x[u]);
+            pos[u] = locate<ORDER>(xs[u], q.inv_h, 0.0);
+        }
+        Cell<ORDER> c[U];
+        cells_at<ORDER, U>(c, pos, ng);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const double ep = gather_poly<ORDER>(ct, c[u]);
+            const double *v = cur.v[u];
+            if constexpr (NV == 1) {
+                vn[u][0] = fma(q.dt, ep, v[0]);
+            } else {
+                // v^{n+1/2} = a + v^{n+1/2} x t, a = v^n + dt/2 E, t = dt/2 B; v^{n+1} = 2 v^{n+1/2} - v^n
+                const double a[3] = {fma(q.hdt, ep, v[0]), v[1], v[2]};
+                const double t[3] = {q.hdt * q.bext[0], q.hdt * q.bext[1], q.hdt * q.bext[2]};
+                double vh[3];
+                rotate_half(a, t, vh);
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    vn[u][k] = fma(2.0, vh[k], -v[k]);
             }
-            const double x1 = fma(q.hdt, vn[0], xs);
-            const double xw = wrap_pos(x1, q.L);
-            const double wp = valid ? w[u] : 0.0;
+            x1[u] = fma(q.hdt, vn[u][0], xs[u]);
+        }
+        wrap_all<U>(xw, x1, q);
+        store_all<NV, U>(xw, vn, valid, Xo, Vo, bcur, q.vstride);
+        // the density of step n + 1 at x*_{n+1}
+        double qv[U][1];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
             double v2 = 0.0, v20 = 0.0;
 #pragma unroll
-            for (int c = 0; c < NV; ++c) {
-                v2 = fma(vn[c], vn[c], v2);
-                v20 = fma(v[c], v[c], v20);
+            for (int k = 0; k < NV; ++k) {
+                v2 = fma(vn[u][k], vn[u][k], v2);
+                v20 = fma(cur.v[u][k], cur.v[u][k], v20);
             }
-            if (valid) {
-#pragma unroll
-                for (int c = 0; c < NV; ++c)
-                    __hip_atomic_store(&(Vo + c * q.vstride + bcur)[o], vn[c], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_SYSTEM);
-                __hip_atomic_store(&Xob[o], xw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                ke1 = fma(wp, v2, ke1);
-                ke0 = fma(wp, v20, ke0);
-                if (!isfinite(v2) || !isfinite(x1))
-                    nonfinite = 1;
-            }
-            // the density of step n + 1 at x*_{n+1}
-            const double qd[1] = {wp * q.qs};
-            dep.add(jt, tw, ng, stencil<ORDER>(fma(q.hdt, vn[0], xw) * q.inv_h), qd, valid, u == 0);
+            ke1 = fma(w[u], v2, ke1);
+            ke0 = fma(w[u], v20, ke0);
+            qv[u][0] = w[u] * q.qs;
+            pos[u] = locate<ORDER>(fma(q.hdt, vn[u][0], xw[u]), q.inv_h, 0.0);
         }
+        deposit_all<ORDER, 1, DEP, U>(dep, jt, tw, ng, pos, qv, valid);
         cur = nxt;
         bcur = bnxt;
     }
     dep.finish(jt, tw, ng);
-    nonfinite |= dep.over;
+    const int nonfinite = isfinite(ke1) ? dep.over : 1;
     // slots: kinetic energy after, no fallbacks, no Gamma, non-finite; kinetic energy before
     const double sc[4] = {ke1, 0.0, 0.0, (double)nonfinite};
     wave_partials<0xcu>(sc, red);

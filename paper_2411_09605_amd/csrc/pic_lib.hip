@@ -299,6 +299,8 @@ void bind_run_work(const pic_params *p, const pic_buffers *b, const Layout &L, c
     r.h = p->length / p->n_cells;
     r.inv_h = p->n_cells / p->length;
     r.inv_ng = 1.0 / p->n_cells;
+    r.inv_L = 1.0 / p->length;
+    r.hinv_h = 0.5 * r.inv_h;
     r.dt = p->dt;
     r.hdt = 0.5 * p->dt;
     r.c2 = p->c * p->c;
@@ -1339,6 +1341,8 @@ int pic_batch_init(const pic_batch_params *p, const pic_batch_buffers *b, void *
         R.h = q.length / q.n_cells;
         R.inv_h = q.n_cells / q.length;
         R.inv_ng = 1.0 / q.n_cells;
+        R.inv_L = 1.0 / q.length;
+        R.hinv_h = 0.5 * R.inv_h;
         R.dt = q.dt;
         R.hdt = 0.5 * q.dt;
         R.c2 = q.c * q.c;

@@ -84,7 +84,7 @@ struct Run {
     int32_t em_fields;     // EMEC(LI), EMEC(PSATD): a field launch before pass B computes
                            // E^{n+1}, B^{n+1} and the gathered averages (Work::pf); 0:
                            // pass B's prologue does (EMEC(LF), the batched form)
-    double L, h, inv_h, inv_ng, dt, hdt, c2;
+    double L, inv_L, h, inv_h, hinv_h, inv_ng, dt, hdt, c2;   // hinv_h = 1 / (2 h)
     double xshift;         // grid offset of E_x and j in cells: 0.5 with cc (half nodes), else 0
     double qs;             // 1/h: deposit factor (times w_p)
     double wu;             // uniform weight L / N_p
