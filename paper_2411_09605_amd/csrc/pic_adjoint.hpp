@@ -48,43 +48,65 @@ struct AdjWork {
     double *gpart;         // [nblocks][nparam] per-workgroup gradient partial sums
 };
 
-// Derivative of the B-spline weights of stencil<ORDER> with respect to xi, on the same
-// nodes (first unchanged).
-template <int ORDER> __device__ __forceinline__ Stencil<ORDER> dstencil(double xi);
-
-template <> __device__ __forceinline__ Stencil<1> dstencil<1>(double xi)
+// Derivative of the B-spline weights with respect to x / h, on the stencil's nodes (first
+// unchanged), from the particle's offset.
+template <int ORDER> __device__ __forceinline__ Stencil<ORDER> dstencil_at(const Pos &p)
 {
-    Stencil<1> s;
-    s.first = (int)floor(xi);
-    s.w[0] = -1.0;
-    s.w[1] = 1.0;
-    return s;
-}
-
-template <> __device__ __forceinline__ Stencil<2> dstencil<2>(double xi)
-{
-    const double f = floor(xi + 0.5);
-    const double d = xi - f;
-    Stencil<2> s;
-    s.first = (int)f - 1;
-    s.w[0] = d - 0.5;
-    s.w[1] = -2.0 * d;
-    s.w[2] = 0.5 + d;
+    Stencil<ORDER> s;
+    if constexpr (ORDER == 2) {
+        s.first = p.i - 1;
+        s.w[0] = p.d - 0.5;
+        s.w[1] = -2.0 * p.d;
+        s.w[2] = 0.5 + p.d;
+    } else {
+        s.first = p.i;
+        s.w[0] = -1.0;
+        s.w[1] = 1.0;
+    }
     return s;
 }
 
 // Gamma and its branch: ok = the root is real (no fallback).  num2 = 2 num is formed as in
 // the forward pass, but from a recomputed state that agrees with the forward run only to
-// rounding (see adj_particle), and Gamma uses IEEE division and square root where the
-// forward pass uses a Newton-refined reciprocal and a Taylor series: a particle whose
-// radicand is within rounding of zero could take the other branch than in the forward run
-// (the tests compare the fallback counts of the two; they agree).
-__device__ __forceinline__ double adj_gamma(double num2, double den, double &rho, bool &ok)
+// rounding (see adj_particle), and Gamma takes the whole quotient and root where the forward
+// pass uses a Taylor series for small corrections: a particle whose radicand is within
+// rounding of zero could take the other branch than in the forward run (the tests compare the
+// fallback counts of the two; they agree).
+// The derivative needs 1 / den and 1 / (2 Gamma) too, so the reciprocal and the reciprocal
+// root are refined themselves (two Newton steps; Goldschmidt's iteration) and the quotient and
+// the root are corrected with them: 20 operations where three divisions and a square root
+// take 50 of a reverse step's 330.
+__device__ __forceinline__ double adj_gamma(double num2, double den, double &rho, double &rden,
+                                            double &half_inv, bool &ok)
 {
-    rho = num2 / den;
+    double y = __builtin_amdgcn_rcp(den);
+    y = fma(y, fma(-den, y, 1.0), y);
+    y = fma(y, fma(-den, y, 1.0), y);
+    rden = y;
+    rho = num2 * y;
+    rho = fma(fma(-rho, den, num2), y, rho);
+    if (__any(den < 1e-280)) {
+        asm volatile("");              // (not to be computed beside the usual quotient)
+        if (den < 1e-280) {
+            rden = 1.0 / den;
+            rho = num2 / den;
+        }
+    }
     const double rr = 1.0 + rho;
     ok = rr >= 0.0 && isfinite(rr);
-    return ok ? sqrt(rr) : 1.0;
+    const double s = __builtin_amdgcn_rsq(rr);
+    double root = rr * s, half = 0.5 * s;
+    double e = fma(-half, root, 0.5);
+    root = fma(root, e, root);
+    half = fma(half, e, half);
+    root = fma(fma(-root, root, rr), half, root);
+    e = fma(-half, root, 0.5);
+    half_inv = fma(half, e, half);     // 1 / (2 Gamma)
+    if (!(rr > 0.0)) {
+        root = 0.0;
+        half_inv = 0.5 / root;         // (as the division by Gamma = 0 gives)
+    }
+    return ok ? root : 1.0;
 }
 
 // Everything a reverse pass needs about one particle.  STAGE 1: the adjoint of the
@@ -97,42 +119,46 @@ struct AdjOut {
     double ebar_b, ehat_b, xb, vb;
 };
 
-// es, eb: predictor and averaged fields; jb2, jb1: current adjoints (ghost-padded LDS
-// tiles).  x, v: state n; axp, avp: adjoint of state n+1; q: w_p / h.
+// es, eb: predictor and averaged fields; lt, g2: the adjoint of E^{n+1} and the deposits of
+// R2, with their means (ghost-padded LDS tiles).  The current adjoints are affine in them,
+// jbar2 = -dt (lt - mean) and jbar1 = -dt/2 (G2 - mean), and a spline's weights sum to one
+// (those of its derivative to zero), so the gathers take lt and G2 themselves and the particle
+// applies the rest: no second round over the grid.
+// x, v: state n; axp, avp: adjoint of state n+1; q: w_p / h.
 template <int ORDER, int STAGE>
 __device__ __forceinline__ AdjOut<ORDER, STAGE> adj_particle(const Run &r, double x, double v,
                                                             double axp, double avp, double q,
                                                             const double *es, const double *eb,
-                                                            const double *jb2, const double *jb1)
+                                                            const double *lt, double mean_l,
+                                                            const double *g2, double mean_g)
 {
     AdjOut<ORDER, STAGE> o;
     // forward recompute: the quantities of pass A / pass B, equal to theirs up to rounding
     // (the gathers here take the stencil weights, the passes the cell polynomials of
     // gather_poly; the derivative needs the weights anyway)
-    const double xs = fma(r.hdt, v, x);
-    o.ss = stencil<ORDER>(xs * r.inv_h);
+    const Pos ps = locate<ORDER>(fma(r.hdt, v, x), r.inv_h, 0.0);        // x*
+    o.ss = stencil_at<ORDER>(ps);
     o.ns = slots_of<ORDER>(o.ss, r.ng);
     const double vs = fma(r.hdt, gather1<ORDER>(es, o.ss, o.ns), v);
     const double x1 = fma(r.dt, vs, x);
-    const double xh = 0.5 * (x + x1);
-    o.sh = stencil<ORDER>(xh * r.inv_h);
+    const Pos ph = locate<ORDER>(x + x1, r.hinv_h, 0.0);                 // x^{n+1/2}
+    o.sh = stencil_at<ORDER>(ph);
     o.nh = slots_of<ORDER>(o.sh, r.ng);
     const double vd = fma(r.dt, gather1<ORDER>(eb, o.sh, o.nh), v);
     // num2 = 2 num = a2 b with a2 = 2 v* - (vd + v), b = vd - v
     const double a2 = fma(2.0, vs, -(vd + v)), b = vd - v;
     const double num2 = fma(a2, b, 0.0), den = fma(vd, vd, 0.0);
-    double rho;
+    double rho, rden, half_inv;
     bool ok;
-    const double gam = adj_gamma(num2, den, rho, ok);
+    const double gam = adj_gamma(num2, den, rho, rden, half_inv, ok);
 
     // v^{n+1} = Gamma vd
     double vdb = gam * avp;
     const double gb = avp * vd;
     double numb = 0.0, denb = 0.0;              // adjoints of num2 and den
     if (ok) {
-        const double rhob = gb / (2.0 * gam);
-        numb = rhob / den;
-        denb = -rho * rhob / den;
+        numb = gb * half_inv * rden;
+        denb = -rho * numb;
     }
     const double ab = numb * b, bb = numb * a2;  // adjoints of a2 and b
     double vsb = 2.0 * ab;
@@ -144,10 +170,10 @@ __device__ __forceinline__ AdjOut<ORDER, STAGE> adj_particle(const Run &r, doubl
     o.vb = vb;
     if constexpr (STAGE >= 2) {
         // x^{n+1/2}: averaged-field gather and centred deposit
-        const Stencil<ORDER> dh = dstencil<ORDER>(xh * r.inv_h);
+        const Stencil<ORDER> dh = dstencil_at<ORDER>(ph);
         const double xhb = r.inv_h * (o.ebar_b * gather1<ORDER>(eb, dh, o.nh)
-                                      + q * vs * gather1<ORDER>(jb2, dh, o.nh));
-        vsb = fma(q, gather1<ORDER>(jb2, o.sh, o.nh), vsb);
+                                      - r.dt * q * vs * gather1<ORDER>(lt, dh, o.nh));
+        vsb = fma(-r.dt * q, gather1<ORDER>(lt, o.sh, o.nh) - mean_l, vsb);
         double x1b = axp + 0.5 * xhb;            // x^{n+1} = wrap(x1): a translation
         double xb = 0.5 * xhb + x1b;             // x1 = x + dt v*
         vsb = fma(r.dt, x1b, vsb);
@@ -157,10 +183,10 @@ __device__ __forceinline__ AdjOut<ORDER, STAGE> adj_particle(const Run &r, doubl
         o.vb = vb;
         if constexpr (STAGE >= 3) {
             // x*: predictor gather and predictor deposit
-            const Stencil<ORDER> ds = dstencil<ORDER>(xs * r.inv_h);
+            const Stencil<ORDER> ds = dstencil_at<ORDER>(ps);
             const double xsb = r.inv_h * (o.ehat_b * gather1<ORDER>(es, ds, o.ns)
-                                          + q * v * gather1<ORDER>(jb1, ds, o.ns));
-            vb = fma(q, gather1<ORDER>(jb1, o.ss, o.ns), vb);
+                                          - r.hdt * q * v * gather1<ORDER>(g2, ds, o.ns));
+            vb = fma(-r.hdt * q, gather1<ORDER>(g2, o.ss, o.ns) - mean_g, vb);
             o.xb = xb + xsb;
             o.vb = fma(r.hdt, xsb, vb);
         }
@@ -174,133 +200,186 @@ __device__ __forceinline__ double *g_slot(double *G, int nrep, int ng)
     return G + (size_t)(blockIdx.x % nrep) * ng;
 }
 
-// LDS of the reverse passes: es | eb | jb2 | jb1-or-tile (tw each) | lt (ng), and for the
-// fused pass (STAGE 4) the previous step's es | eb | tile (tw each).
-__host__ __device__ constexpr size_t adj_lds_doubles(int tw, int ng, int stage)
+// LDS of the reverse passes: es | eb | lt | G2-or-deposit tile (tw each), and for the fused
+// pass (STAGE 4) the previous step's es | eb | deposit tile (tw each).
+__host__ __device__ constexpr size_t adj_lds_doubles(int tw, int stage)
 {
-    return stage == 4 ? 7 * (size_t)tw + (size_t)ng : 4 * (size_t)tw + (size_t)ng;
+    return stage == 4 ? 7 * (size_t)tw : 4 * (size_t)tw;
 }
+
+// Node i's value into its slot of a tile and the slots of its periodic images.
+__device__ __forceinline__ void tile_put(double *t, int i, double v, int ng, int tw)
+{
+    t[kGhost + i] = v;
+    if (i < kGhost)
+        for (int s = i + kGhost + ng; s < tw; s += ng)
+            t[s] = v;
+    if (i >= ng - kGhost)
+        for (int s = i + kGhost - ng; s >= 0; s -= ng)
+            t[s] = v;
+}
+
+// A lane's batch of the reverse passes: the state, its adjoint and (STAGE 4) the state of
+// the step before.
+template <int STAGE> struct AdjBatch {
+    double x, v, ax, av, xm, vm;
+    __device__ __forceinline__ void load(const double *X, const double *V, const AdjWork &aw,
+                                         const double *Xm, const double *Vm, int64_t start, int64_t p1)
+    {
+        const BatchAddr a(start, p1, 64);
+        const unsigned o = a.off(threadIdx.x & 63, 0);
+        x = (X + a.b0)[o];
+        v = (V + a.b0)[o];
+        ax = (aw.ax + a.b0)[o];
+        av = (aw.av + a.b0)[o];
+        if constexpr (STAGE == 4) {
+            xm = (Xm + a.b0)[o];
+            vm = (Vm + a.b0)[o];
+        }
+    }
+};
 
 // Reverse pass of step n.  STAGE 1, 2, 3 as described at the top; STAGE 4 is R3 of step n
 // fused with R1 of step n - 1: with the adjoint of (x^n, v^n) just computed, the same
 // thread recomputes step n - 1 of its particle (Xm, Vm, grids gm) and deposits its
 // E-bar adjoint into the other parity's G1.  G1 and G2 have nrep replicas.
+//
+// What bounds it at 1e6 particles: each pass has about four batches per wavefront, so the
+// round trips before and inside the loop.  The prologue is one round of loads (the fields the
+// forward pass B built for step n, and n - 1, and the grid adjoints), one barrier for the
+// tiles, their ghosts and the means; the next batch loads while the current one is processed
+// (STAGE 4 22.7 -> 18.6 us, STAGE 2 13.7 -> 10.6 us at 1e6 particles, 256 cells).
 template <int ORDER, int STAGE>
-__global__ __launch_bounds__(1024) void k_adj_reverse(Run r, Work wk, AdjWork aw, AdjParams ap,
-                                                      int q, const double *__restrict__ X,
-                                                      const double *__restrict__ V,
-                                                      const double *__restrict__ g,
-                                                      const double *__restrict__ Xm,
-                                                      const double *__restrict__ Vm,
-                                                      const double *__restrict__ gm)
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4)))
+void k_adj_reverse(Run r, AdjWork aw, AdjParams ap, int q, const double *__restrict__ X,
+                   const double *__restrict__ V, const double *__restrict__ g,
+                   const double *__restrict__ Xm, const double *__restrict__ Vm,
+                   const double *__restrict__ gm)
 {
     extern __shared__ double smem[];
     __shared__ double red[kRedSize];
     __shared__ int wctr;
     const int ng = r.ng, tw = r.tw, nrep = r.nrep;
+    const unsigned nt = nthreads();
     const int64_t p0 = (int64_t)blockIdx.x * r.chunk;
     const int64_t p1 = min(r.np, p0 + r.chunk);
-    // wavefronts claim batches of 64 particles (the counter is set before the barriers below)
+    // wavefronts claim batches of 64 particles (the counter is set before the barrier below)
     WaveBatches<1> wb(p0, &wctr);
-    wb.reset();
-    double *es = smem, *eb = es + tw, *jb2 = eb + tw, *t4 = jb2 + tw, *lt = t4 + tw;
-    double *esm = lt + ng, *ebm = esm + tw, *tm = ebm + tw;   // STAGE 4
-    // One round of loads: the fields the forward pass B built for step n (and n - 1),
-    // E* | E-bar | E^{n+1} after the three grids, and the grid adjoints.
+    wb.reset(nt);
+    double *es = smem, *eb = es + tw, *lt = eb + tw, *t4 = lt + tw;
+    double *esm = t4 + tw, *ebm = esm + tw, *tm = ebm + tw;   // STAGE 4
+    double *dt_tile = STAGE == 4 ? tm : t4;                   // the deposit
     //   lt = lambda + lbw E^{n+1} + G1 / 2 (the adjoint of E^{n+1}); t4 = G2 (STAGE >= 3)
     double m[2] = {0.0, 0.0};
-    for (int i = threadIdx.x; i < ng; i += nthreads()) {
-        es[kGhost + i] = g[3 * ng + i];
-        eb[kGhost + i] = g[4 * ng + i];
+    AdjBatch<STAGE> cur, nxt;
+    int64_t bcur = wb.first();
+    bool loaded = false;
+    for (int base = 0; base < ng; base += (int)nt) {
+        const int i = base + (int)threadIdx.x, j = min(i, ng - 1);
+        const double fe = g[3 * ng + j], fb = g[4 * ng + j];
+        double fem = 0.0, fbm = 0.0, e1 = 0.0, lam = 0.0, g1 = 0.0, g2 = 0.0;
         if constexpr (STAGE == 4) {
-            esm[kGhost + i] = gm[3 * ng + i];
-            ebm[kGhost + i] = gm[4 * ng + i];
+            fem = gm[3 * ng + j];
+            fbm = gm[4 * ng + j];
         }
+        double a1[STAGE >= 2 ? kMaxRep : 1], a2[STAGE >= 3 ? kMaxRep : 1];
         if constexpr (STAGE >= 2) {
-            const double g1 = rep_sum(aw.G1[q], i, nrep, ng);
-            const double l = fma(ap.lbw, g[5 * ng + i], aw.lam[q][i]) + 0.5 * g1;
-            lt[i] = l;
-            m[0] += l;
-            if constexpr (STAGE >= 3) {
-                const double g2 = rep_sum(aw.G2[q], i, nrep, ng);
-                t4[kGhost + i] = g2;
-                m[1] += g2;
-                // adjoint of E^n for step n - 1
-                if (blockIdx.x == 0)
-                    aw.lam[q ^ 1][i] = l + 0.5 * g1 + g2;
+            e1 = g[5 * ng + j];
+            lam = aw.lam[q][j];
+#pragma unroll
+            for (int k = 0; k < kMaxRep; ++k) {
+                a1[k] = (aw.G1[q] + (size_t)min(k, nrep - 1) * ng)[j];
+                if constexpr (STAGE >= 3)
+                    a2[k] = (aw.G2[q] + (size_t)min(k, nrep - 1) * ng)[j];
+            }
+        }
+        if (!loaded) {
+            // the first particles, behind the first round of grid loads
+            cur.load(X, V, aw, Xm, Vm, bcur, p1);
+            if constexpr (STAGE != 3)
+                tile_zero(dt_tile, tw, nt);
+            loaded = true;
+        }
+        if (i < ng) {
+            tile_put(es, i, fe, ng, tw);
+            tile_put(eb, i, fb, ng, tw);
+            if constexpr (STAGE == 4) {
+                tile_put(esm, i, fem, ng, tw);
+                tile_put(ebm, i, fbm, ng, tw);
+            }
+            if constexpr (STAGE >= 2) {
+                g1 = a1[0];
+#pragma unroll
+                for (int k = 1; k < kMaxRep; ++k)
+                    g1 += k < nrep ? a1[k] : 0.0;
+                const double l = fma(ap.lbw, e1, lam) + 0.5 * g1;
+                tile_put(lt, i, l, ng, tw);
+                m[0] += l;
+                if constexpr (STAGE >= 3) {
+                    g2 = a2[0];
+#pragma unroll
+                    for (int k = 1; k < kMaxRep; ++k)
+                        g2 += k < nrep ? a2[k] : 0.0;
+                    tile_put(t4, i, g2, ng, tw);
+                    m[1] += g2;
+                    // adjoint of E^n for step n - 1
+                    if (blockIdx.x == 0)
+                        aw.lam[q ^ 1][i] = l + 0.5 * g1 + g2;
+                }
             }
         }
     }
-    if constexpr (STAGE >= 2) {
-        block_reduce<0u>(m, red);
-        const double mean_l = m[0] / ng, mean_g2 = m[1] / ng;
-        // jb2 = -dt (lt - mean lt): the adjoint of the centred current (Ampere update with
-        // its mean removed); jb1 = -dt/2 (G2 - mean G2), the predictor current's
-        for (int i = threadIdx.x; i < ng; i += nthreads()) {
-            jb2[kGhost + i] = -r.dt * (lt[i] - mean_l);
-            if constexpr (STAGE >= 3)
-                t4[kGhost + i] = -r.hdt * (t4[kGhost + i] - mean_g2);
-        }
-    }
-    if (blockIdx.x == 0) {
-        // the next reverse step deposits into the other parity's G1 (R2, in the pass after
-        // this) and G2; the lead of R3 clears the latter
-        if constexpr (STAGE == 2)
-            rep_zero(aw.G1[q ^ 1], ng, nrep, ng);
-        if constexpr (STAGE >= 3)
-            rep_zero(aw.G2[q ^ 1], ng, nrep, ng);
-    }
-    if constexpr (STAGE <= 2)
-        tile_zero(t4, tw);
-    if constexpr (STAGE == 4)
-        tile_zero(tm, tw);
-    __syncthreads();
-    ghost_fill(es, 1, ng, tw);
-    ghost_fill(eb, 1, ng, tw);
-    if constexpr (STAGE == 4) {
-        ghost_fill(esm, 1, ng, tw);
-        ghost_fill(ebm, 1, ng, tw);
-    }
-    if constexpr (STAGE >= 2)
-        ghost_fill(jb2, 1, ng, tw);
+    // the next reverse step deposits into the other parity's G1 (R2, in the pass after this)
+    // and G2 (cleared by R3): every workgroup clears its share
+    if constexpr (STAGE == 2)
+        rep_zero_part(aw.G1[q ^ 1], ng, nrep, ng, blockIdx.x, r.nblocks, nt);
     if constexpr (STAGE >= 3)
-        ghost_fill(t4, 1, ng, tw);
-    __syncthreads();
+        rep_zero_part(aw.G2[q ^ 1], ng, nrep, ng, blockIdx.x, r.nblocks, nt);
+    double mean_l = 0.0, mean_g2 = 0.0;
+    if constexpr (STAGE >= 2)
+        wave_partials<0u>(m, red);
+    lds_barrier();
+    if constexpr (STAGE >= 2) {
+        mean_l = read_lane(wave_total(red, 0, nt >> 6), 0) * r.inv_ng;
+        mean_g2 = read_lane(wave_total(red, 1, nt >> 6), 0) * r.inv_ng;
+    }
 
     Depo<ORDER, 1, 3> dep;          // adjoint values: FP64 atomics (no fixed-point scale)
-    dep.init(nullptr, r, nullptr);
-    for (int64_t b = wb.first(); b < p1; b = wb.claim()) {
-        const int64_t p = b + (threadIdx.x & 63);
-        if (p >= p1)
-            continue;
-        const double x = X[p], v = V[p], axp = aw.ax[p], avp = aw.av[p];
-        const double qp = (r.w ? r.w[p] : r.wu) * r.qs;
-        const AdjOut<ORDER, STAGE == 4 ? 3 : STAGE> o =
-            adj_particle<ORDER, STAGE == 4 ? 3 : STAGE>(r, x, v, axp, avp, qp, es, eb, jb2, t4);
-        if constexpr (STAGE == 1) {
-            const double c[1] = {o.ebar_b};
-            dep.add(t4, tw, ng, o.sh, c);
-        } else if constexpr (STAGE == 2) {
-            const double c[1] = {o.ehat_b};
-            dep.add(t4, tw, ng, o.ss, c);
-        } else {
-            aw.ax[p] = o.xb;
-            aw.av[p] = o.vb;
-            if constexpr (STAGE == 4) {
-                const AdjOut<ORDER, 1> o1 = adj_particle<ORDER, 1>(r, Xm[p], Vm[p], o.xb, o.vb, qp,
-                                                                   esm, ebm, jb2, t4);
-                const double c[1] = {o1.ebar_b};
-                dep.add(tm, tw, ng, o1.sh, c);
+    while (bcur < p1) {
+        const int64_t bnxt = wb.claim(), p = bcur + (threadIdx.x & 63);
+        const bool valid = p < p1;
+        double w = r.wu;
+        if (r.w)
+            w = r.w[min(p, p1 - 1)];
+        nxt.load(X, V, aw, Xm, Vm, bnxt, p1);          // the last one is discarded
+        const double qp = w * r.qs;
+        const AdjOut<ORDER, STAGE == 4 ? 3 : STAGE> o = adj_particle<ORDER, STAGE == 4 ? 3 : STAGE>(
+            r, cur.x, cur.v, cur.ax, cur.av, qp, es, eb, lt, mean_l, t4, mean_g2);
+        if (valid) {
+            if constexpr (STAGE == 1) {
+                const double c[1] = {o.ebar_b};
+                dep.add(dt_tile, tw, ng, o.sh, c);
+            } else if constexpr (STAGE == 2) {
+                const double c[1] = {o.ehat_b};
+                dep.add(dt_tile, tw, ng, o.ss, c);
+            } else {
+                aw.ax[p] = o.xb;
+                aw.av[p] = o.vb;
+                if constexpr (STAGE == 4) {
+                    const AdjOut<ORDER, 1> o1 = adj_particle<ORDER, 1>(
+                        r, cur.xm, cur.vm, o.xb, o.vb, qp, esm, ebm, lt, mean_l, t4, mean_g2);
+                    const double c[1] = {o1.ebar_b};
+                    dep.add(dt_tile, tw, ng, o1.sh, c);
+                }
             }
         }
+        cur = nxt;
+        bcur = bnxt;
     }
-    if constexpr (STAGE == 1 || STAGE == 2) {
-        __syncthreads();
-        tile_flush(t4, g_slot(STAGE == 1 ? aw.G1[q] : aw.G2[q], nrep, ng), 1, ng, tw);
-    }
-    if constexpr (STAGE == 4) {
-        __syncthreads();
-        tile_flush(tm, g_slot(aw.G1[q ^ 1], nrep, ng), 1, ng, tw);
+    if constexpr (STAGE != 3) {
+        lds_barrier();
+        double *G = STAGE == 1 ? aw.G1[q] : (STAGE == 2 ? aw.G2[q] : aw.G1[q ^ 1]);
+        tile_flush(dt_tile, g_slot(G, nrep, ng), 1, ng, tw);
     }
 }
 
@@ -379,9 +458,9 @@ __global__ __launch_bounds__(1024) void k_adj_grad(Run r, AdjWork aw, AdjParams 
     for (int64_t p = p0 + threadIdx.x; p < p1; p += nthreads()) {
         const double x = X0[p];
         const double q = (r.w ? r.w[p] : r.wu) * r.qs;
-        const Stencil<ORDER> s = stencil<ORDER>(x * r.inv_h);
+        const Stencil<ORDER> s = stencil_at<ORDER>(locate<ORDER>(x, r.inv_h, 0.0));
         const Slots<ORDER> n = slots_of<ORDER>(s, ng);
-        const Stencil<ORDER> d = dstencil<ORDER>(x * r.inv_h);
+        const Stencil<ORDER> d = dstencil_at<ORDER>(locate<ORDER>(x, r.inv_h, 0.0));
         const double xb = aw.ax[p] + q * r.inv_h * gather1<ORDER>(rb, d, n);
         double dens = 1.0;
         for (int m = 0; m < ap.n_modes; ++m)

@@ -1556,7 +1556,7 @@ pic_params adj_forward_params(const pic_adj_params *p)
 
 size_t adj_lds(const pic_params *q, int stage = 4)
 {
-    return adj_lds_doubles((int)tile_width(q), q->n_cells, stage) * 8;
+    return adj_lds_doubles((int)tile_width(q), stage) * 8;
 }
 
 int adj_validate(const pic_adj_params *p)
@@ -1704,7 +1704,7 @@ void adj_rev(pic_adj *c, int q, const double *X, const double *V, const double *
              const double *Xm = nullptr, const double *Vm = nullptr, const double *gm = nullptr)
 {
     hipLaunchKernelGGL((k_adj_reverse<ORDER, STAGE>), dim3(c->run.nblocks), dim3(c->threads),
-                       adj_lds(&c->q, STAGE), c->stream, c->run, c->wk, c->aw, c->ap, q, X, V, g, Xm, Vm,
+                       adj_lds(&c->q, STAGE), c->stream, c->run, c->aw, c->ap, q, X, V, g, Xm, Vm,
                        gm);
 }
 
