@@ -129,18 +129,17 @@ size_t lds_esec1_of(int order, size_t ng)
 }
 
 // standard scheme: the particle pass (jt | es | side | coefficient tile) and the field
-// launch (rho | Green's row twice | filtered rho)
+// launch (rho | Green's row | filtered rho)
 size_t lds_std_pass_of(int order, size_t ng)
 {
     const size_t tw = ng + 2 * kGhost;
     return ((size_t)pic::coef_offset((int)(3 * tw)) + (order + 1) * tw) * 8;
 }
 
-size_t lds_std_field_of(size_t ng) { return 4 * ng * 8; }
+size_t lds_std_field_of(size_t ng) { return 3 * ng * 8; }
 
-// the EM field launch (k_em_fields): one pair's E, B and j, three rows and the partial
-// sums of 256 threads
-size_t lds_psatd_of(size_t ng) { return (6 * ng + 256) * 8; }
+// the EM field launch (k_em_fields): one pair's E, B and j and three rows
+size_t lds_psatd_of(size_t ng) { return 6 * ng * 8; }
 
 size_t lds_pass_a(const pic_params *p) { return lds_pass_a_of(is_em(p), p->shape_order, (size_t)p->n_cells); }
 

@@ -140,8 +140,8 @@ void launch_std_field(pic_ctx *c, int64_t n)
     const int par = (int)(n & 1);
     hipEvent_t e0 = c->kev[0], e1 = c->kev[1];
     c->kev[0] = c->kev[1] = nullptr;
-    const unsigned grid = (unsigned)((c->p.n_cells + kRedEntries - 1) / kRedEntries);
-    hipExtLaunchKernelGGL(k_std_field, dim3(grid), dim3(256),
+    const unsigned grid = (unsigned)((c->p.n_cells + kFieldNodes - 1) / kFieldNodes);
+    hipExtLaunchKernelGGL(k_std_field, dim3(grid), dim3(64 * kFieldNodes),
                           (uint32_t)lds_std_field_of((size_t)c->p.n_cells), c->stream, e0, e1, 0u,
                           c->run, c->wk, (const double *)c->wk.J2[par], c->wk.Ef[par],
                           (int)c->run.filter_rho);
@@ -152,8 +152,8 @@ void launch_std_field(pic_ctx *c, int64_t n)
 void launch_em_fields(pic_ctx *c, int par, int full)
 {
     const int ng = c->p.n_cells;
-    hipLaunchKernelGGL(k_em_fields, dim3((unsigned)((ng + kPsatdOut - 1) / kPsatdOut), full ? 6u : 4u),
-                       dim3(kPsatdOut * kPsatdSeg), (uint32_t)lds_psatd_of((size_t)ng), c->stream,
+    hipLaunchKernelGGL(k_em_fields, dim3((unsigned)((ng + kFieldNodes - 1) / kFieldNodes), full ? 6u : 4u),
+                       dim3(64 * kFieldNodes), (uint32_t)lds_psatd_of((size_t)ng), c->stream,
                        c->run, by_parity(c->wk, par), full);
 }
 
@@ -1161,7 +1161,7 @@ BatchLayout batch_layout(const pic_batch_params *p)
     L.rec = take((size_t)p->n_runs * batch_records(p) * sizeof(DevRecord));
     L.runs = take((size_t)p->n_runs * sizeof(BatchRun));
     L.items = take((size_t)L.nitems * sizeof(BatchItem));
-    L.stepc = take(8);
+    L.stepc = take(2 * 8);
     L.total = o;
     return L;
 }
@@ -1213,7 +1213,6 @@ void batch_step_kind(pic_batch *c)
     else
         hipLaunchKernelGGL((k_batch_pass_b<ORDER, NV, EM, false, 0>), dim3(c->grid), dim3(c->threads),
                            c->lds_b, c->stream, c->bt);
-    hipLaunchKernelGGL(k_batch_tick, dim3(1), dim3(64), 0, c->stream, c->bt);
 }
 
 template <int ORDER>
