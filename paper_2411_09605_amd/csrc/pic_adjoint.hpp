@@ -264,8 +264,8 @@ void k_adj_reverse(Run r, AdjWork aw, AdjParams ap, int q, const double *__restr
     const int64_t p0 = (int64_t)blockIdx.x * r.chunk;
     const int64_t p1 = min(r.np, p0 + r.chunk);
     // wavefronts claim batches of 64 particles (the counter is set before the barrier below)
-    WaveBatches<1> wb(p0, &wctr);
-    wb.reset(nt);
+    WaveBatches<1> wb(p0, &wctr, nt);
+    wb.reset();
     double *es = smem, *eb = es + tw, *lt = eb + tw, *t4 = lt + tw;
     double *esm = t4 + tw, *ebm = esm + tw, *tm = ebm + tw;   // STAGE 4
     double *dt_tile = STAGE == 4 ? tm : t4;                   // the deposit

@@ -68,6 +68,14 @@ __device__ __forceinline__ RunPtr kernarg_run()
     return (RunPtr)__builtin_amdgcn_kernarg_segment_ptr();
 }
 
+// A value that is the same in every lane, in a scalar register pair of its own.
+__device__ __forceinline__ double scalar_pair(double v)
+{
+    unsigned lo = __double2loint(v), hi = __double2hiint(v);
+    asm("" : "+s"(lo), "+s"(hi));
+    return __hiloint2double((int)hi, (int)lo);
+}
+
 // The run's scalars read (again) at this point, with scalar loads.  The passes read them once
 // for their prologue and once for the particle loop: values held from one to the other would
 // not fit the scalar registers beside the prologue's addresses, and the loop would fetch its
@@ -79,7 +87,21 @@ __device__ __forceinline__ Run reload(RunPtr p)
         int w[sizeof(Run) / 4];
     };
     typedef const __attribute__((address_space(4))) Words *words;
-    return __builtin_bit_cast(Run, *(words)p);
+    Run r = __builtin_bit_cast(Run, *(words)p);
+    // one register pair each: as parts of the wide loads they would be spilled eight at a time
+    double *c[] = {&r.dt, &r.hdt, &r.L, &r.inv_L, &r.inv_h, &r.hinv_h, &r.qs, &r.wu, &r.xshift};
+#pragma unroll
+    for (double *d : c)
+        *d = scalar_pair(*d);
+    return r;
+}
+
+// Likewise a pointer that the particle loop uses.
+template <typename P> __device__ __forceinline__ void settle_pointer(P &p)
+{
+    typedef __attribute__((address_space(1))) double *global_ptr;   // (stays a global address)
+    p = (P)(global_ptr)__builtin_bit_cast(unsigned long long,
+                                          scalar_pair(__builtin_bit_cast(double, (unsigned long long)p)));
 }
 
 // Written by k_group_size_probe: nthreads() as read in one-workgroup launches of 64 and
@@ -97,7 +119,7 @@ __global__ void k_group_size_probe(int slot)
 // while they compute on the current one (and the first batch's loads in flight during the
 // field prologue), so HBM latency overlaps LDS and ALU work.
 template <int U, int NV> struct PBatch {
-    double x[U], v[U][NV];
+    double x[U], v[U][NV], w[U];
 };
 
 // Addressing of a wavefront's batch of 64 U consecutive particles starting at `start` (the
@@ -119,12 +141,14 @@ struct BatchAddr {
     }
 };
 
-// Loads the batch at `start` (U particles per lane).  The compiler then knows how many
-// loads are in flight and lets the next batch load while the current one is processed.
-// Callers mask the entries past p1 with their own bounds test.
+// Loads the batch at `start` (U particles per lane, with their weights W[p], or wu when W is
+// null).  The weights come with the batch: loaded when the batch is processed, they would be
+// waited for in the middle of it, and with them, in order, the next batch's loads.  Callers
+// mask the entries past p1 with their own bounds test.
 template <int U, int NV>
 __device__ __forceinline__ void load_batch(PBatch<U, NV> &b, const double *__restrict__ X,
                                            const double *__restrict__ V, int64_t vstride,
+                                           const double *__restrict__ W, double wu,
                                            int64_t start, int64_t p1)
 {
     const BatchAddr a(start, p1, 64u * U);
@@ -137,20 +161,13 @@ __device__ __forceinline__ void load_batch(PBatch<U, NV> &b, const double *__res
 #pragma unroll
         for (int c = 0; c < NV; ++c)
             b.v[u][c] = (V + c * vstride + a.b0)[o];
+        b.w[u] = wu;
     }
-}
-
-// Weights of the batch at `start` (W[p], or wu when W is null).  Issued before the next
-// batch's loads, so that waiting for them does not wait for the prefetch.
-template <int U>
-__device__ __forceinline__ void load_weights(double (&w)[U], const double *__restrict__ W,
-                                             double wu, int64_t start, int64_t p1)
-{
-    const BatchAddr a(start, p1, 64u * U);
-    const unsigned lane = threadIdx.x & 63;
+    if (W) {
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-        w[u] = W ? (W + a.b0)[a.off(lane, u)] : wu;
+        for (int u = 0; u < U; ++u)
+            b.w[u] = (W + a.b0)[a.off(lane, u)];
+    }
 }
 
 // A workgroup's particles go to its wavefronts in batches of 64 U consecutive particles
@@ -171,47 +188,50 @@ __device__ __forceinline__ void load_weights(double (&w)[U], const double *__res
 // Static (the deterministic mode): wavefront w takes batches w, w + W, w + 2W, ... of
 // its workgroup's W wavefronts, so every thread always sees the same particles in the
 // same order and its running sums (kinetic energy) are reproducible bit for bit.
+// Starts are kept in units of 64 particles (chunks are whole wavefronts), in 32 bits: 2^37
+// particles, far more than the memory holds.
 template <int U> struct WaveBatches {
-    static constexpr int kBatch = 64 * U;
-    int64_t origin, step;
-    int64_t np, last;      // reversed order: batch start s maps to last - s while s < np
+    int origin, step;
+    int nu, last;          // reversed order: batch start s maps to last - s while s < nu
     int *ctr;
     int fixed;             // 1: static assignment
     int k;                 // static: index of the wavefront's current batch
+    int nw;
     // Interleaved runs (the state larger than the 256 MB Infinity Cache) can walk the state
     // from its end (reverse): a pass that starts where the previous pass ended finds up to
     // 256 MB of the state still in the cache.  The set of batches is the same either way.
-    __device__ __forceinline__ WaveBatches(int64_t p0, int *counter, int interleave = 0,
+    __device__ __forceinline__ WaveBatches(int64_t p0, int *counter, unsigned nt, int interleave = 0,
                                            int nblocks = 1, int static_order = 0,
                                            int64_t n_particles = 0, bool reverse = false)
-        : ctr(counter), fixed(static_order)
+        : ctr(counter), fixed(static_order), nw((int)(nt >> 6))
     {
-        origin = interleave ? (int64_t)blockIdx.x * kBatch : p0;
-        step = interleave ? (int64_t)nblocks * kBatch : (int64_t)kBatch;
+        origin = interleave ? (int)blockIdx.x * U : (int)(p0 >> 6);
+        step = interleave ? nblocks * U : U;
         k = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        np = (interleave && reverse && n_particles > 0) ? n_particles : 0;
-        last = np > 0 ? (np - 1) / kBatch * kBatch : 0;
+        // units of the run rounded up to whole batches
+        nu = (interleave && reverse) ? (int)((n_particles + 64 * U - 1) / (64 * U)) * U : 0;
+        last = nu - U;
     }
-    __device__ __forceinline__ int64_t order(int64_t s) const
+    __device__ __forceinline__ int64_t order(int s) const
     {
-        return s < np ? last - s : s;
+        return (int64_t)(s < nu ? last - s : s) << 6;
     }
-    __device__ __forceinline__ void reset(unsigned nt = nthreads()) const
+    __device__ __forceinline__ void reset() const
     {
         if (threadIdx.x == 0)
-            *ctr = (int)(nt >> 6);
+            *ctr = nw;
     }
     // first particle of this wavefront's first batch (the same in every lane)
     __device__ __forceinline__ int64_t first() const
     {
-        return order(origin + (int64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * step);
+        return order(origin + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * step);
     }
     // claim the next batch (every lane of the wavefront active)
     __device__ __forceinline__ int64_t claim()
     {
         if (fixed) {
-            k += (int)(nthreads() >> 6);
-            return order(origin + (int64_t)k * step);
+            k += nw;
+            return order(origin + k * step);
         }
         // (an address the compiler takes to differ by lane keeps it from wrapping the one
         // lane's atomic in a wavefront-wide sum)
@@ -220,7 +240,7 @@ template <int U> struct WaveBatches {
         asm("" : "+v"(zero));
         if ((threadIdx.x & 63) == 0)
             kc = atomicAdd(ctr + zero, 1);
-        return order(origin + (int64_t)__builtin_amdgcn_readlane(kc, 0) * step);
+        return order(origin + __builtin_amdgcn_readlane(kc, 0) * step);
     }
 };
 
@@ -1638,6 +1658,8 @@ __device__ __forceinline__ void gamma_all(double (&g)[U], const double (&vs)[U][
     // num2 = 2 num = sum (2 v* - (v-dagger + v)) . (v-dagger - v)
     double num2[U], den[U], rc[U], rho[U];
     bool large[U];
+    double c3 = 0.0625;
+    asm("" : "+v"(c3));        // (kept in registers: an FMA takes one constant that is not)
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         num2[u] = 0.0;
@@ -1652,7 +1674,7 @@ __device__ __forceinline__ void gamma_all(double (&g)[U], const double (&vs)[U][
         rc[u] = fma(y, fma(-den[u], y, 1.0), y);
         rho[u] = num2[u] * rc[u];
         large[u] = !(fabs(rho[u]) < 1e-4);
-        g[u] = fma(rho[u], fma(rho[u], fma(rho[u], fma(rho[u], -0.0390625, 0.0625), -0.125), 0.5), 1.0);
+        g[u] = fma(rho[u], fma(rho[u], fma(rho[u], fma(rho[u], -0.0390625, c3), -0.125), 0.5), 1.0);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -1817,10 +1839,10 @@ __device__ __forceinline__ void pass_a_body(const Run &r0, RunPtr rp, const Work
     double *ct = smem + coef_offset((2 * T::ncur + T::ne + T::nb + 1) * tw);   // ES: coefficients
     Depo<ORDER, T::ncur, DEP> dep;
     // pass A walks the state from its end, pass B from its start (see WaveBatches)
-    WaveBatches<U> wb(p0, wctr, r.interleave, r.nblocks, r.det, r.np, true);
+    WaveBatches<U> wb(p0, wctr, nt, r.interleave, r.nblocks, r.det, r.np, true);
     PBatch<U, NV> cur, nxt;
     int64_t bcur = wb.first();
-    wb.reset(nt);
+    wb.reset();
     NodeLoad<false> nodes;
     // ESEC1 gathers E^n itself: no predictor current
     const double *j1 = EM || r.scheme != 0 ? nullptr : wk.J1[0];
@@ -1828,7 +1850,7 @@ __device__ __forceinline__ void pass_a_body(const Run &r0, RunPtr rp, const Work
         nodes.issue(r, wk.Ef[0], j1, nullptr, threadIdx.x);
         dep.init(side, r, wk.st);
         __builtin_amdgcn_sched_barrier(0);
-        load_batch(cur, X, V, r.vstride, bcur, p1);
+        load_batch(cur, X, V, r.vstride, r.w, r.wu, bcur, p1);
     } else {
         dep.init(side, r, wk.st);
     }
@@ -1844,7 +1866,7 @@ __device__ __forceinline__ void pass_a_body(const Run &r0, RunPtr rp, const Work
             psatd_tiles(r, wk.ps, es, bs, nt);    // E*, B* come from the field launch before
         else
             predictor_fields(r, wk.Ef[0], wk.Bf[0], wk.J1[0], es, bs, r.nrep);
-        load_batch(cur, X, V, r.vstride, bcur, p1);
+        load_batch(cur, X, V, r.vstride, r.w, r.wu, bcur, p1);
         lds_barrier();
         ghost_fill(es, T::ne, ng, tw, nt);
         ghost_fill(bs, T::nb, ng, tw, nt);
@@ -1870,28 +1892,29 @@ __device__ __forceinline__ void pass_a_body(const Run &r0, RunPtr rp, const Work
     const double *eg = EM ? es : ct;     // what half_step gathers E from
 
     const Run q = reload(rp);
+    settle_pointer(X);
+    settle_pointer(V);
     dep.settle();
     // whole wavefronts run the loop (DEP = 2 needs them in its deposit); particles past the
     // end are masked with `valid`
     while (bcur < p1) {
         const int64_t bnxt = wb.claim();
         const unsigned nval = (unsigned)min(p1 - bcur, (int64_t)(64 * U));
-        double w[U];
-        load_weights(w, q.w, q.wu, bcur, p1);
-        load_batch(nxt, X, V, q.vstride, bnxt, p1);   // the last one is discarded
+        load_batch(nxt, X, V, q.vstride, q.w, q.wu, bnxt, p1);   // the last one is discarded
         bool valid[U];
-        // lanes past the end repeat the last particle, without weight
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int u = 0; u < U; ++u)
             valid[u] = lane + 64u * u < nval;
-            w[u] = valid[u] ? w[u] : 0.0;
-        }
+        if (nval < 64u * U)       // lanes past the end repeat the last particle, without weight
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                cur.w[u] = valid[u] ? cur.w[u] : 0.0;
         double vs[U][NV], x1[U];
         half_steps<ORDER, NV, EM, U>(q, cur.x, cur.v, eg, bs, vs, x1);
         double qv[U][T::ncur];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const double qw = w[u] * q.qs;
+            const double qw = cur.w[u] * q.qs;
 #pragma unroll
             for (int c = 0; c < T::ncur; ++c)
                 qv[u][c] = qw * vs[u][c];
@@ -1980,10 +2003,10 @@ __device__ __forceinline__ void pass_b_body(const Run &r0, RunPtr rp, const Work
     using T = TileSizes<NV, EM>;
     const int ng = r.ng, tw = r.tw;
     const unsigned lane = threadIdx.x & 63, nt = nthreads();
-    WaveBatches<U> wb(p0, wctr, r.interleave, r.nblocks, r.det);
+    WaveBatches<U> wb(p0, wctr, nt, r.interleave, r.nblocks, r.det);
     PBatch<U, NV> cur, nxt;
     int64_t bcur = wb.first();
-    wb.reset(nt);
+    wb.reset();
     double *jt = smem;
     double *es = jt + T::ncur * tw;
     double *bs = es + T::ne * tw;
@@ -2005,7 +2028,7 @@ __device__ __forceinline__ void pass_b_body(const Run &r0, RunPtr rp, const Work
         nodes.issue(r, En, j1, wk.J2[0], threadIdx.x);
         dep.init(side, r, wk.st);
         __builtin_amdgcn_sched_barrier(0);
-        load_batch(cur, X, V, r.vstride, bcur, p1);
+        load_batch(cur, X, V, r.vstride, r.w, r.wu, bcur, p1);
     } else {
         dep.init(side, r, wk.st);
     }
@@ -2028,14 +2051,14 @@ __device__ __forceinline__ void pass_b_body(const Run &r0, RunPtr rp, const Work
                 tile_load(e1, wk.Ef[1], 3 * ng, nt);
                 tile_load(b1, wk.Bf[1], 2 * ng, nt);
             }
-            load_batch(cur, X, V, r.vstride, bcur, p1);
+            load_batch(cur, X, V, r.vstride, r.w, r.wu, bcur, p1);
         } else if (r.scheme == kLeapfrog) {
             predictor_fields(r, En, Bn, wk.J1[0], es, bs, r.nrep);
-            load_batch(cur, X, V, r.vstride, bcur, p1);
+            load_batch(cur, X, V, r.vstride, r.w, r.wu, bcur, p1);
             lf_full_fields(r, En, wk.J2[0], bs, e1, b1, eb, bb, r.nrep);
         } else {
             predictor_fields(r, En, Bn, wk.J1[0], es, bs, r.nrep);
-            load_batch(cur, X, V, r.vstride, bcur, p1);
+            load_batch(cur, X, V, r.vstride, r.w, r.wu, bcur, p1);
             field_update(r, wk, En, Bn, wk.J2[0], e1, b1, eb, bb, scratch, r.nrep);
         }
         lds_barrier();
@@ -2103,20 +2126,23 @@ __device__ __forceinline__ void pass_b_body(const Run &r0, RunPtr rp, const Work
     double ke = 0.0, gdev = 0.0;
     int fb = 0;
     const Run q = reload(rp);
+    settle_pointer(X);
+    settle_pointer(V);
+    settle_pointer(Xo);
+    settle_pointer(Vo);
     dep.settle();
     while (bcur < p1) {
         const int64_t bnxt = wb.claim();
         const unsigned nval = (unsigned)min(p1 - bcur, (int64_t)(64 * U));
-        double w[U];
-        load_weights(w, q.w, q.wu, bcur, p1);
-        load_batch(nxt, X, V, q.vstride, bnxt, p1);   // the last one is discarded
+        load_batch(nxt, X, V, q.vstride, q.w, q.wu, bnxt, p1);   // the last one is discarded
         bool valid[U];
-        // lanes past the end repeat the last particle, without weight
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int u = 0; u < U; ++u)
             valid[u] = lane + 64u * u < nval;
-            w[u] = valid[u] ? w[u] : 0.0;
-        }
+        if (nval < 64u * U)       // lanes past the end repeat the last particle, without weight
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                cur.w[u] = valid[u] ? cur.w[u] : 0.0;
         double vs[U][NV], x1[U], vd[U][NV];
         Pos pos[U];
         half_steps<ORDER, NV, EM, U>(q, cur.x, cur.v, eg, bs, vs, x1);
@@ -2180,13 +2206,13 @@ __device__ __forceinline__ void pass_b_body(const Run &r0, RunPtr rp, const Work
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             gdev = fmax(gdev, fabs(g[u] - 1.0));
-            ke = fma(w[u], v2[u], ke);
+            ke = fma(cur.w[u], v2[u], ke);
         }
         if constexpr (PRED) {
             double qv[U][T::ncur];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const double qw = w[u] * q.qs;
+                const double qw = cur.w[u] * q.qs;
 #pragma unroll
                 for (int c = 0; c < T::ncur; ++c)
                     qv[u][c] = qw * vn[u][c];
@@ -2255,10 +2281,10 @@ __device__ __forceinline__ void esec1_body(const Run &r0, RunPtr rp, const Work 
     const int ng = r.ng, tw = r.tw;
     const unsigned lane = threadIdx.x & 63, nt = nthreads();
     // one pass per step: alternate directions (see WaveBatches)
-    WaveBatches<U> wb(p0, wctr, r.interleave, r.nblocks, r.det, r.np, (step & 1) != 0);
+    WaveBatches<U> wb(p0, wctr, nt, r.interleave, r.nblocks, r.det, r.np, (step & 1) != 0);
     PBatch<U, NV> cur, nxt;
     int64_t bcur = wb.first();
-    wb.reset(nt);
+    wb.reset();
     double *jt = smem;
     double *es = jt + tw;
     double *eb = es + tw;
@@ -2274,7 +2300,7 @@ __device__ __forceinline__ void esec1_body(const Run &r0, RunPtr rp, const Work 
     nodes.issue(r, En, Jr, nullptr, threadIdx.x);
     dep.init(side, r, wk.st);
     __builtin_amdgcn_sched_barrier(0);
-    load_batch(cur, X, V, r.vstride, bcur, p1);
+    load_batch(cur, X, V, r.vstride, r.w, r.wu, bcur, p1);
     tile_zero(jt, tw, nt);
     tile_zero(side, tw, nt);
     rep_zero_part(Jc, ng, r.nrep, 3 * ng, slot, r.nblocks, nt);
@@ -2307,20 +2333,23 @@ __device__ __forceinline__ void esec1_body(const Run &r0, RunPtr rp, const Work 
     double ke = 0.0, gdev = 0.0;
     int fb = 0;
     const Run q = reload(rp);
+    settle_pointer(X);
+    settle_pointer(V);
+    settle_pointer(Xo);
+    settle_pointer(Vo);
     dep.settle();
     while (bcur < p1) {
         const int64_t bnxt = wb.claim();
         const unsigned nval = (unsigned)min(p1 - bcur, (int64_t)(64 * U));
-        double w[U];
-        load_weights(w, q.w, q.wu, bcur, p1);
-        load_batch(nxt, X, V, q.vstride, bnxt, p1);   // the last one is discarded
+        load_batch(nxt, X, V, q.vstride, q.w, q.wu, bnxt, p1);   // the last one is discarded
         bool valid[U];
-        // lanes past the end repeat the last particle, without weight
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int u = 0; u < U; ++u)
             valid[u] = lane + 64u * u < nval;
-            w[u] = valid[u] ? w[u] : 0.0;
-        }
+        if (nval < 64u * U)       // lanes past the end repeat the last particle, without weight
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                cur.w[u] = valid[u] ? cur.w[u] : 0.0;
         double vs[U][NV], x1[U], vd[U][NV];
         Pos pos[U];
         half_steps<ORDER, NV, false, U>(q, cur.x, cur.v, ctn, nullptr, vs, x1);
@@ -2346,7 +2375,7 @@ __device__ __forceinline__ void esec1_body(const Run &r0, RunPtr rp, const Work 
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             gdev = fmax(gdev, fabs(g[u] - 1.0));
-            ke = fma(w[u], v2[u], ke);
+            ke = fma(cur.w[u], v2[u], ke);
         }
         // step n + 1: v* from E^{n+1} at x*_{n+1}, and the centred deposit j^{n+3/2}
         double va[U][NV], xa[U], qv[U][1];
@@ -2354,7 +2383,7 @@ __device__ __forceinline__ void esec1_body(const Run &r0, RunPtr rp, const Work 
         mid_points<ORDER, U>(pos, xw, xa, q);
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            qv[u][0] = (w[u] * q.qs) * va[u][0];
+            qv[u][0] = (cur.w[u] * q.qs) * va[u][0];
         deposit_all<ORDER, 1, DEP, U>(dep, jt, tw, ng, pos, qv, valid);
         cur = nxt;
         bcur = bnxt;
@@ -2508,10 +2537,10 @@ __device__ __forceinline__ void std_pass_body(const Run &r0, RunPtr rp, const Wo
     const int ng = r.ng, tw = r.tw;
     const unsigned lane = threadIdx.x & 63, nt = nthreads();
     // one pass per step: alternate directions (see WaveBatches)
-    WaveBatches<U> wb(p0, wctr, r.interleave, r.nblocks, r.det, r.np, (step & 1) != 0);
+    WaveBatches<U> wb(p0, wctr, nt, r.interleave, r.nblocks, r.det, r.np, (step & 1) != 0);
     PBatch<U, NV> cur, nxt;
     int64_t bcur = wb.first();
-    wb.reset(nt);
+    wb.reset();
     double *jt = smem;
     double *es = jt + tw;
     double *side = es + tw;
@@ -2521,7 +2550,7 @@ __device__ __forceinline__ void std_pass_body(const Run &r0, RunPtr rp, const Wo
     const double eh0 = Eh[min((int)threadIdx.x, ng - 1)];
     dep.init(side, r, wk.st, 1);
     __builtin_amdgcn_sched_barrier(0);
-    load_batch(cur, X, V, r.vstride, bcur, p1);
+    load_batch(cur, X, V, r.vstride, r.w, r.wu, bcur, p1);
     tile_zero(jt, tw, nt);
     tile_zero(side, tw, nt);
     rep_zero_part(Jc, ng, r.nrep, 3 * ng, slot, r.nblocks, nt);
@@ -2544,20 +2573,23 @@ __device__ __forceinline__ void std_pass_body(const Run &r0, RunPtr rp, const Wo
 
     double ke1 = 0.0, ke0 = 0.0;
     const Run q = reload(rp);
+    settle_pointer(X);
+    settle_pointer(V);
+    settle_pointer(Xo);
+    settle_pointer(Vo);
     dep.settle();
     while (bcur < p1) {
         const int64_t bnxt = wb.claim();
         const unsigned nval = (unsigned)min(p1 - bcur, (int64_t)(64 * U));
-        double w[U];
-        load_weights(w, q.w, q.wu, bcur, p1);
-        load_batch(nxt, X, V, q.vstride, bnxt, p1);   // the last one is discarded
+        load_batch(nxt, X, V, q.vstride, q.w, q.wu, bnxt, p1);   // the last one is discarded
         bool valid[U];
-        // lanes past the end repeat the last particle, without weight
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int u = 0; u < U; ++u)
             valid[u] = lane + 64u * u < nval;
-            w[u] = valid[u] ? w[u] : 0.0;
-        }
+        if (nval < 64u * U)       // lanes past the end repeat the last particle, without weight
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                cur.w[u] = valid[u] ? cur.w[u] : 0.0;
         double xs[U], vn[U][NV], x1[U], xw[U];
         Pos pos[U];
 #pragma unroll
@@ -2597,9 +2629,9 @@ __device__ __forceinline__ void std_pass_body(const Run &r0, RunPtr rp, const Wo
                 v2 = fma(vn[u][k], vn[u][k], v2);
                 v20 = fma(cur.v[u][k], cur.v[u][k], v20);
             }
-            ke1 = fma(w[u], v2, ke1);
-            ke0 = fma(w[u], v20, ke0);
-            qv[u][0] = w[u] * q.qs;
+            ke1 = fma(cur.w[u], v2, ke1);
+            ke0 = fma(cur.w[u], v20, ke0);
+            qv[u][0] = cur.w[u] * q.qs;
             pos[u] = locate<ORDER>(fma(q.hdt, vn[u][0], xw[u]), q.inv_h, 0.0);
         }
         deposit_all<ORDER, 1, DEP, U>(dep, jt, tw, ng, pos, qv, valid);
