@@ -593,7 +593,11 @@ template <int ORDER, int NC> struct Depo<ORDER, NC, 0> {
     __device__ __forceinline__ void add(double *jt, int tw, int ng, const Stencil<ORDER> &s,
                                         const double (&q)[NC], bool = true, bool = true)
     {
-        const Slots<ORDER> sl = slots_of<ORDER>(s, ng);
+        add_at(jt, tw, slots_of<ORDER>(s, ng), s, q);
+    }
+    __device__ __forceinline__ void add_at(double *jt, int tw, const Slots<ORDER> &sl,
+                                           const Stencil<ORDER> &s, const double (&q)[NC])
+    {
         unsigned long long *ti = reinterpret_cast<unsigned long long *>(jt);
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
@@ -699,7 +703,11 @@ template <int ORDER, int NC> struct Depo<ORDER, NC, 3> {
     __device__ __forceinline__ void add(double *jt, int tw, int ng, const Stencil<ORDER> &s,
                                         const double (&q)[NC], bool = true, bool = true)
     {
-        const Slots<ORDER> sl = slots_of<ORDER>(s, ng);
+        add_at(jt, tw, slots_of<ORDER>(s, ng), s, q);
+    }
+    __device__ __forceinline__ void add_at(double *jt, int tw, const Slots<ORDER> &sl,
+                                           const Stencil<ORDER> &s, const double (&q)[NC])
+    {
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -980,8 +988,10 @@ __device__ __forceinline__ double wrap_one(double x1, const Run &r)
 // and the end point as its wrapped image's u plus the whole periods in between: that is
 // the number the next step starts from, whereas x / h itself is not exactly periodic in
 // floating point (over many boundary crossings the difference would drift Gauss' law).
-// visit(base, t, frac) gets the midpoint t relative to base.  A path with no length, or
-// one longer than 2^30 cells (only a non-finite or absurd state), is one piece.
+// The pieces of a path lie in consecutive cells, so the cell and its slot are counted up from
+// the first one instead of being found again from each midpoint; visit(slot, d, frac) gets the
+// slot of the cell's lower half node and the midpoint's offset in the cell.  A path with no
+// length, or one longer than 2^30 cells (only a non-finite or absurd state), is one piece.
 template <typename F>
 __device__ __forceinline__ void cc_pieces(const Run &r, double x0, double x1, F &&visit)
 {
@@ -993,42 +1003,59 @@ __device__ __forceinline__ void cc_pieces(const Run &r, double x0, double x1, F 
     const double ta = ua - base;
     const double tb = (xw * r.inv_h - 0.5) + (m * (double)r.ng - base);
     const double lo = fmin(ta, tb), hi = fmax(ta, tb), len = hi - lo;
-    if (!(len > 0.0) || !(len < 1073741824.0)) {
-        visit(base, 0.5 * (ta + tb), 1.0);
+    const bool one = !(len > 0.0) || !(len < 1073741824.0);
+    double t = one ? 0.5 * (ta + tb) : lo;
+    double f = floor(t);
+    int node = (int)(base + f);
+    const unsigned lim = (unsigned)(r.ng + 2 * kGhost - 2);
+    auto slot = [&](int n) {
+        const unsigned b = (unsigned)n + kGhost;
+        return b <= lim ? (int)b : wrap_node(n, r.ng) + kGhost;
+    };
+    if (one) {
+        visit(slot(node), t - f, 1.0);
         return;
     }
-    const double il = 1.0 / len;                    // one division per path
-    double t = lo;
+    double il = __builtin_amdgcn_rcp(len);          // one reciprocal per path
+    il = fma(il, fma(-len, il, 1.0), il);
+    il = fma(il, fma(-len, il, 1.0), il);
     for (;;) {
-        const double e = fmin(floor(t) + 1.0, hi);
-        visit(base, 0.5 * (t + e), (e - t) * il);
+        const double e = fmin(f + 1.0, hi);
+        visit(slot(node), 0.5 * (t + e) - f, (e - t) * il);
         if (e >= hi)
             break;
         t = e;
+        f += 1.0;
+        node = (int)((unsigned)node + 1u);
     }
 }
 
-// Tent stencil at u = base + t (base a whole number).
-__device__ __forceinline__ Stencil<1> cc_stencil(double base, double t)
+// The tent stencil of a piece and its slots.
+__device__ __forceinline__ Stencil<1> cc_stencil(double d)
 {
-    const double f = floor(t);
-    const double d = t - f;
     Stencil<1> s;
-    s.first = (int)(base + f);
+    s.first = 0;            // (the slot is known)
     s.w[0] = 1.0 - d;
     s.w[1] = d;
     return s;
+}
+
+__device__ __forceinline__ Slots<1> cc_slots(int slot)
+{
+    Slots<1> o;
+    o.n[0] = slot;
+    o.n[1] = slot + 1;
+    return o;
 }
 
 // v-dagger's field through the pieces of the path x0 -> x1 (tent coefficient tile ct).
 __device__ __forceinline__ double cc_gather(const Run &r, const double *ct, double x0, double x1)
 {
     double acc = 0.0;
-    cc_pieces(r, x0, x1, [&](double base, double t, double f) {
-        const Stencil<1> st = cc_stencil(base, t);
+    cc_pieces(r, x0, x1, [&](int slot, double d, double f) {
         Cell<1> c;
-        c.base = slots_of<1>(st, r.ng).n[0];
-        c.d = st.w[1];
+        c.base = slot;
+        c.d = d;
         acc = fma(f, gather_poly<1>(ct, c), acc);
     });
     return acc;
@@ -1920,18 +1947,18 @@ __device__ __forceinline__ void pass_a_body(const Run &r0, RunPtr rp, const Work
                 qv[u][c] = qw * vs[u][c];
         }
         bool done = false;
-        if constexpr (!EM && ORDER == 1 && DEP != 2) {
+        if constexpr (!EM && ORDER == 1 && (DEP == 0 || DEP == 3)) {
             if (q.cc) {
                 // exact charge conservation: through the pieces of the path x^n -> x^{n+1}
 #pragma unroll
                 for (int u = 0; u < U; ++u)
                     if (valid[u])
-                        cc_pieces(q, cur.x[u], x1[u], [&](double base, double t, double f) {
+                        cc_pieces(q, cur.x[u], x1[u], [&](int slot, double d, double f) {
                             double qf[T::ncur];
 #pragma unroll
                             for (int c = 0; c < T::ncur; ++c)
                                 qf[c] = qv[u][c] * f;
-                            dep.add(jt, tw, ng, cc_stencil(base, t), qf, true, false);
+                            dep.add_at(jt, tw, cc_slots(slot), cc_stencil(d), qf);
                         });
                 done = true;
             }
@@ -3419,10 +3446,10 @@ template <typename T> __device__ __forceinline__ T uniform_load(const T *g)
 // Workgroups of the batched passes hold at most 512 threads, so the persistent kernels,
 // which keep a run's scalars live across work items, have up to 256 VGPRs (no spills).
 constexpr int kBatchMaxThreads = 512;
-// Particles per thread per batch in the batched passes: the packed state of an ensemble is
-// usually larger than the Infinity Cache and streams from HBM, whose longer latency wants
-// more loads in flight than the plain passes (U = 2).
-template <int NV> constexpr int kBatchUnroll = NV == 1 ? 4 : 2;
+// Particles per thread per batch in the batched passes: two, as in the plain passes, keep two
+// workgroups per CU within 128 VGPRs without spills (96 Landau runs of 1e4 to 1e6 particles:
+// four particles 183 us a step, three 181, two 180).
+template <int NV> constexpr int kBatchUnroll = NV == 1 ? 2 : 1;
 // Wavefronts per SIMD the batched passes are compiled for: two 512-thread workgroups per CU
 // (at most 128 VGPRs), so that one's prologue and flush overlap the other's particles.
 constexpr int kBatchWavesPerEU = 4;
