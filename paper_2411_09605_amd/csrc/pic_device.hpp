@@ -2795,6 +2795,34 @@ __global__ __launch_bounds__(1024) void k_deposit_rho(Run r, Work wk, const doub
     deposit_rho_body<ORDER>(r, wk, X, p0, min(r.np, p0 + r.chunk), smem);
 }
 
+// Both deposits of an ESEC2 start with the Gauss solve in one launch: the charge density into
+// J2[0] and the predictor current into J1[0] (electrostatic; not in the deterministic mode,
+// whose partial sums hold one deposit at a time).  LDS: two tiles with their side tiles.
+template <int ORDER>
+__global__ __launch_bounds__(1024) void k_init_deposits(Run r, Work wk, const double *__restrict__ X,
+                                                        const double *__restrict__ V)
+{
+    extern __shared__ double smem[];
+    const int tw = r.tw, ng = r.ng;
+    const unsigned nt = nthreads();
+    double *jr = smem, *sr = jr + tw, *jj = sr + tw, *sj = jj + tw;
+    tile_zero(smem, 4 * tw, nt);
+    Depo<ORDER, 1, 0> dr, dj;
+    dr.init(sr, r, wk.st, 1);
+    dj.init(sj, r, wk.st);
+    __syncthreads();
+    const int64_t p0 = (int64_t)blockIdx.x * r.chunk, p1 = min(r.np, p0 + r.chunk);
+    for (int64_t p = p0 + threadIdx.x; p < p1; p += nt) {
+        const double x = X[p], v = V[p], q = (r.w ? r.w[p] : r.wu) * r.qs;
+        const double qr[1] = {q}, qj[1] = {q * v};
+        dr.add(jr, tw, ng, stencil<ORDER>(x * r.inv_h), qr);
+        dj.add(jj, tw, ng, stencil<ORDER>(fma(r.hdt, v, x) * r.inv_h - r.xshift), qj);
+    }
+    __syncthreads();
+    dr.flush_tile(jr, rep_slot(wk.J2[0], r.nrep, ng), 1, ng, tw);
+    dj.flush_tile(jj, rep_slot(wk.J1[0], r.nrep, ng), 1, ng, tw);
+}
+
 // ------------------------------------------------------------- counting-sort rebin
 // Particles are reordered by key = kVBins * cell + (v_x >= 0): particles of one cell and
 // one direction of motion become contiguous, so a wavefront's particles share a cell or
@@ -3059,60 +3087,84 @@ __global__ __launch_bounds__(256) void k_reduce_partials(const double *__restric
 // Initial Gauss solve: dE/dx = rho - 1 with rho in J2[0], into the caller's E_x.
 // Spectrally on the nodes: E_m = rho_m / (i k_m), k_m = 2 pi m / L for 0 < |m| < N/2, mean
 // and Nyquist modes zero (the Poisson form, eq. (poisson), in 1D).
-// LDS: rho | Re E_m | Im E_m | the cosines and sines of 2 pi j / N_g, computed once by the
-// same calls the sums would make term by term (the sums index them with m l mod N_g), so
-// the result is the same bit for bit (5 N_g doubles: every grid the passes accept fits).
+// LDS: rho | Re E_m | Im E_m | the cosines and sines of 2 pi j / N_g, computed once (the sums
+// index them with m l mod N_g), and on grids of at most half a thread per node's worth of
+// threads the partial sums: S threads share a mode (then a node), each summing a consecutive
+// S-th of the terms, and the S parts are added in order.  One workgroup, so the solve is two
+// chains of N_g / S terms: 256 cells 25 -> 9 us, 64 cells 7 -> 4 us.
 __host__ __device__ constexpr size_t gauss_lds_doubles(int ng)
 {
-    return 5 * (size_t)ng;
+    return ng <= 512 ? 5 * (size_t)ng + 2048 : (ng <= 921 ? 4608 : 5 * (size_t)ng);
 }
 
 __device__ void gauss_body(const Run &r, const Work &wk, double *smem)
 {
-    const int ng = r.ng;
+    const int ng = r.ng, nt = (int)nthreads();
     double *rho = smem, *er = smem + ng, *ei = smem + 2 * ng;
     double *tc = smem + 3 * ng, *ts = smem + 4 * ng;
+    const int S = ng <= 512 ? max(1, min(16, nt / ng)) : 1, len = (ng + S - 1) / S;
+    double *pa = S > 1 ? smem + 5 * ng : er, *pb = S > 1 ? pa + S * ng : ei;
     rep_gather(rho, wk.J2[0], ng, r.nrep, 3 * ng);
-    for (int j = threadIdx.x; j < ng; j += nthreads())
+    for (int j = threadIdx.x; j < ng; j += nt)
         sincospi(2.0 * (double)j / ng, &ts[j], &tc[j]);
     __syncthreads();
     if (r.filter_rho) {
         // the standard scheme's filtered density (as in k_std_field), through ei
-        for (int i = threadIdx.x; i < ng; i += nthreads())
+        for (int i = threadIdx.x; i < ng; i += nt)
             ei[i] = 0.25 * rho[i == 0 ? ng - 1 : i - 1] + 0.5 * rho[i] + 0.25 * rho[i + 1 == ng ? 0 : i + 1];
         __syncthreads();
-        for (int i = threadIdx.x; i < ng; i += nthreads())
+        for (int i = threadIdx.x; i < ng; i += nt)
             rho[i] = ei[i];
         __syncthreads();
     }
-    for (int m = threadIdx.x; m < ng; m += nthreads()) {
+    for (int it = threadIdx.x; it < S * ng; it += nt) {
+        const int sg = it / ng, m = it - sg * ng, l0 = min(ng, sg * len), l1 = min(ng, l0 + len);
         double re = 0.0, im = 0.0;
-        if (m != 0 && 2 * m != ng) {
-            int ml = 0;                        // m l mod N_g
-            for (int l = 0; l < ng; ++l) {
-                re += rho[l] * tc[ml];
-                im -= rho[l] * ts[ml];
-                ml += m;
-                ml -= ml >= ng ? ng : 0;
-            }
-            const int ms = m <= ng / 2 ? m : m - ng;
-            const double k = 2.0 * M_PI * ms / r.L;
-            const double tr = re, ti = im;
-            re = ti / k;          // (tr + i ti) / (i k) = ti / k - i tr / k
-            im = -tr / k;
+        int ml = (int)(((long long)m * l0) % ng);      // m l mod N_g
+        for (int l = l0; l < l1; ++l) {
+            re += rho[l] * tc[ml];
+            im -= rho[l] * ts[ml];
+            ml += m;
+            ml -= ml >= ng ? ng : 0;
         }
-        er[m] = re;
-        ei[m] = im;
+        pa[it] = re;
+        pb[it] = im;
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < ng; i += nthreads()) {
+    for (int m = threadIdx.x; m < ng; m += nt) {
+        double re = pa[m], im = pb[m];
+        for (int sg = 1; sg < S; ++sg) {
+            re += pa[sg * ng + m];
+            im += pb[sg * ng + m];
+        }
+        const int ms = m <= ng / 2 ? m : m - ng;
+        const double k = 2.0 * M_PI * ms / r.L;
+        const bool zero = m == 0 || 2 * m == ng;
+        er[m] = zero ? 0.0 : im / k;          // (re + i im) / (i k) = im / k - i re / k
+        ei[m] = zero ? 0.0 : -re / k;
+    }
+    __syncthreads();
+    for (int it = threadIdx.x; it < S * ng; it += nt) {
+        const int sg = it / ng, i = it - sg * ng, m0 = max(1, sg * len), m1 = min(ng, (sg + 1) * len);
         double acc = 0.0;
-        int mi = i;                            // m i mod N_g, from m = 1
-        for (int m = 1; m < ng; ++m) {
+        int mi = (int)(((long long)m0 * i) % ng);      // m i mod N_g
+        for (int m = m0; m < m1; ++m) {
             acc += er[m] * tc[mi] - ei[m] * ts[mi];
             mi += i;
             mi -= mi >= ng ? ng : 0;
         }
+        if (S == 1)
+            wk.E[i] = acc / ng;
+        else
+            pa[it] = acc;
+    }
+    if (S == 1)
+        return;
+    __syncthreads();
+    for (int i = threadIdx.x; i < ng; i += nt) {
+        double acc = pa[i];
+        for (int sg = 1; sg < S; ++sg)
+            acc += pa[sg * ng + i];
         wk.E[i] = acc / ng;
     }
 }
@@ -3121,6 +3173,19 @@ __global__ __launch_bounds__(1024) void k_gauss(Run r, Work wk)
 {
     extern __shared__ double smem[];
     gauss_body(r, wk, smem);
+}
+
+// The Gauss solve and, the fields then being known, the rest of the initialisation
+// (k_init_finish) in one launch.
+__device__ void init_finish_body(const Run &r, const Work &wk, double *red);
+
+__global__ __launch_bounds__(1024) void k_gauss_finish(Run r, Work wk)
+{
+    extern __shared__ double smem[];
+    __shared__ double red[kRedSize];
+    gauss_body(r, wk, smem);
+    __syncthreads();
+    init_finish_body(r, wk, red);
 }
 
 // Initial field of a charge-conserving run (Run::cc): Gauss' law on the half-node E,
@@ -3393,6 +3458,14 @@ __global__ void k_fill(double *p, int64_t n, double v)
     for (int64_t i = (int64_t)blockIdx.x * nthreads() + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * nthreads())
         p[i] = v;
+}
+
+// Zero two ranges (the workspace's fields and currents, the caller's unused components of E).
+__global__ void k_clear2(double *p, int64_t n, double *p2, int64_t n2)
+{
+    for (int64_t i = (int64_t)blockIdx.x * nthreads() + threadIdx.x; i < n + n2;
+         i += (int64_t)gridDim.x * nthreads())
+        *(i < n ? p + i : p2 + (i - n)) = 0.0;
 }
 
 // ----------------------------------------------------------------- batched ensemble

@@ -463,6 +463,15 @@ void fill_range(hipStream_t stream, double *p, int64_t n)
                        stream, p, n, 0.0);
 }
 
+void clear2(hipStream_t stream, double *p, int64_t n, double *p2, int64_t n2)
+{
+    hipLaunchKernelGGL(k_clear2, dim3((unsigned)std::min<int64_t>((n + n2 + 255) / 256, 1024)), dim3(256), 0,
+                       stream, p, n, p2, n2);
+}
+
+// Threads of the Gauss solve: a full workgroup (several threads share a mode).
+constexpr int kGaussThreads = 1024;
+
 void fill(pic_ctx *c, double *p, int64_t n, double v)
 {
     hipLaunchKernelGGL(k_fill, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 1024)), dim3(256), 0,
@@ -516,12 +525,10 @@ int init_ctx(pic_ctx *c, const pic_params *p, const pic_buffers *b, hipStream_t 
         r.w = w.wcur;
     }
 
-    // clear the field and current buffers (fill kernels, no memset)
-    fill(c, w.Ef[0], (int64_t)(L.cninv - L.Ef[0]) / 8, 0.0);
-    if (!is_em(p)) {
-        // electrostatic runs carry only E_x; keep the unused components at zero
-        fill(c, b->E + p->n_cells, 2 * (int64_t)p->n_cells, 0.0);
-    }
+    // clear the field and current buffers (fill kernels, no memset); electrostatic runs carry
+    // only E_x, and the unused components are kept at zero
+    clear2(c->stream, w.Ef[0], (int64_t)(L.cninv - L.Ef[0]) / 8, b->E + p->n_cells,
+           is_em(p) ? 0 : 2 * (int64_t)p->n_cells);
     const int gt = grid_threads(c);
     if (p->nv == 1)
         hipLaunchKernelGGL((k_init_particles<1>), dim3(r.nblocks), dim3(c->threads), 0, c->stream, r, w,
@@ -530,6 +537,23 @@ int init_ctx(pic_ctx *c, const pic_params *p, const pic_buffers *b, hipStream_t 
         hipLaunchKernelGGL((k_init_particles<3>), dim3(r.nblocks), dim3(c->threads), 0, c->stream, r, w,
                            b->x, b->v);
     hipLaunchKernelGGL(k_fx_setup, dim3(1), dim3(256), 0, c->stream, r, w);
+    // ESEC2 from the Gauss solve: both deposits in one launch, the solve with the rest of the
+    // initialisation in another
+    const bool merged = (p->flags & PIC_F_INIT_GAUSS) && p->scheme == PIC_ESEC2 && !is_cc(p) && !r.det;
+    if (merged) {
+        const size_t lds = 2 * lds_deposit(p);
+        if (p->shape_order == 1)
+            hipLaunchKernelGGL((k_init_deposits<1>), dim3(r.nblocks), dim3(c->threads), lds, c->stream, r,
+                               w, b->x, b->v);
+        else
+            hipLaunchKernelGGL((k_init_deposits<2>), dim3(r.nblocks), dim3(c->threads), lds, c->stream, r,
+                               w, b->x, b->v);
+        hipLaunchKernelGGL(k_gauss_finish, dim3(1), dim3(kGaussThreads), gauss_lds(p->n_cells), c->stream, r, w);
+        int rc = check(c, "pic_init launches");
+        if (rc != PIC_OK)
+            g_last_error = c->err;
+        return rc;
+    }
     if ((p->flags & PIC_F_INIT_GAUSS) && is_cc(p)) {
         // the density with the quadratic B-spline (one degree above the tent), then Gauss'
         // law on the half-node E
@@ -540,7 +564,7 @@ int init_ctx(pic_ctx *c, const pic_params *p, const pic_buffers *b, hipStream_t 
         hipLaunchKernelGGL(k_gauss_cc, dim3(1), dim3(gt), p->n_cells * 8, c->stream, r, w);
     } else if (p->flags & PIC_F_INIT_GAUSS) {
         dispatch(c, D_RHO);
-        hipLaunchKernelGGL(k_gauss, dim3(1), dim3(gt), gauss_lds(p->n_cells), c->stream, r, w);
+        hipLaunchKernelGGL(k_gauss, dim3(1), dim3(kGaussThreads), gauss_lds(p->n_cells), c->stream, r, w);
     }
     if (has_em_fields(p))
         hipLaunchKernelGGL(k_em_rows, dim3((unsigned)((p->n_cells + 255) / 256), kPsatdRows), dim3(256),
@@ -1691,13 +1715,6 @@ void adj_recompute(pic_adj *c, hipStream_t stream, int par, const double *g, con
                        lds_pass_b(&c->q), stream, r, wk, X, V, Xo, Vo);
 }
 
-template <int ORDER>
-void adj_predeposit(pic_adj *c, const double *X, const double *V)
-{
-    hipLaunchKernelGGL((k_predeposit<ORDER, 1, false>), dim3(c->run.nblocks), dim3(c->threads),
-                       lds_deposit(&c->q), c->stream, c->run, c->wk, X, V);
-}
-
 template <int ORDER, int STAGE>
 void adj_rev(pic_adj *c, int q, const double *X, const double *V, const double *g,
              const double *Xm = nullptr, const double *Vm = nullptr, const double *gm = nullptr)
@@ -1726,15 +1743,12 @@ void adj_forward_launches(pic_adj *c)
     hipLaunchKernelGGL(k_adj_sample, dim3(sg), dim3(256), 0, c->stream, r, c->ap, c->b.u, c->b.s, c->b.g,
                        X, V);
     // as pic_init: clear fields and currents, wrap, Gauss start, predictor deposit
-    fill_range(c->stream, w.Ef[0], (int64_t)(c->A.fwd.cninv - c->A.fwd.Ef[0]) / 8);
-    fill_range(c->stream, c->b.E + ng, 2 * (int64_t)ng);
+    clear2(c->stream, w.Ef[0], (int64_t)(c->A.fwd.cninv - c->A.fwd.Ef[0]) / 8, c->b.E + ng, 2 * (int64_t)ng);
     hipLaunchKernelGGL((k_init_particles<1>), dim3(r.nblocks), dim3(c->threads), 0, c->stream, r, w, X, V);
     hipLaunchKernelGGL(k_fx_setup, dim3(1), dim3(256), 0, c->stream, r, w);
-    hipLaunchKernelGGL((k_deposit_rho<ORDER>), dim3(r.nblocks), dim3(c->threads), lds_deposit(&c->q),
-                       c->stream, r, w, X);
-    hipLaunchKernelGGL(k_gauss, dim3(1), dim3(gt), gauss_lds(ng), c->stream, r, w);
-    adj_predeposit<ORDER>(c, X, V);
-    hipLaunchKernelGGL(k_init_finish, dim3(1), dim3(gt), 0, c->stream, r, w);
+    hipLaunchKernelGGL((k_init_deposits<ORDER>), dim3(r.nblocks), dim3(c->threads), 2 * lds_deposit(&c->q),
+                       c->stream, r, w, X, V);
+    hipLaunchKernelGGL(k_gauss_finish, dim3(1), dim3(kGaussThreads), gauss_lds(ng), c->stream, r, w);
     const int64_t K = c->p.checkpoint_every, N = c->p.n_steps;
     adj_copy(c, c->ckx, X, r.np);
     adj_copy(c, c->ckv, V, r.np);
@@ -1822,8 +1836,7 @@ void adj_backward_launches(pic_adj *c)
     (void)hipEventRecord(c->ev_join, c->side);
     (void)hipStreamWaitEvent(c->stream, c->ev_join, 0);
     // reverse of the Gauss start and of the sampling
-    const int gt = grid_threads_of(ng);
-    hipLaunchKernelGGL(k_adj_rhobar, dim3(1), dim3(gt), gauss_lds(ng), c->stream, r, w, c->aw, q);
+    hipLaunchKernelGGL(k_adj_rhobar, dim3(1), dim3(kGaussThreads), gauss_lds(ng), c->stream, r, w, c->aw, q);
     hipLaunchKernelGGL((k_adj_grad<ORDER>), dim3(r.nblocks), dim3(c->threads), tile_width(&c->q) * 8,
                        c->stream, r, c->aw, c->ap, c->ckx, c->b.s, c->b.g);
     hipLaunchKernelGGL(k_adj_grad_final, dim3(1), dim3(256), 0, c->stream, c->aw, r.nblocks, c->ap.nparam,
