@@ -276,21 +276,24 @@ void k_adj_reverse(Run r, AdjWork aw, AdjParams ap, int q, const double *__restr
     bool loaded = false;
     for (int base = 0; base < ng; base += (int)nt) {
         const int i = base + (int)threadIdx.x, j = min(i, ng - 1);
-        const double fe = g[3 * ng + j], fb = g[4 * ng + j];
-        double fem = 0.0, fbm = 0.0, e1 = 0.0, lam = 0.0, g1 = 0.0, g2 = 0.0;
-        if constexpr (STAGE == 4) {
-            fem = gm[3 * ng + j];
-            fbm = gm[4 * ng + j];
-        }
-        double a1[STAGE >= 2 ? kMaxRep : 1], a2[STAGE >= 3 ? kMaxRep : 1];
-        if constexpr (STAGE >= 2) {
-            e1 = g[5 * ng + j];
-            lam = aw.lam[q][j];
+        double fe = 0.0, fb = 0.0, fem = 0.0, fbm = 0.0, e1 = 0.0, lam = 0.0, g1 = 0.0, g2 = 0.0;
+        double a1[STAGE >= 2 ? kMaxRep : 1] = {}, a2[STAGE >= 3 ? kMaxRep : 1] = {};
+        if (__builtin_amdgcn_readfirstlane(i) < ng) {        // (the wavefront has nodes)
+            fe = g[3 * ng + j];
+            fb = g[4 * ng + j];
+            if constexpr (STAGE == 4) {
+                fem = gm[3 * ng + j];
+                fbm = gm[4 * ng + j];
+            }
+            if constexpr (STAGE >= 2) {
+                e1 = g[5 * ng + j];
+                lam = aw.lam[q][j];
 #pragma unroll
-            for (int k = 0; k < kMaxRep; ++k) {
-                a1[k] = (aw.G1[q] + (size_t)min(k, nrep - 1) * ng)[j];
-                if constexpr (STAGE >= 3)
-                    a2[k] = (aw.G2[q] + (size_t)min(k, nrep - 1) * ng)[j];
+                for (int k = 0; k < kMaxRep; ++k) {
+                    a1[k] = (aw.G1[q] + (size_t)min(k, nrep - 1) * ng)[j];
+                    if constexpr (STAGE >= 3)
+                        a2[k] = (aw.G2[q] + (size_t)min(k, nrep - 1) * ng)[j];
+                }
             }
         }
         if (!loaded) {

@@ -298,6 +298,18 @@ __device__ __forceinline__ int wrap_node(int i, int ng)
     return r < 0 ? r + ng : r;
 }
 
+// The node of a tile slot (an index within kGhost of [0, ng), ng >= 3): two conditional steps
+// either way, without the set-up of a modulo.
+static_assert(kGhost <= 6, "two periods of the smallest grid cover the ghosts");
+__device__ __forceinline__ int wrap_ghost(int i, int ng)
+{
+    i += i < 0 ? ng : 0;
+    i += i < 0 ? ng : 0;
+    i -= i >= ng ? ng : 0;
+    i -= i >= ng ? ng : 0;
+    return i;
+}
+
 // LDS tiles hold N_g nodes plus kGhost periodic copies on each side: node i of
 // component c sits at slot c * tw + kGhost + i (tw = N_g + 2 kGhost).  The ORDER + 1
 // slots of a stencil are always consecutive: a stencil whose nodes fall inside the padded
@@ -491,7 +503,7 @@ template <int ORDER, typename F>
 __device__ __forceinline__ void coef_fill(double *ct, F &&f, int ng, int tw, unsigned nt)
 {
     for (int s = threadIdx.x; s < tw - ORDER; s += nt) {
-        const int i0 = wrap_node(s - kGhost, ng), i1 = i0 + 1 == ng ? 0 : i0 + 1;
+        const int i0 = wrap_ghost(s - kGhost, ng), i1 = i0 + 1 == ng ? 0 : i0 + 1;
         const double e0 = f(i0), e1 = f(i1);
         if constexpr (ORDER == 1) {
             ct[2 * s] = e0;
@@ -515,7 +527,7 @@ __device__ __forceinline__ void tile_flush(const double *tile, double *J, int nc
         for (int j = threadIdx.x; j < tw; j += nthreads()) {
             const double val = tile[c * tw + j];
             if (val != 0.0)
-                unsafeAtomicAdd(&J[c * ng + wrap_node(j - kGhost, ng)], val);
+                unsafeAtomicAdd(&J[c * ng + wrap_ghost(j - kGhost, ng)], val);
         }
 }
 
@@ -691,7 +703,7 @@ template <int ORDER, int NC> struct Depo<ORDER, NC, 0> {
             for (int j = threadIdx.x; j < tw; j += nthreads()) {
                 const double val = value(jt, c * tw + j);
                 if (val != 0.0)
-                    unsafeAtomicAdd(&J[c * ng + wrap_node(j - kGhost, ng)], val);
+                    unsafeAtomicAdd(&J[c * ng + wrap_ghost(j - kGhost, ng)], val);
             }
     }
 };
@@ -1258,9 +1270,12 @@ __device__ __forceinline__ double *rep_slot(double *J, int nrep, int ng)
 
 // Where a workgroup's deposit tile goes: its replica of the current J, or in the
 // deterministic mode its own row of the partial sums (k_reduce_partials then writes J).
+// Called in the prologue, under the loads (its modulo is a chain of 20 instructions).
 __device__ __forceinline__ double *dep_target(const Run &r, const Work &wk, double *J)
 {
-    return r.det ? wk.part + (size_t)blockIdx.x * 3 * r.ng : rep_slot(J, r.nrep, r.ng);
+    double *t = r.det ? wk.part + (size_t)blockIdx.x * 3 * r.ng : rep_slot(J, r.nrep, r.ng);
+    settle_pointer(t);
+    return t;
 }
 
 // A deterministic-mode deposit met a value it cannot hold: report it with the next record.
@@ -1292,7 +1307,7 @@ __device__ __forceinline__ void ghost_fill(double *tile, int ncomp, int ng, int 
     for (int idx = threadIdx.x; idx < ncomp * 2 * kGhost; idx += nt) {
         const int c = idx / (2 * kGhost), j = idx % (2 * kGhost);
         const int slot = j < kGhost ? j : ng + j;
-        tile[c * tw + slot] = tile[c * tw + wrap_node(slot - kGhost, ng) + kGhost];
+        tile[c * tw + slot] = tile[c * tw + wrap_ghost(slot - kGhost, ng) + kGhost];
     }
 }
 
@@ -1493,6 +1508,11 @@ template <bool TWO> struct NodeLoad {
     __device__ __forceinline__ void issue(const Run &r, const double *E, const double *J1,
                                           const double *J2, int node)
     {
+        live = J1 ? r.nrep : 0;
+        // (wavefronts without a node load nothing: the loads of a 1024-thread workgroup on
+        // 256 cells would otherwise keep the CU's memory pipe busy for about a microsecond)
+        if (__builtin_amdgcn_readfirstlane(node) >= r.ng)
+            return;
         const unsigned i = (unsigned)min(node, r.ng - 1);
         const unsigned rs = 3u * (unsigned)r.ng;
         const double *A = J1 ? J1 : E;
@@ -1504,7 +1524,6 @@ template <bool TWO> struct NodeLoad {
             if constexpr (TWO)
                 b[k] = (J2 + (size_t)((unsigned)min(k, r.nrep - 1) * rs))[i];
         }
-        live = J1 ? r.nrep : 0;
     }
     int live;             // replicas of J1 that count
     __device__ __forceinline__ void commit(const Run &r, int i, double *re, double *ra, double *rb,
@@ -1883,6 +1902,7 @@ __device__ __forceinline__ void pass_a_body(const Run &r0, RunPtr rp, const Work
     }
     tile_zero(jt, T::ncur * tw, nt);
     tile_zero(side, T::ncur * tw, nt);
+    double *target = dep_target(r, wk, wk.J2[0]);
     // the currents of the next step accumulate into the other buffers (nothing reads them
     // in this pass): every workgroup clears its share
     if (r.scheme != 1)
@@ -1974,7 +1994,7 @@ __device__ __forceinline__ void pass_a_body(const Run &r0, RunPtr rp, const Work
     dep.finish(jt, tw, ng);
     flag_over(dep, wk);
     lds_barrier();
-    dep.flush_tile(jt, dep_target(q, wk, wk.J2[0]), T::ncur, ng, tw);
+    dep.flush_tile(jt, target, T::ncur, ng, tw);
 }
 
 template <int ORDER, int NV, bool EM, int DEP>
@@ -2063,6 +2083,7 @@ __device__ __forceinline__ void pass_b_body(const Run &r0, RunPtr rp, const Work
         tile_zero(jt, T::ncur * tw, nt);
         tile_zero(side, T::ncur * tw, nt);
     }
+    double *target = PRED ? dep_target(r, wk, wk.J1[1]) : nullptr;
     if constexpr (EM) {
         if (r.em_fields) {
             // the fields v-dagger gathers come from the field launch before this pass, which
@@ -2260,7 +2281,7 @@ __device__ __forceinline__ void pass_b_body(const Run &r0, RunPtr rp, const Work
     wave_partials<0xcu>(sc, red);
     lds_barrier();
     if constexpr (PRED)
-        dep.flush_tile(jt, dep_target(q, wk, wk.J1[1]), T::ncur, ng, tw);
+        dep.flush_tile(jt, target, T::ncur, ng, tw);
     write_scalars(wk.spart + (size_t)slot * kNS, red, nt);
 }
 
@@ -2330,6 +2351,7 @@ __device__ __forceinline__ void esec1_body(const Run &r0, RunPtr rp, const Work 
     load_batch(cur, X, V, r.vstride, r.w, r.wu, bcur, p1);
     tile_zero(jt, tw, nt);
     tile_zero(side, tw, nt);
+    double *target = dep_target(r, wk, Jd);
     rep_zero_part(Jc, ng, r.nrep, 3 * ng, slot, r.nblocks, nt);
     double m[1] = {0.0}, unused = 0.0;
     nodes.commit(r, threadIdx.x, es, e1, nullptr, m[0], unused, nullptr);
@@ -2420,7 +2442,7 @@ __device__ __forceinline__ void esec1_body(const Run &r0, RunPtr rp, const Work 
     const double sc[4] = {ke, (double)fb, gdev, (double)nonfinite};
     wave_partials<0xcu>(sc, red);
     lds_barrier();
-    dep.flush_tile(jt, dep_target(q, wk, Jd), 1, ng, tw);
+    dep.flush_tile(jt, target, 1, ng, tw);
     write_scalars(spw + (size_t)slot * kNS, red, nt);
 }
 
@@ -2580,6 +2602,7 @@ __device__ __forceinline__ void std_pass_body(const Run &r0, RunPtr rp, const Wo
     load_batch(cur, X, V, r.vstride, r.w, r.wu, bcur, p1);
     tile_zero(jt, tw, nt);
     tile_zero(side, tw, nt);
+    double *target = dep_target(r, wk, Jd);
     rep_zero_part(Jc, ng, r.nrep, 3 * ng, slot, r.nblocks, nt);
     if ((int)threadIdx.x < ng)
         es[threadIdx.x] = eh0;
@@ -2674,7 +2697,7 @@ __device__ __forceinline__ void std_pass_body(const Run &r0, RunPtr rp, const Wo
     if (lane == 0)
         red0[threadIdx.x >> 6] = ke0w;
     lds_barrier();
-    dep.flush_tile(jt, dep_target(q, wk, Jd), 1, ng, tw);
+    dep.flush_tile(jt, target, 1, ng, tw);
     write_scalars(spw + (size_t)slot * kNS, red, nt);
     if (record_wave(nt)) {
         const double k0 = 0.5 * wave_total(red0, 0, nt >> 6);
