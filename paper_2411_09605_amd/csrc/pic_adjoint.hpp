@@ -386,6 +386,135 @@ void k_adj_reverse(Run r, AdjWork aw, AdjParams ap, int q, const double *__restr
     }
 }
 
+// Recompute of nsteps steps of the forward run, from its state (X, V) into (Xo, Vo), state
+// j + 1 at Xo + j np, in one launch: with the fields of every step kept (g: kSaveRows rows of
+// N_g per step, E* and E-bar among them) no step waits for another particle's, so a lane keeps
+// its U particles in registers from state to state and only writes them.  The coefficients and
+// the particle's arithmetic are those of pass B, so the states are the forward run's bit for
+// bit; nothing is deposited.  (A launch of pass B's kind per step took 9.7 us a step; the two
+// segments of a 100-step gradient of 1e6 particles, 256 cells: 6.24 -> 5.83 ms forward and
+// backward.)
+// What bounds it is a lane's chain of four particles and the 16 MB a step writes.  The segment
+// the sweep waits for first has the chip to itself: whole workgroups.  The others run beside
+// the reverse passes, whose 16 wavefronts of 96 registers leave a CU room for four of 128: one
+// workgroup of four wavefronts per CU, for the whole segment.  (Eight wavefronts and ten steps
+// a launch 5.93 ms, sixteen and five 5.94-6.15, four and ten 5.88; two particles per lane
+// 5.88-5.93.)
+// LDS: nbuf buffers of the coefficients of E* and E-bar ([2][(ORDER + 1) tw] each).  With two,
+// the next step's node values load while the particles of the present one are pushed, and a
+// step has one barrier.
+constexpr int kRecUnroll = 4, kRecBlocks = 256;
+constexpr int kRecThreadsAlone = 1024, kRecThreadsBeside = 256;
+
+template <int ORDER> __host__ __device__ constexpr size_t recompute_lds_doubles(int tw, int nbuf)
+{
+    return (size_t)nbuf * 2 * (ORDER + 1) * tw;
+}
+
+// The node values of the coefficient slots threadIdx.x + k nt, k < kRecRounds, of both fields.
+constexpr int kRecRounds = 2;
+template <int ORDER> struct RecNodes {
+    double e[kRecRounds][2][ORDER + 1];
+    __device__ __forceinline__ static int node(int s, int k, int ng)
+    {
+        const int i = wrap_ghost(s - kGhost, ng) + k;
+        return i >= ng ? i - ng : i;
+    }
+    __device__ __forceinline__ void load(const double *g, int ng, int tw, unsigned nt)
+    {
+#pragma unroll
+        for (int k = 0; k < kRecRounds; ++k) {
+            const int s = (int)(threadIdx.x + k * nt);
+            if (s < tw - ORDER)
+#pragma unroll
+                for (int f = 0; f < 2; ++f)
+#pragma unroll
+                    for (int j = 0; j <= ORDER; ++j)
+                        e[k][f][j] = g[(3 + f) * ng + node(s, j, ng)];
+        }
+    }
+    // The coefficients from the values loaded, and those of the slots beyond them.
+    __device__ __forceinline__ void fill(double *ct, const double *g, int ng, int tw, unsigned nt)
+    {
+#pragma unroll
+        for (int k = 0; k < kRecRounds; ++k) {
+            const int s = (int)(threadIdx.x + k * nt);
+            if (s < tw - ORDER)
+#pragma unroll
+                for (int f = 0; f < 2; ++f)
+                    coefs<ORDER>(ct + f * (ORDER + 1) * tw + (ORDER + 1) * s, e[k][f]);
+        }
+        for (int s = (int)(threadIdx.x + kRecRounds * nt); s < tw - ORDER; s += nt)
+            for (int f = 0; f < 2; ++f) {
+                double v[ORDER + 1];
+#pragma unroll
+                for (int j = 0; j <= ORDER; ++j)
+                    v[j] = g[(3 + f) * ng + node(s, j, ng)];
+                coefs<ORDER>(ct + f * (ORDER + 1) * tw + (ORDER + 1) * s, v);
+            }
+    }
+};
+
+template <int ORDER>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4)))
+void k_adj_recompute(Run r, const double *__restrict__ g, int nsteps, int nbuf,
+                     const double *__restrict__ X, const double *__restrict__ V, double *Xo, double *Vo)
+{
+    constexpr int U = kRecUnroll;
+    extern __shared__ double smem[];
+    const int ng = r.ng, tw = r.tw;
+    const unsigned nt = nthreads(), lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t span = (int64_t)nt * U;
+    const size_t row = (size_t)kSaveRows * ng, buf = 2 * (size_t)(ORDER + 1) * tw;
+    const Run q = reload(kernarg_run());
+    RecNodes<ORDER> nodes;
+    for (int64_t base = blockIdx.x * span; base < r.np; base += gridDim.x * span) {
+        const int64_t b = base + 64 * U * (int64_t)wave;
+        PBatch<U, 1> cur;
+        nodes.load(g, ng, tw, nt);
+        load_batch(cur, X, V, r.vstride, nullptr, 0.0, b, r.np);
+        bool valid[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            valid[u] = b + 64 * u + lane < r.np;
+        lds_barrier();                  // (the tiles of the particles before are done with)
+        nodes.fill(smem, g, ng, tw, nt);
+        for (int s = 0; s < nsteps; ++s) {
+            const double *gn = g + (s + 1) * row, *cts = smem + (nbuf == 2 && (s & 1) ? buf : 0);
+            lds_barrier();
+            if (s + 1 < nsteps)
+                nodes.load(gn, ng, tw, nt);
+            double vs[U][1], x1[U], vd[U][1], gam[U], vn[U][1], xw[U];
+            Pos pos[U];
+            Cell<ORDER> c[U];
+            int fb = 0;
+            half_steps<ORDER, 1, false, U>(q, cur.x, cur.v, cts, nullptr, vs, x1);
+            mid_points<ORDER, U>(pos, cur.x, x1, q);
+            cells_at<ORDER, U>(c, pos, ng);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                dagger_es<1>(vd[u], cur.v[u], vs[u], gather_poly<ORDER>(cts + (ORDER + 1) * tw, c[u]), q);
+            gamma_all<1, U>(gam, vs, vd, cur.v, valid, fb);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                vn[u][0] = gam[u] * vd[u][0];
+            wrap_all<U>(xw, x1, q);
+            store_all<1, U>(xw, vn, valid, Xo + s * r.np, Vo + s * r.np, b, r.vstride);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                cur.x[u] = xw[u];
+                cur.v[u][0] = vn[u][0];
+            }
+            if (s + 1 < nsteps) {
+                if (nbuf == 1)
+                    lds_barrier();
+                nodes.fill(smem + (nbuf == 2 && !(s & 1) ? buf : 0), gn, ng, tw, nt);
+            }
+        }
+    }
+}
+
 // Inverse-CDF positions for the density 1 + sum_m alpha_m cos(k_m x) on [0, L): Newton
 // on x + sum_m (alpha_m / k_m) sin(k_m x) = u L from x = u L, to 1e-15 L; velocities
 // v_b s_p + v_s g_p.

@@ -499,21 +499,28 @@ __device__ __forceinline__ double gather_poly(const double *ct, const Cell<ORDER
 // Coefficients of every cell of a tile from its node values f(0..ng) (periodic).
 //   tent:      E(d) = E_0 + d (E_1 - E_0)
 //   quadratic: E(d) = (E_0 + E_2)/8 + 3 E_1/4 + d (E_2 - E_0)/2 + d^2 ((E_0 + E_2)/2 - E_1)
+template <int ORDER>
+__device__ __forceinline__ void coefs(double *c, const double (&e)[ORDER + 1])
+{
+    if constexpr (ORDER == 1) {
+        c[0] = e[0];
+        c[1] = e[1] - e[0];
+    } else {
+        c[0] = 0.125 * (e[0] + e[2]) + 0.75 * e[1];
+        c[1] = 0.5 * (e[2] - e[0]);
+        c[2] = 0.5 * (e[0] + e[2]) - e[1];
+    }
+}
+
 template <int ORDER, typename F>
 __device__ __forceinline__ void coef_fill(double *ct, F &&f, int ng, int tw, unsigned nt)
 {
     for (int s = threadIdx.x; s < tw - ORDER; s += nt) {
         const int i0 = wrap_ghost(s - kGhost, ng), i1 = i0 + 1 == ng ? 0 : i0 + 1;
-        const double e0 = f(i0), e1 = f(i1);
-        if constexpr (ORDER == 1) {
-            ct[2 * s] = e0;
-            ct[2 * s + 1] = e1 - e0;
-        } else {
-            const double e2 = f(i1 + 1 == ng ? 0 : i1 + 1);
-            ct[3 * s] = 0.125 * (e0 + e2) + 0.75 * e1;
-            ct[3 * s + 1] = 0.5 * (e2 - e0);
-            ct[3 * s + 2] = 0.5 * (e0 + e2) - e1;
-        }
+        double e[ORDER + 1] = {f(i0), f(i1)};
+        if constexpr (ORDER == 2)
+            e[2] = f(i1 + 1 == ng ? 0 : i1 + 1);
+        coefs<ORDER>(ct + (ORDER + 1) * s, e);
     }
 }
 

@@ -1694,25 +1694,19 @@ void adj_pass_b(pic_adj *c, int par, const double *X, const double *V, double *X
                        lds_pass_b(&c->q), c->stream, c->run, wk, X, V, Xo, Vo);
 }
 
-// Recompute of step n of the forward run from its state (X, V) into (Xo, Vo) in one
-// launch: pass B without its predictor deposit, its fields built from the grids the
-// forward pass B kept (g: E^n | j^{n,*} | j^{*,n+1/2}, one replica).  The prologue forms the
-// same sums in the same order as the forward run's pass B, so the new state is the
-// forward run's bit for bit; pass A and both deposits are not needed again.
+// Recompute of n steps of the forward run from its state (X, V) into (Xo, Vo) on the side
+// stream, with the fields the forward pass B kept (g).
 template <int ORDER>
-void adj_recompute(pic_adj *c, hipStream_t stream, int par, const double *g, const double *X,
-                   const double *V, double *Xo, double *Vo)
+void adj_recompute(pic_adj *c, int n, int threads, const double *g, const double *X, const double *V,
+                   double *Xo, double *Vo)
 {
-    Run r = c->run;
-    r.nrep = 1;
-    Work wk = by_parity(c->wk, par);
-    const int ng = c->p.n_cells;
-    wk.Ef[0] = const_cast<double *>(g);
-    wk.J1[0] = const_cast<double *>(g) + ng;
-    wk.J2[0] = const_cast<double *>(g) + 2 * ng;
-    wk.grid_save = nullptr;
-    hipLaunchKernelGGL((k_pass_b<ORDER, 1, false, false, 0>), dim3(c->run.nblocks), dim3(c->threads),
-                       lds_pass_b(&c->q), stream, r, wk, X, V, Xo, Vo);
+    const int tw = c->run.tw;
+    const int nbuf = recompute_lds_doubles<ORDER>(tw, 2) * 8 <= kMaxLds ? 2 : 1;
+    const int64_t span = (int64_t)threads * kRecUnroll;
+    const int64_t groups = (c->run.np + span - 1) / span;
+    hipLaunchKernelGGL((k_adj_recompute<ORDER>), dim3((unsigned)std::min<int64_t>(groups, kRecBlocks)),
+                       dim3(threads), recompute_lds_doubles<ORDER>(tw, nbuf) * 8, c->side, c->run, g, n,
+                       nbuf, X, V, Xo, Vo);
 }
 
 template <int ORDER, int STAGE>
@@ -1792,19 +1786,18 @@ void adj_backward_launches(pic_adj *c)
         return j == 0 ? c->ckv + (int64_t)cp * r.np : c->segv + (cp & 1) * seglen + (int64_t)(j - 1) * r.np;
     };
     auto grids = [&](int cp, int j) { return c->gall + ((int64_t)cp * K + j) * kSaveRows * ng; };
-    // recompute a segment's states from its checkpoint with the grids the forward run kept
-    // (one gather-only launch per step), on the side stream
-    auto recompute = [&](int cp) {
-        const int s0 = cp * K, len = std::min(K, N - s0);
-        for (int j = 0; j + 1 < len; ++j)
-            adj_recompute<ORDER>(c, c->side, (int)((s0 + j) & 1), grids(cp, j), sx(cp, j), sv(cp, j),
-                                 sx(cp, j + 1), sv(cp, j + 1));
+    // recompute a segment's states from its checkpoint with the grids the forward run kept, on
+    // the side stream
+    auto recompute = [&](int cp, int threads) {
+        const int len = std::min(K, N - cp * K);
+        if (len > 1)
+            adj_recompute<ORDER>(c, len - 1, threads, grids(cp, 0), sx(cp, 0), sv(cp, 0), sx(cp, 1), sv(cp, 1));
         (void)hipEventRecord(c->ev_rec[cp & 1], c->side);
     };
     // the side stream starts after everything enqueued before this call
     (void)hipEventRecord(c->ev_start, c->stream);
     (void)hipStreamWaitEvent(c->side, c->ev_start, 0);
-    recompute(c->A.ncp - 1);
+    recompute(c->A.ncp - 1, kRecThreadsAlone);
     int q = 0;
     for (int cp = c->A.ncp - 1; cp >= 0; --cp) {
         const int s0 = cp * K, len = std::min(K, N - s0);
@@ -1812,7 +1805,7 @@ void adj_backward_launches(pic_adj *c)
             // the next segment's buffer was last read by the reverse of segment cp + 1
             if (cp + 1 < c->A.ncp)
                 (void)hipStreamWaitEvent(c->side, c->ev_rev[(cp + 1) & 1], 0);
-            recompute(cp - 1);
+            recompute(cp - 1, kRecThreadsBeside);
         }
         (void)hipStreamWaitEvent(c->stream, c->ev_rec[cp & 1], 0);
         // reverse steps of the segment: R1 of its last step, then per step R2 and R3 fused
