@@ -32,13 +32,6 @@ constexpr int kDefaultThreads = 1024;
 // contiguous chunks are faster.
 constexpr double kInterleaveBytes = 192.0 * 1024 * 1024;
 constexpr int kDefaultRecords = 4096;
-// The adjoint form defaults to two 512-thread workgroups per CU once every thread gets two
-// particles or more: its passes are short, and one workgroup's prologue and flush then
-// overlap the other's particles (two-stream gradient, 1e6 particles, 256 cells: forward +
-// backward 45.3 ms against 46.6 ms at 1024 x 256). The plain step is faster with one
-// 1024-thread workgroup per CU at every size measured (1e6 to 4e7 particles).
-constexpr int kAdjThreads = 512;
-constexpr int kAdjGroupsPerCU = 2;
 constexpr size_t kAlign = 256;
 // LDS a workgroup may use on gfx950 (160 KB per CU, all of it available to one workgroup),
 // less what the kernels declare statically (reduction scratch, counters: under 1 KB); this
