@@ -3118,86 +3118,104 @@ __global__ __launch_bounds__(256) void k_reduce_partials(const double *__restric
 
 // Initial Gauss solve: dE/dx = rho - 1 with rho in J2[0], into the caller's E_x.
 // Spectrally on the nodes: E_m = rho_m / (i k_m), k_m = 2 pi m / L for 0 < |m| < N/2, mean
-// and Nyquist modes zero (the Poisson form, eq. (poisson), in 1D).
-// LDS: rho | Re E_m | Im E_m | the cosines and sines of 2 pi j / N_g, computed once (the sums
-// index them with m l mod N_g), and on grids of at most half a thread per node's worth of
-// threads the partial sums: S threads share a mode (then a node), each summing a consecutive
-// S-th of the terms, and the S parts are added in order.  One workgroup, so the solve is two
-// chains of N_g / S terms: 256 cells 25 -> 9 us, 64 cells 7 -> 4 us.
+// and Nyquist modes zero (the Poisson form, eq. (poisson), in 1D), as the convolution of rho
+// with the row G_d = (2 / N_g) sum_m sin(2 pi m d / N_g) / k_m (0 < m < N_g / 2), which is odd
+// in d.  The constant part of rho convolves to zero: rho_0 is taken off first, so it doesn't
+// round into the sum.
+// One workgroup, so the LDS bounds it: the row takes N_g^2 / 4 reads of the table of sines (m d
+// mod N_g: bank conflicts) and the convolution N_g^2 of consecutive addresses, where the two
+// transforms of the spectral form took 4 N_g^2 of the first kind (with the launch's other work,
+// 512 cells 71.7 -> 26.7 us, 256 cells 24.1 -> 13.6, 64 cells 7.9 -> 6.7).  On grids of at
+// most 512 cells S threads share an element of either sum, each taking a consecutive S-th of
+// its terms, and the S parts are added in order.
+// LDS: rho | sines of 2 pi j / N_g | 1 / k_m [N_g / 2] | G twice over [2 N_g] | partial sums
+//      (for the largest of several grids: room for any of them)
 __host__ __device__ constexpr size_t gauss_lds_doubles(int ng)
 {
-    return ng <= 512 ? 5 * (size_t)ng + 2048 : (ng <= 921 ? 4608 : 5 * (size_t)ng);
+    return ng <= 512 ? 5 * (size_t)ng + 1024 : (ng <= 716 ? 3584 : 5 * (size_t)ng);
 }
 
 __device__ void gauss_body(const Run &r, const Work &wk, double *smem)
 {
-    const int ng = r.ng, nt = (int)nthreads();
-    double *rho = smem, *er = smem + ng, *ei = smem + 2 * ng;
-    double *tc = smem + 3 * ng, *ts = smem + 4 * ng;
-    const int S = ng <= 512 ? max(1, min(16, nt / ng)) : 1, len = (ng + S - 1) / S;
-    double *pa = S > 1 ? smem + 5 * ng : er, *pb = S > 1 ? pa + S * ng : ei;
+    const int ng = r.ng, nt = (int)nthreads(), M = (ng - 1) / 2;
+    double *rho = smem, *ts = smem + ng, *ik = smem + 2 * ng, *G = ik + ng / 2 + 1, *part = smem + 5 * ng;
+    auto split = [&](int n) { return ng <= 512 ? max(1, min(16, nt / n)) : 1; };
     rep_gather(rho, wk.J2[0], ng, r.nrep, 3 * ng);
     for (int j = threadIdx.x; j < ng; j += nt)
-        sincospi(2.0 * (double)j / ng, &ts[j], &tc[j]);
+        ts[j] = sinpi(2.0 * (double)j / ng);
+    for (int m = threadIdx.x; m <= M; m += nt)
+        ik[m] = r.L / (M_PI * m * ng);         // (2 / N_g) / k_m
     __syncthreads();
     if (r.filter_rho) {
-        // the standard scheme's filtered density (as in k_std_field), through ei
+        // the standard scheme's filtered density (as in k_std_field), through G
         for (int i = threadIdx.x; i < ng; i += nt)
-            ei[i] = 0.25 * rho[i == 0 ? ng - 1 : i - 1] + 0.5 * rho[i] + 0.25 * rho[i + 1 == ng ? 0 : i + 1];
+            G[i] = 0.25 * rho[i == 0 ? ng - 1 : i - 1] + 0.5 * rho[i] + 0.25 * rho[i + 1 == ng ? 0 : i + 1];
         __syncthreads();
         for (int i = threadIdx.x; i < ng; i += nt)
-            rho[i] = ei[i];
+            rho[i] = G[i];
         __syncthreads();
     }
-    for (int it = threadIdx.x; it < S * ng; it += nt) {
-        const int sg = it / ng, m = it - sg * ng, l0 = min(ng, sg * len), l1 = min(ng, l0 + len);
-        double re = 0.0, im = 0.0;
-        int ml = (int)(((long long)m * l0) % ng);      // m l mod N_g
-        for (int l = l0; l < l1; ++l) {
-            re += rho[l] * tc[ml];
-            im -= rho[l] * ts[ml];
-            ml += m;
-            ml -= ml >= ng ? ng : 0;
-        }
-        pa[it] = re;
-        pb[it] = im;
-    }
-    __syncthreads();
-    for (int m = threadIdx.x; m < ng; m += nt) {
-        double re = pa[m], im = pb[m];
-        for (int sg = 1; sg < S; ++sg) {
-            re += pa[sg * ng + m];
-            im += pb[sg * ng + m];
-        }
-        const int ms = m <= ng / 2 ? m : m - ng;
-        const double k = 2.0 * M_PI * ms / r.L;
-        const bool zero = m == 0 || 2 * m == ng;
-        er[m] = zero ? 0.0 : im / k;          // (re + i im) / (i k) = im / k - i re / k
-        ei[m] = zero ? 0.0 : -re / k;
-    }
-    __syncthreads();
-    for (int it = threadIdx.x; it < S * ng; it += nt) {
-        const int sg = it / ng, i = it - sg * ng, m0 = max(1, sg * len), m1 = min(ng, (sg + 1) * len);
+    // G_d, 0 < d < N_g / 2
+    const int S1 = split(M), len1 = (M + S1 - 1) / S1;
+    for (int it = threadIdx.x; it < S1 * M; it += nt) {
+        const int sg = it / M, d = it - sg * M + 1, m0 = sg * len1 + 1, m1 = min(M, m0 + len1 - 1);
         double acc = 0.0;
-        int mi = (int)(((long long)m0 * i) % ng);      // m i mod N_g
-        for (int m = m0; m < m1; ++m) {
-            acc += er[m] * tc[mi] - ei[m] * ts[mi];
-            mi += i;
-            mi -= mi >= ng ? ng : 0;
+        int md = (int)(((long long)m0 * d) % ng);      // m d mod N_g
+#pragma unroll 4
+        for (int m = m0; m <= m1; ++m) {
+            acc = fma(ts[md], ik[m], acc);
+            md += d;
+            md -= md >= ng ? ng : 0;
         }
-        if (S == 1)
-            wk.E[i] = acc / ng;
+        if (S1 == 1)
+            G[d] = acc;
         else
-            pa[it] = acc;
+            part[it] = acc;
     }
-    if (S == 1)
+    __syncthreads();
+    // both periods of the row: G[N_g + d] and G[d] hold G_d, 0 <= d < N_g
+    const double r0 = rho[0];
+    __syncthreads();
+    for (int i = threadIdx.x; i < ng; i += nt) {
+        rho[i] -= r0;
+        const int d = 2 * i < ng ? i : ng - i;
+        double g = 0.0;
+        if (i != 0 && 2 * i != ng) {
+            if (S1 == 1)
+                g = G[d];
+            else
+                for (int sg = 0; sg < S1; ++sg)
+                    g += part[sg * M + d - 1];
+            g = i == d ? g : -g;
+        }
+        G[ng + i] = g;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < ng; i += nt)
+        G[i] = G[ng + i];
+    __syncthreads();
+    // E_i = sum_j G_{i - j} rho_j
+    const int S2 = split(ng), len2 = (ng + S2 - 1) / S2;
+    for (int it = threadIdx.x; it < S2 * ng; it += nt) {
+        const int sg = it / ng, i = it - sg * ng, j0 = sg * len2, j1 = min(ng, j0 + len2);
+        const double *g = G + ng + i;
+        double acc = 0.0;
+#pragma unroll 8
+        for (int j = j0; j < j1; ++j)
+            acc = fma(g[-j], rho[j], acc);
+        if (S2 == 1)
+            wk.E[i] = acc;
+        else
+            part[it] = acc;
+    }
+    if (S2 == 1)
         return;
     __syncthreads();
     for (int i = threadIdx.x; i < ng; i += nt) {
-        double acc = pa[i];
-        for (int sg = 1; sg < S; ++sg)
-            acc += pa[sg * ng + i];
-        wk.E[i] = acc / ng;
+        double acc = part[i];
+        for (int sg = 1; sg < S2; ++sg)
+            acc += part[sg * ng + i];
+        wk.E[i] = acc;
     }
 }
 
