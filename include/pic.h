@@ -417,7 +417,7 @@ int pic_batch_destroy(pic_batch *ctx);
  * storing the particle state (x, v) every checkpoint_every steps and every step's grids
  * and fields (E^n, the two currents, E*, E-bar and E^{n+1}: 6 N_g values);
  * pic_adj_backward recomputes each segment's states from its checkpoint and those grids
- * (one gather-only launch per step) and runs the reverse of the steps, of the Gauss solve
+ * (one gather-only launch per segment) and runs the reverse of the steps, of the Gauss solve
  * and of the sampling.  The fallback Gamma := 1 (section 3.2) is a constant in the
  * derivative.
  * Streams: the context enqueues on the caller's stream.  The backward sweep recomputes the

@@ -17,8 +17,8 @@
 //       deposit dt/2 * vstar_bar at x* into G2 (the adjoint of E*).
 //   R3: every workgroup forms jbar1 = -dt/2 (G2 - mean G2); per particle, the adjoints
 //       of x* and of the predictor deposit; write the adjoint of (x^n, v^n).  The lead
-//       workgroup stores the adjoint of E^n = lambda' + G1 / 2 + G2 for step n - 1 and
-//       clears the other parity's G1, G2.
+//       workgroup stores the adjoint of E^n = lambda' + G1 / 2 + G2 for step n - 1; every
+//       workgroup clears its share of the other parity's G2 (of G1 in R2).
 //
 // Gathers and deposits are the forward's (same stencils); their derivatives with
 // respect to the particle position use the derivative of the B-spline weights.
@@ -74,8 +74,8 @@ template <int ORDER> __device__ __forceinline__ Stencil<ORDER> dstencil_at(const
 // fallback counts of the two; they agree).
 // The derivative needs 1 / den and 1 / (2 Gamma) too, so the reciprocal and the reciprocal
 // root are refined themselves (two Newton steps; Goldschmidt's iteration) and the quotient and
-// the root are corrected with them: 20 operations where three divisions and a square root
-// take 50 of a reverse step's 330.
+// the root are corrected with them, in place of three divisions and a square root (with the
+// loop's other changes STAGE 4 21.9 -> 18.8 us, see k_adj_reverse).
 __device__ __forceinline__ double adj_gamma(double num2, double den, double &rho, double &rden,
                                             double &half_inv, bool &ok)
 {
@@ -248,7 +248,11 @@ template <int STAGE> struct AdjBatch {
 // round trips before and inside the loop.  The prologue is one round of loads (the fields the
 // forward pass B built for step n, and n - 1, and the grid adjoints), one barrier for the
 // tiles, their ghosts and the means; the next batch loads while the current one is processed
-// (STAGE 4 22.7 -> 18.6 us, STAGE 2 13.7 -> 10.6 us at 1e6 particles, 256 cells).
+// (beside the recompute, 1e6 particles x 256 cells: STAGE 4 21.9 -> 18.8 us, STAGE 2 13.3 ->
+// 12.2; the shortest 21.2 -> 17.0 and 12.7 -> 10.9).  STAGE 4's floor is the 64 B per particle
+// it moves, 10 us; its 400 vector instructions per particle and wavefront take as long.  Doing
+// its two forward steps together, stage by stage, costs registers that the recompute beside it
+// needs (6.20 -> 6.23 ms for the sweep).
 template <int ORDER, int STAGE>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4)))
 void k_adj_reverse(Run r, AdjWork aw, AdjParams ap, int q, const double *__restrict__ X,

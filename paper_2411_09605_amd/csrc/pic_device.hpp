@@ -1164,7 +1164,7 @@ __device__ __forceinline__ void block_reduce(double (&v)[N], double *red)
 // nw) combines the nw wavefronts' values, in every lane of any wavefront that asks (all
 // lanes active).  The lanes read the values side by side and combine them within rows of 16
 // (DPP), a fixed order; reading them one after the other, as block_reduce does, is a chain of
-// nw LDS round trips (0.7 us for 16 wavefronts).
+// nw LDS round trips.
 template <unsigned MAXMASK, int N>
 __device__ __forceinline__ void wave_partials(const double (&v)[N], double *red)
 {
@@ -2519,7 +2519,7 @@ __device__ __forceinline__ double wave_convolve(const double *const (&K)[N], con
 // 1/2, 1/4)) into E.  A workgroup of kFieldNodes wavefronts computes as many consecutive
 // nodes, one per wavefront.  The launch is a round of loads, a barrier and a few iterations:
 // with 64 lanes to a node the convolution is N_g / 64 iterations long (eight lanes to a node,
-// 32 iterations at 256 cells: 4.8 us; now 3.6).
+// 32 iterations at 256 cells: 4.7 us, the shortest 3.9; now 4.4 and 2.4).
 // LDS: rho[ng] | g[ng] | filtered rho[ng].
 constexpr int kFieldNodes = 8;
 
@@ -3405,7 +3405,8 @@ __global__ __launch_bounds__(256) void k_em_rows(Run r, Work wk)
 // output o (predictor: q = 2 p + o, o = E, B; full: q = 3 p + o, o = E, B, <E>); each node is
 // one wave_convolve, so the update is reproducible.  E_x has no curl term: E_x - tau j_x
 // (average E_x - tau/2 j_x), written by q = 0.  (As k_std_field: the launch is round trips, and
-// 64 lanes to a node instead of eight make it 6.5 -> 4.6 us at 256 cells.)
+// 64 lanes to a node instead of eight make it 6.3 -> 4.8 us at 251 cells, the shortest 5.9 ->
+// 3.8.)
 // LDS: e | B (signed) | j | the three rows [6][N].
 __global__ __launch_bounds__(64 * kFieldNodes) void k_em_fields(Run r, Work wk, int full)
 {
