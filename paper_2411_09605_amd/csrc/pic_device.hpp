@@ -3567,8 +3567,8 @@ template <typename T> __device__ __forceinline__ T uniform_load(const T *g)
     return __builtin_bit_cast(T, *(const_ptr)g);
 }
 
-// Workgroups of the batched passes hold at most 512 threads, so the persistent kernels,
-// which keep a run's scalars live across work items, have up to 256 VGPRs (no spills).
+// Workgroups of the batched passes hold at most 512 threads: items are small, and two
+// workgroups share a CU.
 constexpr int kBatchMaxThreads = 512;
 // Particles per thread per batch in the batched passes: two, as in the plain passes, keep two
 // workgroups per CU within 128 VGPRs without spills (96 Landau runs of 1e4 to 1e6 particles:

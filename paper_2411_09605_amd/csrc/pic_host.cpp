@@ -154,7 +154,7 @@ size_t lds_need(const pic_params *p)
                : is_std(p) ? std::max(lds_std_pass_of(p->shape_order, (size_t)p->n_cells),
                                       lds_std_field_of((size_t)p->n_cells))
                            : std::max(lds_pass_a(p), lds_pass_b(p));
-    // the Gauss solve with its twiddle table (and partial sums on small grids: 37 KB at most)
+    // the Gauss solve (with its partial sums, up to 716 cells, 28 KB at most)
     m = std::max(m, (size_t)5 * p->n_cells * 8);
     if (has_em_fields(p))
         m = std::max(m, lds_psatd_of((size_t)p->n_cells));
