@@ -54,12 +54,12 @@ template <int ORDER> __device__ __forceinline__ Stencil<ORDER> dstencil_at(const
 {
     Stencil<ORDER> s;
     if constexpr (ORDER == 2) {
-        s.first = p.i - 1;
+        s.first = (int)(p.n - 1);
         s.w[0] = p.d - 0.5;
         s.w[1] = -2.0 * p.d;
         s.w[2] = 0.5 + p.d;
     } else {
-        s.first = p.i;
+        s.first = (int)p.n;
         s.w[0] = -1.0;
         s.w[1] = 1.0;
     }
@@ -119,6 +119,21 @@ struct AdjOut {
     double ebar_b, ehat_b, xb, vb;
 };
 
+// A particle's place, its stencil and the stencil's slots.
+template <int ORDER>
+__device__ __forceinline__ Pos adj_place(Stencil<ORDER> &st, Slots<ORDER> &sl, double s, double scale, int ng)
+{
+    Pos p = locate<ORDER>(s, scale, 0.0);
+    int b = (int)first_slot<ORDER>(p);
+    if (first_slot<ORDER>(p) > (unsigned)(ng + 2 * kGhost - ORDER - 1))
+        b = far_slot<ORDER>(p, ng);
+    st = stencil_at<ORDER>(p);
+#pragma unroll
+    for (int k = 0; k <= ORDER; ++k)
+        sl.n[k] = b + k;
+    return p;
+}
+
 // es, eb: predictor and averaged fields; lt, g2: the adjoint of E^{n+1} and the deposits of
 // R2, with their means (ghost-padded LDS tiles).  The current adjoints are affine in them,
 // jbar2 = -dt (lt - mean) and jbar1 = -dt/2 (G2 - mean), and a spline's weights sum to one
@@ -136,14 +151,10 @@ __device__ __forceinline__ AdjOut<ORDER, STAGE> adj_particle(const Run &r, doubl
     // forward recompute: the quantities of pass A / pass B, equal to theirs up to rounding
     // (the gathers here take the stencil weights, the passes the cell polynomials of
     // gather_poly; the derivative needs the weights anyway)
-    const Pos ps = locate<ORDER>(fma(r.hdt, v, x), r.inv_h, 0.0);        // x*
-    o.ss = stencil_at<ORDER>(ps);
-    o.ns = slots_of<ORDER>(o.ss, r.ng);
+    const Pos ps = adj_place<ORDER>(o.ss, o.ns, fma(r.hdt, v, x), r.inv_h, r.ng);      // x*
     const double vs = fma(r.hdt, gather1<ORDER>(es, o.ss, o.ns), v);
     const double x1 = fma(r.dt, vs, x);
-    const Pos ph = locate<ORDER>(x + x1, r.hinv_h, 0.0);                 // x^{n+1/2}
-    o.sh = stencil_at<ORDER>(ph);
-    o.nh = slots_of<ORDER>(o.sh, r.ng);
+    const Pos ph = adj_place<ORDER>(o.sh, o.nh, x + x1, r.hinv_h, r.ng);               // x^{n+1/2}
     const double vd = fma(r.dt, gather1<ORDER>(eb, o.sh, o.nh), v);
     // num2 = 2 num = a2 b with a2 = 2 v* - (vd + v), b = vd - v
     const double a2 = fma(2.0, vs, -(vd + v)), b = vd - v;

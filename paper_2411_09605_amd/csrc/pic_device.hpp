@@ -366,34 +366,18 @@ template <int ORDER> struct Cell {
 // else to issue) and the rare cases (a stencil beyond the ghost band, a wrap, a large
 // correction) cost one test per stage: a branch the whole wavefront takes or not.
 
-// Slots of the first nodes of stencils that start at node first[u] (see Slots).
-template <int ORDER, int U>
-__device__ __forceinline__ void slot_bases(int (&b)[U], const int (&first)[U], int ng)
-{
-    const unsigned lim = (unsigned)(ng + 2 * kGhost - ORDER - 1);
-    bool out = false;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        b[u] = (int)((unsigned)first[u] + kGhost);
-        out |= (unsigned)b[u] > lim;
-    }
-    if (__any(out)) {
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if ((unsigned)b[u] > lim)
-                b[u] = wrap_node(first[u], ng) + kGhost;
-    }
-}
-
 // Where a particle sits on the grid: its node (the nearest one for the quadratic shape, the
 // lower one for the tent) and the offset from it, both of the coordinate s scale - shift.
 // Adding 1.5 2^52 rounds to the nearest integer and leaves it in the sum's low bits, so
 // neither the coordinate itself nor a conversion is needed.  (A tie may round to either node;
-// the spline's two pieces agree there.  The low bits of a coordinate beyond 2^31, or of one that
-// is not finite, are some integer, which slot_bases puts inside the tile.)
+// the spline's two pieces agree there.)  The sum less the constant, as 64-bit numbers, is the
+// node of a coordinate up to 2^51.  Beyond, and for one that is not finite, it is some large
+// number, and the quadratic shape's offset is no longer the distance from a whole number:
+// slot_bases puts such a particle inside the tile and its offset into [-1/2, 1/2].  The tent's
+// offset always lies in [0, 1), so the low 32 bits do there: beyond 2^31 they are some node.
 constexpr double kRoundMagic = 6755399441055744.0;   // 1.5 * 2^52
 struct Pos {
-    int i;
+    long long n;
     double d;
 };
 
@@ -402,11 +386,11 @@ template <int ORDER> __device__ __forceinline__ Pos locate(double s, double scal
     Pos p;
     if constexpr (ORDER == 2) {
         const double t = fma(s, scale, kRoundMagic);   // (shift is 0: half-node grids use tents)
-        p.i = __double2loint(t);
+        p.n = __double_as_longlong(t) - __double_as_longlong(kRoundMagic);
         p.d = fma(s, scale, -(t - kRoundMagic));
     } else {
         const double xi = fma(s, scale, -shift), f = floor(xi);
-        p.i = __double2loint(f + kRoundMagic);
+        p.n = __double2loint(f + kRoundMagic);
         p.d = xi - f;
     }
     return p;
@@ -419,11 +403,11 @@ template <int ORDER> __device__ __forceinline__ Pos half_node(const Pos &p)
     if constexpr (ORDER == 2) {
         // nearest half node: i or i - 1 by the sign of the offset
         o.d = p.d - __builtin_copysign(0.5, p.d);
-        o.i = p.i + (__double2hiint(p.d) >> 31);
+        o.n = p.n + (__double2hiint(p.d) >> 31);
     } else {
         const bool low = p.d < 0.5;
         o.d = low ? p.d + 0.5 : p.d - 0.5;
-        o.i = low ? p.i - 1 : p.i;
+        o.n = low ? p.n - 1 : p.n;
     }
     return o;
 }
@@ -434,45 +418,83 @@ template <int ORDER> __device__ __forceinline__ Stencil<ORDER> stencil_at(const 
     Stencil<ORDER> s;
     if constexpr (ORDER == 2) {
         const double hd = 0.5 * p.d, t = fma(hd, p.d, 0.125);
-        s.first = p.i - 1;
+        s.first = (int)(p.n - 1);
         s.w[0] = t - hd;
         s.w[1] = fma(-p.d, p.d, 0.75);
         s.w[2] = t + hd;
     } else {
-        s.first = p.i;
+        s.first = (int)p.n;
         s.w[0] = 1.0 - p.d;
         s.w[1] = p.d;
     }
     return s;
 }
 
-template <int ORDER, int U>
-__device__ __forceinline__ void cells_at(Cell<ORDER> (&c)[U], const Pos (&p)[U], int ng)
+// A quadratic shape's offset out of [-1/2, 1/2] (see Pos) taken as the distance from the
+// nearest whole number: its weights, which grow with it, stay those of some particle.
+template <int ORDER> __device__ __forceinline__ void near_offset(Pos &p)
 {
-    int first[U], b[U];
+    if (ORDER == 2 && !(fabs(p.d) <= 0.5))
+        p.d -= rint(p.d);
+}
+
+// The slot of the first node of a particle's stencil if the tile holds it there (see Slots),
+// any larger number if not.  (Of the quadratic shape's 64 bits the comparison with the largest
+// slot is the test for a far offset as well; as a test of its own that was 1-3 % of a step.)
+template <int ORDER> __device__ __forceinline__ auto first_slot(const Pos &p)
+{
+    if constexpr (ORDER == 2)
+        return (unsigned long long)p.n + (kGhost - 1);
+    else
+        return (unsigned)p.n + kGhost;
+}
+
+// A particle that is not in the tile there: its slot, its offset near.
+template <int ORDER> __device__ __forceinline__ int far_slot(Pos &p, int ng)
+{
+    near_offset<ORDER>(p);
+    return wrap_node((int)(p.n - (ORDER == 2 ? 1 : 0)), ng) + kGhost;
+}
+
+// Slots of the first nodes of the particles' stencils.
+template <int ORDER, int U>
+__device__ __forceinline__ void slot_bases(int (&b)[U], Pos (&p)[U], int ng)
+{
+    const unsigned lim = (unsigned)(ng + 2 * kGhost - ORDER - 1);
+    bool out = false;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        c[u].d = p[u].d;
-        first[u] = p[u].i - (ORDER == 2 ? 1 : 0);
+        b[u] = (int)first_slot<ORDER>(p[u]);
+        out |= first_slot<ORDER>(p[u]) > lim;
     }
-    slot_bases<ORDER, U>(b, first, ng);
+    if (__any(out)) {
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u)
+            if (first_slot<ORDER>(p[u]) > lim)
+                b[u] = far_slot<ORDER>(p[u], ng);
+    }
+}
+
+template <int ORDER, int U>
+__device__ __forceinline__ void cells_at(Cell<ORDER> (&c)[U], Pos (&p)[U], int ng)
+{
+    int b[U];
+    slot_bases<ORDER, U>(b, p, ng);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
         c[u].base = b[u];
+        c[u].d = p[u].d;
+    }
 }
 
 // Stencils of the particles and the slots of their first nodes.
 template <int ORDER, int U>
-__device__ __forceinline__ void stencils_at(Stencil<ORDER> (&st)[U], int (&b)[U], const Pos (&p)[U],
-                                            int ng)
+__device__ __forceinline__ void stencils_at(Stencil<ORDER> (&st)[U], int (&b)[U], Pos (&p)[U], int ng)
 {
-    int first[U];
+    slot_bases<ORDER, U>(b, p, ng);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < U; ++u)
         st[u] = stencil_at<ORDER>(p[u]);
-        first[u] = st[u].first;
-    }
-    slot_bases<ORDER, U>(b, first, ng);
 }
 
 template <int ORDER>
@@ -648,7 +670,7 @@ template <int ORDER, int NC> struct Depo<ORDER, NC, 0> {
     // The contributions of a lane's U particles: straight to the tile unless one of the
     // wavefront's is out of range.
     template <int U>
-    __device__ __forceinline__ void add_all(double *jt, int tw, int ng, const Pos (&p)[U],
+    __device__ __forceinline__ void add_all(double *jt, int tw, int ng, Pos (&p)[U],
                                             const double (&q)[U][NC], const bool (&valid)[U])
     {
         Stencil<ORDER> st[U];
@@ -937,16 +959,18 @@ template <int ORDER, int NC> struct Depo<ORDER, NC, 2> {
 // A lane's U particles into any kind of accumulator (Depo<., ., 2> wants every lane).
 template <int ORDER, int NC, int DEP, int U>
 __device__ __forceinline__ void deposit_all(Depo<ORDER, NC, DEP> &dep, double *jt, int tw, int ng,
-                                            const Pos (&p)[U], const double (&q)[U][NC],
+                                            Pos (&p)[U], const double (&q)[U][NC],
                                             const bool (&valid)[U])
 {
     if constexpr (DEP == 0) {
         dep.template add_all<U>(jt, tw, ng, p, q, valid);
     } else {
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u) {
+            near_offset<ORDER>(p[u]);
             if (DEP == 2 || valid[u])
                 dep.add(jt, tw, ng, stencil_at<ORDER>(p[u]), q[u], valid[u], u == 0);
+        }
     }
 }
 
