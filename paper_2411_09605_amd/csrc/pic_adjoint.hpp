@@ -363,7 +363,7 @@ void k_adj_reverse(Run r, AdjWork aw, AdjParams ap, int q, const double *__restr
     }
 
     Depo<ORDER, 1, 3> dep;          // adjoint values: FP64 atomics (no fixed-point scale)
-    while (bcur < p1) {
+    while (batch_begins(bcur, p1)) {
         const int64_t bnxt = wb.claim(), p = bcur + (threadIdx.x & 63);
         const bool valid = p < p1;
         double w = r.wu;

@@ -132,7 +132,7 @@ struct BatchAddr {
     unsigned lim;      // largest offset inside [b0, p1)
     __device__ __forceinline__ BatchAddr(int64_t start, int64_t p1, unsigned span)
     {
-        b0 = min(start, p1 - 1);
+        b0 = batch_begins(start, p1) ? start : p1 - 1;
         lim = (unsigned)min(p1 - 1 - b0, (int64_t)(span - 1));
     }
     __device__ __forceinline__ unsigned off(unsigned lane, int u) const
@@ -188,11 +188,8 @@ __device__ __forceinline__ void load_batch(PBatch<U, NV> &b, const double *__res
 // Static (the deterministic mode): wavefront w takes batches w, w + W, w + 2W, ... of
 // its workgroup's W wavefronts, so every thread always sees the same particles in the
 // same order and its running sums (kinetic energy) are reproducible bit for bit.
-// Starts are kept in units of 64 particles (chunks are whole wavefronts), in 32 bits: 2^37
-// particles, far more than the memory holds.
 template <int U> struct WaveBatches {
-    int origin, step;
-    int nu, last;          // reversed order: batch start s maps to last - s while s < nu
+    BatchOrder o;
     int *ctr;
     int fixed;             // 1: static assignment
     int k;                 // static: index of the wavefront's current batch
@@ -203,18 +200,10 @@ template <int U> struct WaveBatches {
     __device__ __forceinline__ WaveBatches(int64_t p0, int *counter, unsigned nt, int interleave = 0,
                                            int nblocks = 1, int static_order = 0,
                                            int64_t n_particles = 0, bool reverse = false)
-        : ctr(counter), fixed(static_order), nw((int)(nt >> 6))
+        : o(batch_order(p0, 64 * U, interleave != 0, (int)blockIdx.x, nblocks, n_particles, reverse)),
+          ctr(counter), fixed(static_order), nw((int)(nt >> 6))
     {
-        origin = interleave ? (int)blockIdx.x * U : (int)(p0 >> 6);
-        step = interleave ? nblocks * U : U;
         k = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        // units of the run rounded up to whole batches
-        nu = (interleave && reverse) ? (int)((n_particles + 64 * U - 1) / (64 * U)) * U : 0;
-        last = nu - U;
-    }
-    __device__ __forceinline__ int64_t order(int s) const
-    {
-        return (int64_t)(s < nu ? last - s : s) << 6;
     }
     __device__ __forceinline__ void reset() const
     {
@@ -224,14 +213,14 @@ template <int U> struct WaveBatches {
     // first particle of this wavefront's first batch (the same in every lane)
     __device__ __forceinline__ int64_t first() const
     {
-        return order(origin + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * step);
+        return o.origin + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * o.step;
     }
     // claim the next batch (every lane of the wavefront active)
     __device__ __forceinline__ int64_t claim()
     {
         if (fixed) {
             k += nw;
-            return order(origin + k * step);
+            return batch_start(o, k);
         }
         // (an address the compiler takes to differ by lane keeps it from wrapping the one
         // lane's atomic in a wavefront-wide sum)
@@ -240,7 +229,7 @@ template <int U> struct WaveBatches {
         asm("" : "+v"(zero));
         if ((threadIdx.x & 63) == 0)
             kc = atomicAdd(ctr + zero, 1);
-        return order(origin + __builtin_amdgcn_readlane(kc, 0) * step);
+        return batch_start(o, __builtin_amdgcn_readlane(kc, 0));
     }
 };
 
@@ -1977,7 +1966,7 @@ __device__ __forceinline__ void pass_a_body(const Run &r0, RunPtr rp, const Work
     dep.settle();
     // whole wavefronts run the loop (DEP = 2 needs them in its deposit); particles past the
     // end are masked with `valid`
-    while (bcur < p1) {
+    while (batch_begins(bcur, p1)) {
         const int64_t bnxt = wb.claim();
         const unsigned nval = (unsigned)min(p1 - bcur, (int64_t)(64 * U));
         load_batch(nxt, X, V, q.vstride, q.w, q.wu, bnxt, p1);   // the last one is discarded
@@ -2212,7 +2201,7 @@ __device__ __forceinline__ void pass_b_body(const Run &r0, RunPtr rp, const Work
     settle_pointer(Xo);
     settle_pointer(Vo);
     dep.settle();
-    while (bcur < p1) {
+    while (batch_begins(bcur, p1)) {
         const int64_t bnxt = wb.claim();
         const unsigned nval = (unsigned)min(p1 - bcur, (int64_t)(64 * U));
         load_batch(nxt, X, V, q.vstride, q.w, q.wu, bnxt, p1);   // the last one is discarded
@@ -2420,7 +2409,7 @@ __device__ __forceinline__ void esec1_body(const Run &r0, RunPtr rp, const Work 
     settle_pointer(Xo);
     settle_pointer(Vo);
     dep.settle();
-    while (bcur < p1) {
+    while (batch_begins(bcur, p1)) {
         const int64_t bnxt = wb.claim();
         const unsigned nval = (unsigned)min(p1 - bcur, (int64_t)(64 * U));
         load_batch(nxt, X, V, q.vstride, q.w, q.wu, bnxt, p1);   // the last one is discarded
@@ -2661,7 +2650,7 @@ __device__ __forceinline__ void std_pass_body(const Run &r0, RunPtr rp, const Wo
     settle_pointer(Xo);
     settle_pointer(Vo);
     dep.settle();
-    while (bcur < p1) {
+    while (batch_begins(bcur, p1)) {
         const int64_t bnxt = wb.claim();
         const unsigned nval = (unsigned)min(p1 - bcur, (int64_t)(64 * U));
         load_batch(nxt, X, V, q.vstride, q.w, q.wu, bnxt, p1);   // the last one is discarded

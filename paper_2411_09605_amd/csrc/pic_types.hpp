@@ -41,6 +41,31 @@ enum PsatdRow {
 // tent coefficients can be read as pairs.
 constexpr int coef_offset(int doubles) { return (doubles + 1) & ~1; }
 
+// The batches of a workgroup's particles (WaveBatches): batch k starts at particle
+// batch_start(o, k), while batch_begins(start, p1).  In 64 bits: pic_init takes up to 2^40
+// particles.
+struct BatchOrder {
+    int64_t origin;
+    int32_t step;          // negative: from the end of the state to its start
+};
+
+// Batches of `batch` particles of workgroup b of nblocks, whose chunk starts at p0; interleaved
+// ones are dealt over all n particles, from the end if reverse is set.
+constexpr BatchOrder batch_order(int64_t p0, int batch, bool interleave, int b, int nblocks, int64_t n,
+                                 bool reverse)
+{
+    const int32_t first = b * batch, step = nblocks * batch;      // (at most kMaxGrid batches)
+    const int64_t last = (int64_t)((uint64_t)(n - 1) / (unsigned)batch * (unsigned)batch);
+    // (selections, no branches: a pass waits for the origin before it can load a particle)
+    const int64_t dealt = reverse ? last - first : first;
+    return {interleave ? dealt : p0, interleave ? (reverse ? -step : step) : batch};
+}
+
+constexpr int64_t batch_start(const BatchOrder &o, int k) { return o.origin + (int64_t)k * o.step; }
+
+// (unsigned: a reversed order ends below particle 0)
+constexpr bool batch_begins(int64_t start, int64_t p1) { return (uint64_t)start < (uint64_t)p1; }
+
 // Per-step record, laid out exactly like pic_diag.
 struct DevRecord {
     int64_t step;
