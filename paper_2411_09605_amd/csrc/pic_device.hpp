@@ -34,10 +34,17 @@
 
 namespace pic {
 
-// Particles whose loads each thread issues together before computing on them, per pass
-// (more loads in flight against fewer waves per SIMD from the extra registers).
-template <int NV> constexpr int kUnrollA = NV == 1 ? 2 : 1;
-template <int NV> constexpr int kUnrollB = NV == 1 ? 2 : 1;
+// Particles whose loads each thread issues together before computing on them, per pass (more
+// loads in flight against fewer waves per SIMD from the extra registers).  The register windows
+// (Depo kinds 1 and 2) move less often if a lane's next particle is 64 further on rather than in
+// the wavefront's next batch, a thousand on: with three components too they take two (EMEC(LI)
+// 2e6 x 256, one and two particles: wavefront window 128 and 109 us a step, thread window on
+// sorted particles 153 and 126).
+template <int NV, int DEP> constexpr int kUnrollA = NV == 1 || DEP == 1 || DEP == 2 ? 2 : 1;
+template <int NV, int DEP> constexpr int kUnrollB = kUnrollA<NV, DEP>;
+// Of those, how many are computed on together: two particles of three components by stages would
+// need more than the 128 registers (155 and 145 us).
+template <int NV, int U> constexpr int kGroup = NV == 1 ? U : 1;
 // Minimum wavefronts per SIMD the particle passes are compiled for: one 1024-thread
 // workgroup per CU is 4 per SIMD (at most 128 VGPRs); 1D-3V keeps its registers.
 template <int NV> constexpr int kWavesPerEU = NV == 1 ? 4 : 1;
@@ -121,6 +128,22 @@ __global__ void k_group_size_probe(int slot)
 template <int U, int NV> struct PBatch {
     double x[U], v[U][NV], w[U];
 };
+
+// Particles u0 .. u0 + G - 1 of a lane's batch.
+template <int G, int U, int NV>
+__device__ __forceinline__ PBatch<G, NV> batch_group(const PBatch<U, NV> &b, int u0)
+{
+    PBatch<G, NV> o;
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+        o.x[u] = b.x[u0 + u];
+        o.w[u] = b.w[u0 + u];
+#pragma unroll
+        for (int c = 0; c < NV; ++c)
+            o.v[u][c] = b.v[u0 + u][c];
+    }
+    return o;
+}
 
 // Addressing of a wavefront's batch of 64 U consecutive particles starting at `start` (the
 // same in every lane): lane l takes start + l + 64 u.  Entries past p1 are clamped to
@@ -949,7 +972,7 @@ template <int ORDER, int NC> struct Depo<ORDER, NC, 2> {
 template <int ORDER, int NC, int DEP, int U>
 __device__ __forceinline__ void deposit_all(Depo<ORDER, NC, DEP> &dep, double *jt, int tw, int ng,
                                             Pos (&p)[U], const double (&q)[U][NC],
-                                            const bool (&valid)[U])
+                                            const bool (&valid)[U], bool first = true)
 {
     if constexpr (DEP == 0) {
         dep.template add_all<U>(jt, tw, ng, p, q, valid);
@@ -958,7 +981,7 @@ __device__ __forceinline__ void deposit_all(Depo<ORDER, NC, DEP> &dep, double *j
         for (int u = 0; u < U; ++u) {
             near_offset<ORDER>(p[u]);
             if (DEP == 2 || valid[u])
-                dep.add(jt, tw, ng, stencil_at<ORDER>(p[u]), q[u], valid[u], u == 0);
+                dep.add(jt, tw, ng, stencil_at<ORDER>(p[u]), q[u], valid[u], first && u == 0);
         }
     }
 }
@@ -1888,7 +1911,7 @@ __device__ __forceinline__ void store_all(const double (&xw)[U], const double (&
 //      (j^{n,*}) | side[tw] | eraw[tw] (E^n) | coefficients of E*
 // pass_a_body processes particles [p0, p1) of one run, its workgroup `slot`; `lead` marks
 // the one workgroup (per run and launch) that also writes the record.
-template <int ORDER, int NV, bool EM, int DEP, int U = kUnrollA<NV>>
+template <int ORDER, int NV, bool EM, int DEP, int U = kUnrollA<NV, DEP>, int G = kGroup<NV, U>>
 __device__ __forceinline__ void pass_a_body(const Run &r0, RunPtr rp, const Work &wk, int64_t step,
                                             const double *__restrict__ X,
                                             const double *__restrict__ V, int64_t p0,
@@ -1970,45 +1993,49 @@ __device__ __forceinline__ void pass_a_body(const Run &r0, RunPtr rp, const Work
         const int64_t bnxt = wb.claim();
         const unsigned nval = (unsigned)min(p1 - bcur, (int64_t)(64 * U));
         load_batch(nxt, X, V, q.vstride, q.w, q.wu, bnxt, p1);   // the last one is discarded
-        bool valid[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            valid[u] = lane + 64u * u < nval;
         if (nval < 64u * U)       // lanes past the end repeat the last particle, without weight
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                cur.w[u] = valid[u] ? cur.w[u] : 0.0;
-        double vs[U][NV], x1[U];
-        half_steps<ORDER, NV, EM, U>(q, cur.x, cur.v, eg, bs, vs, x1);
-        double qv[U][T::ncur];
+                cur.w[u] = lane + 64u * u < nval ? cur.w[u] : 0.0;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const double qw = cur.w[u] * q.qs;
+        for (int u0 = 0; u0 < U; u0 += G) {
+            const PBatch<G, NV> p = batch_group<G>(cur, u0);
+            bool valid[G];
 #pragma unroll
-            for (int c = 0; c < T::ncur; ++c)
-                qv[u][c] = qw * vs[u][c];
-        }
-        bool done = false;
-        if constexpr (!EM && ORDER == 1 && (DEP == 0 || DEP == 3)) {
-            if (q.cc) {
-                // exact charge conservation: through the pieces of the path x^n -> x^{n+1}
+            for (int u = 0; u < G; ++u)
+                valid[u] = lane + 64u * (u0 + u) < nval;
+            double vs[G][NV], x1[G];
+            half_steps<ORDER, NV, EM, G>(q, p.x, p.v, eg, bs, vs, x1);
+            double qv[G][T::ncur];
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (valid[u])
-                        cc_pieces(q, cur.x[u], x1[u], [&](int slot, double d, double f) {
-                            double qf[T::ncur];
+            for (int u = 0; u < G; ++u) {
+                const double qw = p.w[u] * q.qs;
 #pragma unroll
-                            for (int c = 0; c < T::ncur; ++c)
-                                qf[c] = qv[u][c] * f;
-                            dep.add_at(jt, tw, cc_slots(slot), cc_stencil(d), qf);
-                        });
-                done = true;
+                for (int c = 0; c < T::ncur; ++c)
+                    qv[u][c] = qw * vs[u][c];
             }
-        }
-        if (!done) {
-            Pos pos[U];
-            mid_points<ORDER, U>(pos, cur.x, x1, q);
-            deposit_all<ORDER, T::ncur, DEP, U>(dep, jt, tw, ng, pos, qv, valid);
+            bool done = false;
+            if constexpr (!EM && ORDER == 1 && (DEP == 0 || DEP == 3)) {
+                if (q.cc) {
+                    // exact charge conservation: through the pieces of the path x^n -> x^{n+1}
+#pragma unroll
+                    for (int u = 0; u < G; ++u)
+                        if (valid[u])
+                            cc_pieces(q, p.x[u], x1[u], [&](int slot, double d, double f) {
+                                double qf[T::ncur];
+#pragma unroll
+                                for (int c = 0; c < T::ncur; ++c)
+                                    qf[c] = qv[u][c] * f;
+                                dep.add_at(jt, tw, cc_slots(slot), cc_stencil(d), qf);
+                            });
+                    done = true;
+                }
+            }
+            if (!done) {
+                Pos pos[G];
+                mid_points<ORDER, G>(pos, p.x, x1, q);
+                deposit_all<ORDER, T::ncur, DEP, G>(dep, jt, tw, ng, pos, qv, valid, u0 == 0);
+            }
         }
         cur = nxt;
         bcur = bnxt;
@@ -2062,7 +2089,7 @@ __device__ __forceinline__ void write_scalars(double *sp, const double *red, uns
 //      j^{*,n+1/2}, and the coefficients of E* and E-bar follow side
 // pass_b_body processes particles [p0, p1) of one run and leaves its scalars in
 // spart[slot]; `lead` marks the workgroup that publishes the new fields of the run.
-template <int ORDER, int NV, bool EM, bool PRED, int DEP, int U = kUnrollB<NV>>
+template <int ORDER, int NV, bool EM, bool PRED, int DEP, int U = kUnrollB<NV, DEP>, int G = kGroup<NV, U>>
 __device__ __forceinline__ void pass_b_body(const Run &r0, RunPtr rp, const Work &wk, const double *X,
                                             const double *V, double *Xo, double *Vo,
                                             int64_t p0, int64_t p1, bool lead, int slot,
@@ -2205,90 +2232,94 @@ __device__ __forceinline__ void pass_b_body(const Run &r0, RunPtr rp, const Work
         const int64_t bnxt = wb.claim();
         const unsigned nval = (unsigned)min(p1 - bcur, (int64_t)(64 * U));
         load_batch(nxt, X, V, q.vstride, q.w, q.wu, bnxt, p1);   // the last one is discarded
-        bool valid[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            valid[u] = lane + 64u * u < nval;
         if (nval < 64u * U)       // lanes past the end repeat the last particle, without weight
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                cur.w[u] = valid[u] ? cur.w[u] : 0.0;
-        double vs[U][NV], x1[U], vd[U][NV];
-        Pos pos[U];
-        half_steps<ORDER, NV, EM, U>(q, cur.x, cur.v, eg, bs, vs, x1);
-        mid_points<ORDER, U>(pos, cur.x, x1, q);
-        if constexpr (EM) {
-            Stencil<ORDER> s[U], sh[U];
-            int n[U], nh[U];
-            stencils_at<ORDER, U>(s, n, pos, ng);
+                cur.w[u] = lane + 64u * u < nval ? cur.w[u] : 0.0;
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                pos[u] = half_node<ORDER>(pos[u]);
-            stencils_at<ORDER, U>(sh, nh, pos, ng);
+        for (int u0 = 0; u0 < U; u0 += G) {
+            const PBatch<G, NV> p = batch_group<G>(cur, u0);
+            bool valid[G];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                // v-dagger = v^n + dt (E-bar + v* x B-bar)   (eq. (good_translation), (EMbasic))
-                const double e[3] = {gather_at<ORDER>(eb, s[u], n[u]), gather_at<ORDER>(eb + tw, s[u], n[u]),
-                                     gather_at<ORDER>(eb + 2 * tw, s[u], n[u])};
-                const double b[3] = {q.bext[0], q.bext[1] + gather_at<ORDER>(bb, sh[u], nh[u]),
-                                     q.bext[2] + gather_at<ORDER>(bb + tw, sh[u], nh[u])};
-                const double *v = cur.v[u], *a = vs[u];
-                vd[u][0] = v[0] + q.dt * (e[0] + (a[1] * b[2] - a[2] * b[1]));
-                vd[u][1] = v[1] + q.dt * (e[1] + (a[2] * b[0] - a[0] * b[2]));
-                vd[u][2] = v[2] + q.dt * (e[2] + (a[0] * b[1] - a[1] * b[0]));
+            for (int u = 0; u < G; ++u)
+                valid[u] = lane + 64u * (u0 + u) < nval;
+            double vs[G][NV], x1[G], vd[G][NV];
+            Pos pos[G];
+            half_steps<ORDER, NV, EM, G>(q, p.x, p.v, eg, bs, vs, x1);
+            mid_points<ORDER, G>(pos, p.x, x1, q);
+            if constexpr (EM) {
+                Stencil<ORDER> s[G], sh[G];
+                int n[G], nh[G];
+                stencils_at<ORDER, G>(s, n, pos, ng);
+#pragma unroll
+                for (int u = 0; u < G; ++u)
+                    pos[u] = half_node<ORDER>(pos[u]);
+                stencils_at<ORDER, G>(sh, nh, pos, ng);
+#pragma unroll
+                for (int u = 0; u < G; ++u) {
+                    // v-dagger = v^n + dt (E-bar + v* x B-bar)   (eq. (good_translation), (EMbasic))
+                    const double e[3] = {gather_at<ORDER>(eb, s[u], n[u]), gather_at<ORDER>(eb + tw, s[u], n[u]),
+                                         gather_at<ORDER>(eb + 2 * tw, s[u], n[u])};
+                    const double b[3] = {q.bext[0], q.bext[1] + gather_at<ORDER>(bb, sh[u], nh[u]),
+                                         q.bext[2] + gather_at<ORDER>(bb + tw, sh[u], nh[u])};
+                    const double *v = p.v[u], *a = vs[u];
+                    vd[u][0] = v[0] + q.dt * (e[0] + (a[1] * b[2] - a[2] * b[1]));
+                    vd[u][1] = v[1] + q.dt * (e[1] + (a[2] * b[0] - a[0] * b[2]));
+                    vd[u][2] = v[2] + q.dt * (e[2] + (a[0] * b[1] - a[1] * b[0]));
+                }
+            } else {
+                double e[G];
+                bool done = false;
+                if constexpr (ORDER == 1) {
+                    if (q.cc) {
+#pragma unroll
+                        for (int u = 0; u < G; ++u)
+                            e[u] = cc_gather(q, ctb, p.x[u], x1[u]);
+                        done = true;
+                    }
+                }
+                if (!done) {
+                    Cell<ORDER> c[G];
+                    cells_at<ORDER, G>(c, pos, ng);
+#pragma unroll
+                    for (int u = 0; u < G; ++u)
+                        e[u] = gather_poly<ORDER>(ctb, c[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < G; ++u)
+                    dagger_es<NV>(vd[u], p.v[u], vs[u], e[u], q);
             }
-        } else {
-            double e[U];
-            bool done = false;
-            if constexpr (ORDER == 1) {
-                if (q.cc) {
+            // Gamma (eq. (opt_solution)); an imaginary or undefined root falls back to 1
+            double g[G], vn[G][NV], xw[G], v2[G];
+            gamma_all<NV, G>(g, vs, vd, p.v, valid, fb);
 #pragma unroll
-                    for (int u = 0; u < U; ++u)
-                        e[u] = cc_gather(q, ctb, cur.x[u], x1[u]);
-                    done = true;
+            for (int u = 0; u < G; ++u) {
+                v2[u] = 0.0;
+#pragma unroll
+                for (int c = 0; c < NV; ++c) {
+                    vn[u][c] = g[u] * vd[u][c];
+                    v2[u] = fma(vn[u][c], vn[u][c], v2[u]);
                 }
             }
-            if (!done) {
-                Cell<ORDER> c[U];
-                cells_at<ORDER, U>(c, pos, ng);
+            wrap_all<G>(xw, x1, q);
+            store_all<NV, G>(xw, vn, valid, Xo, Vo, bcur + 64 * u0, q.vstride);
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-                    e[u] = gather_poly<ORDER>(ctb, c[u]);
+            for (int u = 0; u < G; ++u) {
+                gdev = fmax(gdev, fabs(g[u] - 1.0));
+                ke = fma(p.w[u], v2[u], ke);
             }
+            if constexpr (PRED) {
+                double qv[G][T::ncur];
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                dagger_es<NV>(vd[u], cur.v[u], vs[u], e[u], q);
-        }
-        // Gamma (eq. (opt_solution)); an imaginary or undefined root falls back to 1
-        double g[U], vn[U][NV], xw[U], v2[U];
-        gamma_all<NV, U>(g, vs, vd, cur.v, valid, fb);
+                for (int u = 0; u < G; ++u) {
+                    const double qw = p.w[u] * q.qs;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            v2[u] = 0.0;
-#pragma unroll
-            for (int c = 0; c < NV; ++c) {
-                vn[u][c] = g[u] * vd[u][c];
-                v2[u] = fma(vn[u][c], vn[u][c], v2[u]);
+                    for (int c = 0; c < T::ncur; ++c)
+                        qv[u][c] = qw * vn[u][c];
+                    pos[u] = locate<ORDER>(fma(q.hdt, vn[u][0], xw[u]), q.inv_h, q.xshift);
+                }
+                deposit_all<ORDER, T::ncur, DEP, G>(dep, jt, tw, ng, pos, qv, valid, u0 == 0);
             }
-        }
-        wrap_all<U>(xw, x1, q);
-        store_all<NV, U>(xw, vn, valid, Xo, Vo, bcur, q.vstride);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            gdev = fmax(gdev, fabs(g[u] - 1.0));
-            ke = fma(cur.w[u], v2[u], ke);
-        }
-        if constexpr (PRED) {
-            double qv[U][T::ncur];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const double qw = cur.w[u] * q.qs;
-#pragma unroll
-                for (int c = 0; c < T::ncur; ++c)
-                    qv[u][c] = qw * vn[u][c];
-                pos[u] = locate<ORDER>(fma(q.hdt, vn[u][0], xw[u]), q.inv_h, q.xshift);
-            }
-            deposit_all<ORDER, T::ncur, DEP, U>(dep, jt, tw, ng, pos, qv, valid);
         }
         cur = nxt;
         bcur = bnxt;
@@ -2340,7 +2371,7 @@ void k_pass_b(Run r, Work wk, const double *X,
 // the other workgroups write theirs for step n + 1 (spw).
 // LDS: jt[tw] | es[tw] (E^n) | eb[tw] (unused) | e1[ng] (j^{n+1/2}) | side[tw] | three
 //      coefficient tiles (E^n, E-bar, E^{n+1}).
-template <int ORDER, int NV, int DEP, int U = kUnrollB<NV>>
+template <int ORDER, int NV, int DEP, int U = kUnrollB<NV, 0>>
 __device__ __forceinline__ void esec1_body(const Run &r0, RunPtr rp, const Work &wk, int64_t step,
                                            const double *X, const double *V, double *Xo,
                                            double *Vo, const double *Jr, double *Jd, double *Jc,
@@ -2597,7 +2628,7 @@ __global__ __launch_bounds__(1024) void k_std_prime(Run r, Work wk, const double
 // One particle pass of step n: gather E^{n+1/2} at x*, the Boris velocity update, the new
 // state, the kinetic energies before and after, and the density at x*_{n+1}.
 // LDS: jt[tw] | es[tw] | side[tw] | coefficient tile of E^{n+1/2}.
-template <int ORDER, int NV, int DEP, int U = kUnrollB<NV>>
+template <int ORDER, int NV, int DEP, int U = kUnrollB<NV, 0>>
 __device__ __forceinline__ void std_pass_body(const Run &r0, RunPtr rp, const Work &wk, int64_t step,
                                               const double *X, const double *V, double *Xo,
                                               double *Vo, double *Jd, double *Jc, double *spw,

@@ -515,7 +515,7 @@ int init_ctx(pic_ctx *c, const pic_params *p, const pic_buffers *b, hipStream_t 
     const double state_bytes = (double)p->n_particles * 8.0 * (1 + p->nv + (b->w ? 1 : 0));
     if ((p->flags & PIC_F_INTERLEAVE) || (p->rebin_every == 0 && state_bytes > kInterleaveBytes)) {
         // a workgroup then takes up to one batch more than its chunk
-        constexpr int64_t umax = std::max({kUnrollA<1>, kUnrollA<3>, kUnrollB<1>, kUnrollB<3>});
+        constexpr int64_t umax = std::max({kUnrollA<1, 0>, kUnrollA<3, 1>, kUnrollB<1, 0>, kUnrollB<3, 1>});
         r.interleave = 1;
         fixed_point_of(r.chunk + 64 * umax, r);
     }

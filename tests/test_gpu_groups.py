@@ -1,0 +1,44 @@
+"""How many of a lane's particles a pass loads at once and computes on together: one or two
+of each by the number of velocity components, the kind of deposit and the form (single or
+batched).  Every combination against the oracle on counts around a batch (the 1e-10 bar of
+tests/gpu_util.py)."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2411_09605_amd  # noqa: F401
+
+
+def _say(msg):
+    print(msg, flush=True)
+
+
+def _weibel(n, ng, order, seed=11):
+    wl = workloads.weibel(n_particles=n, n_cells=ng, order=order, steps=4, seed=seed)
+    wl.dt = min(wl.dt, 0.9 * wl.length / ng)
+    wl.B0 = wl.B0 * 50.0
+    wl.w = wl.length / n * (1.0 + 0.5 * workloads.uniforms(31, 7, n))
+    return wl
+
+
+@pytest.mark.parametrize("n", [1, 64, 65, 128, 129, 4001])
+@pytest.mark.parametrize("mode", ["window", "wave", "lds_f64", "lds_atomic"])
+@pytest.mark.parametrize("scheme,order", [("emec_li", 1), ("emec_li", 2), ("emec_lf", 2), ("esec2", 1), ("esec2", 2)])
+def test_three_components_by_deposit(scheme, order, mode, n):
+    _say(f"case: {scheme} order {order} deposit {mode} particles {n}")
+    wl = _weibel(n, 33, order)
+    if scheme == "esec2":
+        wl.E0 = wl.B0 = None
+        wl.init_gauss, wl.b_ext = True, (0.3, 0.1, -0.2)
+    gu.run_pair(wl, 3, scheme=scheme, deposit_mode=mode, block_threads=64, grid_blocks=5)
