@@ -3614,13 +3614,18 @@ template <typename T> __device__ __forceinline__ T uniform_load(const T *g)
 // Workgroups of the batched passes hold at most 512 threads: items are small, and two
 // workgroups share a CU.
 constexpr int kBatchMaxThreads = 512;
-// Particles per thread per batch in the batched passes: two, as in the plain passes, keep two
-// workgroups per CU within 128 VGPRs without spills (96 Landau runs of 1e4 to 1e6 particles:
-// four particles 183 us a step, three 181, two 180).
-template <int NV> constexpr int kBatchUnroll = NV == 1 ? 2 : 1;
+// Particles per lane in the batched passes, loaded and computed on together: two (96 Landau
+// runs of 1e4 to 1e6 particles: four particles 183 us a step, three 181, two 180; 16 runs of
+// 3e5 particles with three components: one particle 208, two 160).  The electrostatic pass B
+// then needs a few registers more than its 128: 3 of them, with three components 5 to 14, are
+// kept in scratch memory.
+constexpr int kBatchUnroll = 2;
 // Wavefronts per SIMD the batched passes are compiled for: two 512-thread workgroups per CU
-// (at most 128 VGPRs), so that one's prologue and flush overlap the other's particles.
-constexpr int kBatchWavesPerEU = 4;
+// (at most 128 VGPRs), so that one's prologue and flush overlap the other's particles.  The
+// electromagnetic pass B, 163 registers with two quadratic particles, is compiled for three:
+// kept within 128 it takes 414 us instead of 370 on 16 runs of 3e5 particles x 256 cells, 280
+// instead of 225 on 16 of 1e5 x 512 (one particle per lane at four wavefronts 424 and 290).
+template <bool EM> constexpr int kBatchWavesPerEU = EM ? 3 : 4;
 
 struct Batch {
     const BatchRun *runs;
@@ -3635,7 +3640,7 @@ struct Batch {
 };
 
 template <int ORDER, int NV, bool EM, int DEP>
-__global__ __launch_bounds__(kBatchMaxThreads) __attribute__((amdgpu_waves_per_eu(kBatchWavesPerEU))) void k_batch_pass_a(Batch b)
+__global__ __launch_bounds__(kBatchMaxThreads) __attribute__((amdgpu_waves_per_eu(kBatchWavesPerEU<false>))) void k_batch_pass_a(Batch b)
 {
     extern __shared__ double smem[];
     __shared__ double red[kRedSize];
@@ -3649,15 +3654,15 @@ __global__ __launch_bounds__(kBatchMaxThreads) __attribute__((amdgpu_waves_per_e
         const BatchRun br = uniform_load(b.runs + item.run);
         const Run &r = br.r;
         const Work wk = by_parity(br.wk, par);
-        pass_a_body<ORDER, NV, EM, DEP, kBatchUnroll<NV>>(r, (RunPtr)&b.runs[item.run].r, wk, step, b.X + br.poff,
-                                                          b.V + br.poff, item.p0, item.p1,
-                                                          item.slot == 0, item.slot, smem, red, &wctr);
+        pass_a_body<ORDER, NV, EM, DEP, kBatchUnroll, kBatchUnroll>(
+            r, (RunPtr)&b.runs[item.run].r, wk, step, b.X + br.poff, b.V + br.poff, item.p0, item.p1,
+            item.slot == 0, item.slot, smem, red, &wctr);
         lds_barrier();
     }
 }
 
 template <int ORDER, int NV, bool EM, bool PRED, int DEP>
-__global__ __launch_bounds__(kBatchMaxThreads) __attribute__((amdgpu_waves_per_eu(kBatchWavesPerEU))) void k_batch_pass_b(Batch b)
+__global__ __launch_bounds__(kBatchMaxThreads) __attribute__((amdgpu_waves_per_eu(kBatchWavesPerEU<EM>))) void k_batch_pass_b(Batch b)
 {
     extern __shared__ double smem[];
     __shared__ double red[kRedSize];
@@ -3671,7 +3676,7 @@ __global__ __launch_bounds__(kBatchMaxThreads) __attribute__((amdgpu_waves_per_e
         const BatchRun br = uniform_load(b.runs + item.run);
         const Run &r = br.r;
         const Work wk = by_parity(br.wk, par);
-        pass_b_body<ORDER, NV, EM, PRED, DEP, kBatchUnroll<NV>>(
+        pass_b_body<ORDER, NV, EM, PRED, DEP, kBatchUnroll, kBatchUnroll>(
             r, (RunPtr)&b.runs[item.run].r, wk, b.X + br.poff, b.V + br.poff, b.X + br.poff, b.V + br.poff, item.p0,
             item.p1, item.slot == 0, item.slot, smem, red, &wctr);
         lds_barrier();

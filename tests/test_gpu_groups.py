@@ -42,3 +42,26 @@ def test_three_components_by_deposit(scheme, order, mode, n):
         wl.E0 = wl.B0 = None
         wl.init_gauss, wl.b_ext = True, (0.3, 0.1, -0.2)
     gu.run_pair(wl, 3, scheme=scheme, deposit_mode=mode, block_threads=64, grid_blocks=5)
+
+
+@pytest.mark.parametrize("scheme,order", [("emec_li", 1), ("emec_li", 2), ("esec2", 1), ("esec2", 2), ("esec1", 2)])
+@pytest.mark.parametrize("threads", [64, 512])
+def test_batched_three_components(scheme, order, threads):
+    from paper_2411_09605_amd import PicBatch
+    _say(f"case: batch of {scheme} order {order} threads {threads}")
+    runs = []
+    for n, ng in ((1, 5), (64, 33), (65, 64), (129, 65), (4001, 193)):
+        wl = _weibel(n, ng, order, seed=40 + ng)
+        wl.scheme, wl.dt = scheme, 0.01
+        if scheme != "emec_li":
+            wl.E0 = wl.B0 = None
+            wl.init_gauss, wl.b_ext = True, (0.3, 0.1, -0.2)
+        runs.append(wl)
+    b = PicBatch(runs, block_threads=threads, chunk=1024)
+    orcs = [oracle.State(wl) for wl in runs]
+    for n in (1, 2, 3):
+        b.step(n)
+        for k, (wl, o) in enumerate(zip(runs, orcs)):
+            o.run(n)
+            gu.compare_state(b.state(k), o, wl.length, max(1.0, float(np.abs(wl.v).max())), scheme == "emec_li",
+                             where=f"run {k}")
