@@ -168,7 +168,9 @@ typedef struct {
     int32_t block_threads; /* threads per workgroup of the particle passes: 0 = default
                               (1024, halved down to 64 while N_p < 512 block_threads,
                               i.e. two particles per thread of 256 workgroups; then
-                              doubled while below both N_g and 512), else a
+                              doubled while below both N_g and 512; 704 for ESEC2 and
+                              PIC_STANDARD in 1D-1V beyond 5e7 particles, with an LDS
+                              deposit, no rebin and no charge conservation), else a
                               multiple of 64 in [64, 1024]                                */
     int32_t grid_blocks;   /* workgroups of the particle passes: 0 = default,
                               min(256, ceil(N_p / (2 block_threads))), one per CU.

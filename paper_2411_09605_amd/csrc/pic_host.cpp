@@ -31,6 +31,17 @@ constexpr int kDefaultThreads = 1024;
 // region of HBM at a time is faster (two-stream 4e7 particles: step -8 %); below it,
 // contiguous chunks are faster.
 constexpr double kInterleaveBytes = 192.0 * 1024 * 1024;
+// Electrostatic 1D-1V states (x, v) beyond this stream from HBM, and in a long run the loops of
+// ESEC2 and the standard scheme ask for them faster than they come: 16 wavefronts per CU then
+// hold more requests than HBM serves best, 11 are faster (60 steps at a time, 1024 and 704
+// threads: ESEC2 with tents 8e7 particles 672 and 640 us a step, 1.08e8 910 and 877, quadratic
+// 932 and 899; standard 1.08e8 607 and 602, 2e8 1168 and 1162).  The first dozen steps after a
+// pause are bound by the arithmetic (the clock is lower): there 16 are faster (1.08e8 quadratic
+// 988 and 1036, 4e7 339 and 348), so runs that gain less from it keep them, as do ESEC1 (1.08e8
+// 597 and 590, 6e7 305 and 308), the register windows, the charge-conserving and the
+// three-component runs, which the arithmetic or the LDS binds.
+constexpr double kStreamBytes = 800e6;
+constexpr int kStreamThreads = 704;
 constexpr int kDefaultRecords = 4096;
 constexpr size_t kAlign = 256;
 // LDS a workgroup may use on gfx950 (160 KB per CU, all of it available to one workgroup),
@@ -51,10 +62,9 @@ struct Layout {
     size_t total;
 };
 
-int threads_of(const pic_params *p)
+// The default width of a workgroup (block_threads = 0) but for the largest runs.
+int default_threads(const pic_params *p)
 {
-    if (p->block_threads)
-        return p->block_threads;
     const int64_t per_cu = (p->n_particles + kCUs - 1) / kCUs;
     int t = kDefaultThreads;
     while (t > 64 && per_cu < 2 * t)
@@ -66,6 +76,30 @@ int threads_of(const pic_params *p)
     while (t < 512 && t < p->n_cells)
         t *= 2;
     return t;
+}
+
+int deposit_kind(const pic_params *p)
+{
+    if (p->deposit_mode == PIC_DEPOSIT_LDS_ATOMIC)
+        return 0;
+    if (p->deposit_mode == PIC_DEPOSIT_WINDOW)
+        return 1;
+    if (p->deposit_mode == PIC_DEPOSIT_WAVE)
+        return 2;
+    if (p->deposit_mode == PIC_DEPOSIT_LDS_F64)
+        return 3;
+    return p->rebin_every > 0 ? 1 : 0;
+}
+
+int threads_of(const pic_params *p)
+{
+    if (p->block_threads)
+        return p->block_threads;
+    const int kind = deposit_kind(p);
+    if ((p->scheme == PIC_ESEC2 || is_std(p)) && p->nv == 1 && !is_cc(p) && p->rebin_every == 0 &&
+        (kind == 0 || kind == 3) && 16.0 * (double)p->n_particles > kStreamBytes)
+        return kStreamThreads;
+    return default_threads(p);
 }
 
 int records_of(const pic_params *p) { return p->record_capacity ? p->record_capacity : kDefaultRecords; }
@@ -191,19 +225,6 @@ void scan_shape(int64_t n, int *nseg, int64_t *seg)
     int64_t ns = std::min<int64_t>(1024, std::max<int64_t>(1, (n + 2047) / 2048));
     *seg = (n + ns - 1) / ns;
     *nseg = (int)((n + *seg - 1) / *seg);
-}
-
-int deposit_kind(const pic_params *p)
-{
-    if (p->deposit_mode == PIC_DEPOSIT_LDS_ATOMIC)
-        return 0;
-    if (p->deposit_mode == PIC_DEPOSIT_WINDOW)
-        return 1;
-    if (p->deposit_mode == PIC_DEPOSIT_WAVE)
-        return 2;
-    if (p->deposit_mode == PIC_DEPOSIT_LDS_F64)
-        return 3;
-    return p->rebin_every > 0 ? 1 : 0;
 }
 
 Layout layout_of(const pic_params *p)

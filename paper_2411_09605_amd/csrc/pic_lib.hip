@@ -1568,9 +1568,12 @@ pic_params adj_forward_params(const pic_adj_params *p)
     q.flags = PIC_F_INIT_GAUSS;
     q.block_threads = p->block_threads;
     q.grid_blocks = p->grid_blocks;
-    // (the plain step's default shape.  Forward and backward in ms, two 512-thread workgroups
-    // per CU against one of 1024: 5.23 / 4.77 at 2^19 particles x 512 cells, 5.80 / 5.60 at
-    // 1e6 x 256, 6.06 / 5.97 at 2.5e6 x 256, 8.44 / 8.42 at 1e7 x 512)
+    // the plain step's default shape, without its narrower workgroups of the largest runs.
+    // (Forward and backward in ms, two 512-thread workgroups per CU against one of 1024: 5.23 /
+    // 4.77 at 2^19 particles x 512 cells, 5.80 / 5.60 at 1e6 x 256, 6.06 / 5.97 at 2.5e6 x 256,
+    // 8.44 / 8.42 at 1e7 x 512)
+    if (!q.block_threads)
+        q.block_threads = default_threads(&q);
     q.record_capacity = p->n_steps + 1;
     return q;
 }

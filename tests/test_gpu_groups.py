@@ -65,3 +65,28 @@ def test_batched_three_components(scheme, order, threads):
             o.run(n)
             gu.compare_state(b.state(k), o, wl.length, max(1.0, float(np.abs(wl.v).max())), scheme == "emec_li",
                              where=f"run {k}")
+
+
+@pytest.mark.parametrize("scheme", ["esec2", "standard"])
+@pytest.mark.parametrize("n", [1, 703, 1409, 8449, 30_001])
+def test_eleven_wavefronts(scheme, n):
+    """The workgroups of the largest runs (704 threads, interleaved batches) on small ones."""
+    _say(f"case: 704 threads, {scheme}, {n} particles")
+    wl = workloads.two_stream(n_particles=n, n_cells=77, steps=4)
+    wl.w = wl.length / n * (1.0 + 0.5 * workloads.uniforms(31, 7, n))
+    gu.run_pair(wl, 4, scheme=scheme, block_threads=704, grid_blocks=3, interleave=True)
+
+
+@pytest.mark.parametrize("n,scheme,knobs,threads", [
+    (50_000_000, "esec2", {}, 1024), (50_000_001, "esec2", {}, 704), (50_000_001, "standard", {}, 704),
+    (50_000_001, "esec1", {}, 1024), (50_000_001, "esec2", dict(charge_conserving=True), 1024),
+    (50_000_001, "esec2", dict(deposit_mode="window"), 1024), (50_000_001, "esec2", dict(block_threads=512), 512)])
+def test_default_threads_of_the_largest_runs(n, scheme, knobs, threads):
+    import torch
+    from paper_2411_09605_amd import Pic, binding
+    _say(f"case: default threads of {n} particles, {scheme} {knobs}")
+    p = binding.make_params(1, scheme, 1, n, 64, 12.0, 0.1, init_gauss=True, **knobs)
+    x = torch.arange(n, device="cuda", dtype=torch.float64) * (12.0 / n)
+    gpu = Pic(p, x, torch.zeros(1, n, device="cuda", dtype=torch.float64),
+              torch.zeros(3, 64, device="cuda", dtype=torch.float64))
+    assert gpu.launch_shape()[0] == threads
