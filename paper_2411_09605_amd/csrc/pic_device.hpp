@@ -1242,13 +1242,6 @@ __device__ __forceinline__ double block_sum(double v, double *red)
     return a[0];
 }
 
-__device__ __forceinline__ double block_max(double v, double *red)
-{
-    double a[1] = {v};
-    block_reduce<1u>(a, red);
-    return a[0];
-}
-
 // Mean of n values (LDS or global), identical in every workgroup of a launch.
 __device__ __forceinline__ double block_mean(const double *a, int n, double *red)
 {
@@ -2369,8 +2362,8 @@ void k_pass_b(Run r, Work wk, const double *X,
 // into.  The per-workgroup scalars alternate between two arrays as well: this pass's lead
 // writes the record of step n from the scalars of the previous pass (wk.spart) while
 // the other workgroups write theirs for step n + 1 (spw).
-// LDS: jt[tw] | es[tw] (E^n) | eb[tw] (unused) | e1[ng] (j^{n+1/2}) | side[tw] | three
-//      coefficient tiles (E^n, E-bar, E^{n+1}).
+// LDS: jt[tw] | es[tw] (E^n) | e1[ng] (j^{n+1/2}) | side[tw] | three coefficient tiles (E^n,
+//      E-bar, E^{n+1}).
 template <int ORDER, int NV, int DEP, int U = kUnrollB<NV, 0>>
 __device__ __forceinline__ void esec1_body(const Run &r0, RunPtr rp, const Work &wk, int64_t step,
                                            const double *X, const double *V, double *Xo,
@@ -2388,10 +2381,9 @@ __device__ __forceinline__ void esec1_body(const Run &r0, RunPtr rp, const Work 
     wb.reset();
     double *jt = smem;
     double *es = jt + tw;
-    double *eb = es + tw;
-    double *e1 = eb + tw;
+    double *e1 = es + tw;
     double *side = e1 + ng;
-    double *ctn = smem + coef_offset(4 * tw + ng);     // E^n
+    double *ctn = smem + coef_offset(3 * tw + ng);     // E^n
     double *ctb = ctn + (ORDER + 1) * tw;               // E-bar
     double *ct1 = ctb + (ORDER + 1) * tw;               // E^{n+1}
     const double *En = wk.Ef[0];

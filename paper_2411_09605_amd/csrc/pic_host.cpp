@@ -154,11 +154,12 @@ size_t lds_pass_b_of(bool em, int order, size_t ng)
               : ((size_t)pic::coef_offset((int)(4 * tw + ng)) + 2 * (order + 1) * tw) * 8;
 }
 
-// ESEC1 in one pass (esec1_body): jt | es | eb | e1[ng] | side | three coefficient tiles
-size_t lds_esec1_of(int order, size_t ng)
+// ESEC1 in one pass (esec1_body): jt | es | e1[ng] | side | three coefficient tiles.  The grids
+// that ESEC1 accepts are those that would fit with a fourth tile (lds_need).
+size_t lds_esec1_of(int order, size_t ng, int tiles = 3)
 {
     const size_t tw = ng + 2 * kGhost;
-    return ((size_t)pic::coef_offset((int)(4 * tw + ng)) + 3 * (order + 1) * tw) * 8;
+    return ((size_t)pic::coef_offset((int)(tiles * tw + ng)) + 3 * (order + 1) * tw) * 8;
 }
 
 // standard scheme: the particle pass (jt | es | side | coefficient tile) and the field
@@ -184,7 +185,7 @@ size_t lds_rebin(const pic_params *p) { return (size_t)kVBins * p->n_cells * 8; 
 
 size_t lds_need(const pic_params *p)
 {
-    size_t m = p->scheme == PIC_ESEC1 ? std::max(lds_pass_a(p), lds_esec1_of(p->shape_order, (size_t)p->n_cells))
+    size_t m = p->scheme == PIC_ESEC1 ? std::max(lds_pass_a(p), lds_esec1_of(p->shape_order, (size_t)p->n_cells, 4))
                : is_std(p) ? std::max(lds_std_pass_of(p->shape_order, (size_t)p->n_cells),
                                       lds_std_field_of((size_t)p->n_cells))
                            : std::max(lds_pass_a(p), lds_pass_b(p));

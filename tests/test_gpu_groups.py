@@ -90,3 +90,14 @@ def test_default_threads_of_the_largest_runs(n, scheme, knobs, threads):
     gpu = Pic(p, x, torch.zeros(1, n, device="cuda", dtype=torch.float64),
               torch.zeros(3, 64, device="cuda", dtype=torch.float64))
     assert gpu.launch_shape()[0] == threads
+
+
+@pytest.mark.parametrize("order,ng", [(1, 1842), (2, 1446)])
+def test_esec1_on_the_largest_grids(order, ng):
+    """The largest grids that ESEC1 accepts (its tiles in LDS end within the launch)."""
+    from paper_2411_09605_amd import binding
+    _say(f"case: ESEC1 order {order} on {ng} cells")
+    wl = workloads.two_stream(n_particles=6001, n_cells=ng, order=order, steps=3)
+    gu.run_pair(wl, 3, scheme="esec1")
+    p = binding.make_params(1, "esec1", order, 6001, ng + 1, wl.length, wl.dt)
+    assert binding.validate(p) == -6
