@@ -414,7 +414,10 @@ void k_adj_reverse(Run r, AdjWork aw, AdjParams ap, int q, const double *__restr
 // the reverse passes, whose 16 wavefronts of 96 registers leave a CU room for four of 128: one
 // workgroup of four wavefronts per CU, for the whole segment.  (Eight wavefronts and ten steps
 // a launch 5.93 ms, sixteen and five 5.94-6.15, four and ten 5.88; two particles per lane
-// 5.88-5.93.)
+// 5.88-5.93.)  Both shapes were chosen there: with fewer particles the first segment's launch
+// leaves CUs idle (5e4: 13 workgroups), and on grids beyond about 1070 cells two buffers no longer
+// fit a CU beside a reverse workgroup; a step is faster than with a launch of its own all the
+// same (backward of 40 steps, 5e4 x 256 1345 -> 715 us, 1e6 x 1200 2920 -> 2000).
 // LDS: nbuf buffers of the coefficients of E* and E-bar ([2][(ORDER + 1) tw] each).  With two,
 // the next step's node values load while the particles of the present one are pushed, and a
 // step has one barrier.

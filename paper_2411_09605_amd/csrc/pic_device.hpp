@@ -43,7 +43,7 @@ namespace pic {
 template <int NV, int DEP> constexpr int kUnrollA = NV == 1 || DEP == 1 || DEP == 2 ? 2 : 1;
 template <int NV, int DEP> constexpr int kUnrollB = kUnrollA<NV, DEP>;
 // Of those, how many are computed on together: two particles of three components by stages would
-// need more than the 128 registers (155 and 145 us).
+// need more than the 128 registers (the same two 155 and 145 us).
 template <int NV, int U> constexpr int kGroup = NV == 1 ? U : 1;
 // Minimum wavefronts per SIMD the particle passes are compiled for: one 1024-thread
 // workgroup per CU is 4 per SIMD (at most 128 VGPRs); 1D-3V keeps its registers.
@@ -201,7 +201,7 @@ __device__ __forceinline__ void load_batch(PBatch<U, NV> &b, const double *__res
 // about one batch of each other.  The counter is set by reset() before a barrier that
 // precedes the first claim.
 //
-// Batch k of a workgroup starts at origin + k step.  Chunks (the default): the
+// Batch k of a workgroup starts at origin + k step (batch_order).  Chunks (the default): the
 // workgroup's particles are [p0, p1), origin = p0 and step = one batch.  Interleaved:
 // batches are dealt to the workgroups round-robin, origin = b batches for workgroup b
 // and step = nblocks batches, so that at any moment the grid reads one region of the
