@@ -498,7 +498,10 @@ int init_ctx(pic_ctx *c, const pic_params *p, const pic_buffers *b, hipStream_t 
     c->p = *p;
     c->b = *b;
     c->stream = stream;
-    c->threads = threads_of(p);
+    // the initialisation's launches take the widest default workgroups at any size (the state is
+    // read without a prefetch: 1.08e8 particles 1.31 ms with the 704 threads of the steps, 1.03 with
+    // 1024)
+    c->threads = p->block_threads ? p->block_threads : default_threads(p);
     c->poisoned = 0;
     c->records_read = 0;
     c->steps_done = 0;
@@ -530,6 +533,13 @@ int init_ctx(pic_ctx *c, const pic_params *p, const pic_buffers *b, hipStream_t 
     clear2(c->stream, w.Ef[0], (int64_t)(L.cninv - L.Ef[0]) / 8, b->E + p->n_cells,
            is_em(p) ? 0 : 2 * (int64_t)p->n_cells);
     const int gt = grid_threads(c);
+    auto launched = [&] {
+        c->threads = threads_of(p);
+        int rc = check(c, "pic_init launches");
+        if (rc != PIC_OK)
+            g_last_error = c->err;
+        return rc;
+    };
     if (p->nv == 1)
         hipLaunchKernelGGL((k_init_particles<1>), dim3(r.nblocks), dim3(c->threads), 0, c->stream, r, w,
                            b->x, b->v);
@@ -549,10 +559,7 @@ int init_ctx(pic_ctx *c, const pic_params *p, const pic_buffers *b, hipStream_t 
             hipLaunchKernelGGL((k_init_deposits<2>), dim3(r.nblocks), dim3(c->threads), lds, c->stream, r,
                                w, b->x, b->v);
         hipLaunchKernelGGL(k_gauss_finish, dim3(1), dim3(kGaussThreads), gauss_lds(p->n_cells), c->stream, r, w);
-        int rc = check(c, "pic_init launches");
-        if (rc != PIC_OK)
-            g_last_error = c->err;
-        return rc;
+        return launched();
     }
     if ((p->flags & PIC_F_INIT_GAUSS) && is_cc(p)) {
         // the density with the quadratic B-spline (one degree above the tent), then Gauss'
@@ -578,10 +585,7 @@ int init_ctx(pic_ctx *c, const pic_params *p, const pic_buffers *b, hipStream_t 
         hipLaunchKernelGGL(k_std_green, dim3(1), dim3(gt), 0, c->stream, r, w);
         dispatch(c, D_STD_PRIME);       // the density at x*_0 for the first field launch
     }
-    int rc = check(c, "pic_init launches");
-    if (rc != PIC_OK)
-        g_last_error = c->err;
-    return rc;
+    return launched();
 }
 
 // Enqueue n_steps >= 0 steps of a live context (pic_step after its argument checks).
