@@ -279,7 +279,7 @@ void k_adj_reverse(Run r, AdjWork aw, AdjParams ap, int q, const double *__restr
     const int64_t p0 = (int64_t)blockIdx.x * r.chunk;
     const int64_t p1 = min(r.np, p0 + r.chunk);
     // wavefronts claim batches of 64 particles (the counter is set before the barrier below)
-    WaveBatches<1> wb(p0, &wctr, nt);
+    WaveBatches<1> wb(batch_order(p0, 64, false, blockIdx.x, r.nblocks, r.np, false), &wctr, nt);
     wb.reset();
     double *es = smem, *eb = es + tw, *lt = eb + tw, *t4 = lt + tw;
     double *esm = t4 + tw, *ebm = esm + tw, *tm = ebm + tw;   // STAGE 4

@@ -218,13 +218,10 @@ template <int U> struct WaveBatches {
     int k;                 // static: index of the wavefront's current batch
     int nw;
     // Interleaved runs (the state larger than the 256 MB Infinity Cache) can walk the state
-    // from its end (reverse): a pass that starts where the previous pass ended finds up to
-    // 256 MB of the state still in the cache.  The set of batches is the same either way.
-    __device__ __forceinline__ WaveBatches(int64_t p0, int *counter, unsigned nt, int interleave = 0,
-                                           int nblocks = 1, int static_order = 0,
-                                           int64_t n_particles = 0, bool reverse = false)
-        : o(batch_order(p0, 64 * U, interleave != 0, (int)blockIdx.x, nblocks, n_particles, reverse)),
-          ctr(counter), fixed(static_order), nw((int)(nt >> 6))
+    // from its end (a reversed order): a pass that starts where the previous pass ended finds
+    // up to 256 MB of the state still in the cache.  The set of batches is the same either way.
+    __device__ __forceinline__ WaveBatches(const BatchOrder &order, int *counter, unsigned nt, int static_order = 0)
+        : o(order), ctr(counter), fixed(static_order), nw((int)(nt >> 6))
     {
         k = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     }
@@ -1923,7 +1920,7 @@ __device__ __forceinline__ void pass_a_body(const Run &r0, RunPtr rp, const Work
     double *ct = smem + coef_offset((2 * T::ncur + T::ne + T::nb + 1) * tw);   // ES: coefficients
     Depo<ORDER, T::ncur, DEP> dep;
     // pass A walks the state from its end, pass B from its start (see WaveBatches)
-    WaveBatches<U> wb(p0, wctr, nt, r.interleave, r.nblocks, r.det, r.np, true);
+    WaveBatches<U> wb(batch_order(p0, 64 * U, r.interleave != 0, blockIdx.x, r.nblocks, r.np, true), wctr, nt, r.det);
     PBatch<U, NV> cur, nxt;
     int64_t bcur = wb.first();
     wb.reset();
@@ -2092,7 +2089,7 @@ __device__ __forceinline__ void pass_b_body(const Run &r0, RunPtr rp, const Work
     using T = TileSizes<NV, EM>;
     const int ng = r.ng, tw = r.tw;
     const unsigned lane = threadIdx.x & 63, nt = nthreads();
-    WaveBatches<U> wb(p0, wctr, nt, r.interleave, r.nblocks, r.det);
+    WaveBatches<U> wb(batch_order(p0, 64 * U, r.interleave != 0, blockIdx.x, r.nblocks, r.np, false), wctr, nt, r.det);
     PBatch<U, NV> cur, nxt;
     int64_t bcur = wb.first();
     wb.reset();
@@ -2375,7 +2372,8 @@ __device__ __forceinline__ void esec1_body(const Run &r0, RunPtr rp, const Work 
     const int ng = r.ng, tw = r.tw;
     const unsigned lane = threadIdx.x & 63, nt = nthreads();
     // one pass per step: alternate directions (see WaveBatches)
-    WaveBatches<U> wb(p0, wctr, nt, r.interleave, r.nblocks, r.det, r.np, (step & 1) != 0);
+    WaveBatches<U> wb(batch_order<true>(p0, 64 * U, r.interleave != 0, blockIdx.x, r.nblocks, r.np, (step & 1) != 0),
+                      wctr, nt, r.det);
     PBatch<U, NV> cur, nxt;
     int64_t bcur = wb.first();
     wb.reset();
@@ -2631,7 +2629,8 @@ __device__ __forceinline__ void std_pass_body(const Run &r0, RunPtr rp, const Wo
     const int ng = r.ng, tw = r.tw;
     const unsigned lane = threadIdx.x & 63, nt = nthreads();
     // one pass per step: alternate directions (see WaveBatches)
-    WaveBatches<U> wb(p0, wctr, nt, r.interleave, r.nblocks, r.det, r.np, (step & 1) != 0);
+    WaveBatches<U> wb(batch_order<true>(p0, 64 * U, r.interleave != 0, blockIdx.x, r.nblocks, r.np, (step & 1) != 0),
+                      wctr, nt, r.det);
     PBatch<U, NV> cur, nxt;
     int64_t bcur = wb.first();
     wb.reset();

@@ -18,7 +18,7 @@ static int fails = 0;
 #define CHECK(c) do { if (!(c)) { std::printf("line %d: %s, n %lld\n", __LINE__, #c, (long long)n); ++fails; } } while (0)
 
 // a small run: each batch of each workgroup, as the passes' loops visit them
-static void small(long long n, int batch, int nblocks, bool interleave, bool reverse)
+template <bool MASKS> static void small(long long n, int batch, int nblocks, bool interleave, bool reverse)
 {
     int64_t chunk = (n + nblocks - 1) / nblocks;
     chunk = (chunk + 63) / 64 * 64;
@@ -26,7 +26,7 @@ static void small(long long n, int batch, int nblocks, bool interleave, bool rev
     std::vector<int> seen(n, 0);
     for (int b = 0; b < nblocks; ++b) {
         const int64_t p0 = b * chunk, p1 = interleave ? n : (p0 + chunk < n ? p0 + chunk : n);
-        const BatchOrder o = batch_order(p0, batch, interleave, b, nblocks, n, reverse);
+        const BatchOrder o = batch_order<MASKS>(p0, batch, interleave, b, nblocks, n, reverse);
         for (int k = 0; batch_begins(batch_start(o, k), p1); ++k)
             for (int64_t p = batch_start(o, k); p < batch_start(o, k) + batch && p < p1; ++p)
                 ++seen[p];
@@ -41,14 +41,14 @@ static void small(long long n, int batch, int nblocks, bool interleave, bool rev
         CHECK(v == 1);
 }
 
-int main()
+template <bool MASKS> static void run()
 {
     const long long sizes[] = {1, 63, 64, 65, 127, 128, 129, 1000, 8191, 8192, 8193};
     for (long long n : sizes)
         for (int batch : {64, 128, 256})
             for (int nblocks : {1, 2, 7, 256})
                 for (int how = 0; how < 3; ++how)
-                    small(n, batch, nblocks, how > 0, how == 2);
+                    small<MASKS>(n, batch, nblocks, how > 0, how == 2);
     // large runs: the chunks of 256 workgroups, first and last batches of every order
     for (int e = 30; e <= 40; ++e)
         for (long long d : {-65LL, 0LL, 64LL}) {
@@ -57,10 +57,10 @@ int main()
             const int nb = (int)((n + chunk - 1) / chunk);
             for (int b : {0, 1, nb / 2, nb - 1}) {
                 const int64_t p0 = b * chunk;
-                CHECK(batch_start(batch_order(p0, 128, false, b, nb, n, false), 0) == p0);
+                CHECK(batch_start(batch_order<MASKS>(p0, 128, false, b, nb, n, false), 0) == p0);
                 const int last = (int)(((n - 1) / 128 - b) / nb);      // its last batch
-                const BatchOrder f = batch_order(p0, 128, true, b, nb, n, false);
-                const BatchOrder r = batch_order(p0, 128, true, b, nb, n, true);
+                const BatchOrder f = batch_order<MASKS>(p0, 128, true, b, nb, n, false);
+                const BatchOrder r = batch_order<MASKS>(p0, 128, true, b, nb, n, true);
                 CHECK(batch_start(f, 0) == 128LL * b && batch_begins(batch_start(f, last), n));
                 CHECK(!batch_begins(batch_start(f, last + 1), n));
                 CHECK(batch_start(r, 0) == ((n - 1) / 128 - b) * 128 && batch_begins(batch_start(r, 0), n));
@@ -68,6 +68,12 @@ int main()
                 CHECK(!batch_begins(batch_start(r, last + 1), n));
             }
         }
+}
+
+int main()
+{
+    run<false>();
+    run<true>();
     std::printf(fails ? "failed\n" : "ok\n");
     return fails != 0;
 }
