@@ -155,7 +155,7 @@ struct BatchAddr {
     unsigned lim;      // largest offset inside [b0, p1)
     __device__ __forceinline__ BatchAddr(int64_t start, int64_t p1, unsigned span)
     {
-        b0 = batch_begins(start, p1) ? start : p1 - 1;
+        b0 = (int64_t)min((uint64_t)start, (uint64_t)(p1 - 1));      // (as batch_begins compares)
         lim = (unsigned)min(p1 - 1 - b0, (int64_t)(span - 1));
     }
     __device__ __forceinline__ unsigned off(unsigned lane, int u) const
@@ -1983,17 +1983,15 @@ __device__ __forceinline__ void pass_a_body(const Run &r0, RunPtr rp, const Work
         const int64_t bnxt = wb.claim();
         const unsigned nval = (unsigned)min(p1 - bcur, (int64_t)(64 * U));
         load_batch(nxt, X, V, q.vstride, q.w, q.wu, bnxt, p1);   // the last one is discarded
+        bool in[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            in[u] = lane + 64u * u < nval;
         if (nval < 64u * U)       // lanes past the end repeat the last particle, without weight
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                cur.w[u] = lane + 64u * u < nval ? cur.w[u] : 0.0;
-#pragma unroll
-        for (int u0 = 0; u0 < U; u0 += G) {
-            const PBatch<G, NV> p = batch_group<G>(cur, u0);
-            bool valid[G];
-#pragma unroll
-            for (int u = 0; u < G; ++u)
-                valid[u] = lane + 64u * (u0 + u) < nval;
+                cur.w[u] = in[u] ? cur.w[u] : 0.0;
+        auto process = [&](const PBatch<G, NV> &p, const bool (&valid)[G], int u0) __attribute__((always_inline)) {
             double vs[G][NV], x1[G];
             half_steps<ORDER, NV, EM, G>(q, p.x, p.v, eg, bs, vs, x1);
             double qv[G][T::ncur];
@@ -2025,6 +2023,18 @@ __device__ __forceinline__ void pass_a_body(const Run &r0, RunPtr rp, const Work
                 Pos pos[G];
                 mid_points<ORDER, G>(pos, p.x, x1, q);
                 deposit_all<ORDER, T::ncur, DEP, G>(dep, jt, tw, ng, pos, qv, valid, u0 == 0);
+            }
+        };
+        if constexpr (G == U) {
+            process(cur, in, 0);
+        } else {
+#pragma unroll
+            for (int u0 = 0; u0 < U; u0 += G) {
+                bool valid[G];
+#pragma unroll
+                for (int u = 0; u < G; ++u)
+                    valid[u] = in[u0 + u];
+                process(batch_group<G>(cur, u0), valid, u0);
             }
         }
         cur = nxt;
@@ -2222,17 +2232,15 @@ __device__ __forceinline__ void pass_b_body(const Run &r0, RunPtr rp, const Work
         const int64_t bnxt = wb.claim();
         const unsigned nval = (unsigned)min(p1 - bcur, (int64_t)(64 * U));
         load_batch(nxt, X, V, q.vstride, q.w, q.wu, bnxt, p1);   // the last one is discarded
+        bool in[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            in[u] = lane + 64u * u < nval;
         if (nval < 64u * U)       // lanes past the end repeat the last particle, without weight
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                cur.w[u] = lane + 64u * u < nval ? cur.w[u] : 0.0;
-#pragma unroll
-        for (int u0 = 0; u0 < U; u0 += G) {
-            const PBatch<G, NV> p = batch_group<G>(cur, u0);
-            bool valid[G];
-#pragma unroll
-            for (int u = 0; u < G; ++u)
-                valid[u] = lane + 64u * (u0 + u) < nval;
+                cur.w[u] = in[u] ? cur.w[u] : 0.0;
+        auto process = [&](const PBatch<G, NV> &p, const bool (&valid)[G], int u0) __attribute__((always_inline)) {
             double vs[G][NV], x1[G], vd[G][NV];
             Pos pos[G];
             half_steps<ORDER, NV, EM, G>(q, p.x, p.v, eg, bs, vs, x1);
@@ -2309,6 +2317,18 @@ __device__ __forceinline__ void pass_b_body(const Run &r0, RunPtr rp, const Work
                     pos[u] = locate<ORDER>(fma(q.hdt, vn[u][0], xw[u]), q.inv_h, q.xshift);
                 }
                 deposit_all<ORDER, T::ncur, DEP, G>(dep, jt, tw, ng, pos, qv, valid, u0 == 0);
+            }
+        };
+        if constexpr (G == U) {
+            process(cur, in, 0);
+        } else {
+#pragma unroll
+            for (int u0 = 0; u0 < U; u0 += G) {
+                bool valid[G];
+#pragma unroll
+                for (int u = 0; u < G; ++u)
+                    valid[u] = in[u0 + u];
+                process(batch_group<G>(cur, u0), valid, u0);
             }
         }
         cur = nxt;
