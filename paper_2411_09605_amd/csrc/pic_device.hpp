@@ -1449,7 +1449,7 @@ __device__ __forceinline__ void predictor_fields(const Run &r, const double *E, 
 //     (I - s L_h) E_z' = (I + s L_h) E_z + dt c^2 D-B_y - dt j_z,  B_y' = B_y + a D+(E_z + E_z')
 //     E_x' = E_x - dt j_x
 //   The circulant system is solved with the first row g of its inverse.
-// scratch: 8 N_g doubles of LDS (E^n, B^n, right-hand sides, g).
+// scratch: 7 N_g doubles of LDS (E^n, B^n, right-hand sides).
 __device__ __forceinline__ void field_update(const Run &r, const Work &wk, const double *E, const double *B,
                              const double *J, double *e1, double *b1, double *eb, double *bb,
                              double *scratch, int nrep)
@@ -1458,10 +1458,11 @@ __device__ __forceinline__ void field_update(const Run &r, const Work &wk, const
     double *E0 = scratch;            // [3][ng]
     double *B0 = E0 + 3 * ng;        // [2][ng]
     double *R = B0 + 2 * ng;         // [2][ng]
-    double *g = R + 2 * ng;          // [ng]
+    double *g2 = b1;                 // [2][ng]: g twice (b1 is written after their last use)
     tile_load(E0, E, 3 * ng);
     tile_load(B0, B, 2 * ng);
-    tile_load(g, wk.cninv, ng);
+    for (int i = threadIdx.x; i < ng; i += nthreads())
+        g2[i] = g2[ng + i] = wk.cninv[i];
     __syncthreads();
     const double a = r.hdt, s = a * a * r.c2, ih2 = r.inv_h * r.inv_h;
     const double *Ey = E0 + ng, *Ez = E0 + 2 * ng, *By = B0, *Bz = B0 + ng;
@@ -1474,13 +1475,16 @@ __device__ __forceinline__ void field_update(const Run &r, const Work &wk, const
                     + r.dt * r.c2 * dminus(By, i, ng, r.inv_h) - r.dt * rep_sum(J, 2 * ng + i, nrep, rs);
     }
     __syncthreads();
+    // (The row twice over, so that no index wraps: with a selection on each one it was left to
+    // the registers of the surrounding pass whether the reads overlap, and the solve took what
+    // they gave: batches of 16 runs of 1e5 particles x 512 cells 225 to 290 us a step, now 155.)
     for (int i = threadIdx.x; i < ng; i += nthreads()) {
+        const double *gi = g2 + ng + i;
         double ay = 0.0, az = 0.0;
+#pragma unroll 4
         for (int j = 0; j < ng; ++j) {
-            int k = i - j;
-            k += k < 0 ? ng : 0;
-            ay += g[k] * R[j];
-            az += g[k] * R[ng + j];
+            ay += gi[-j] * R[j];
+            az += gi[-j] * R[ng + j];
         }
         e1[ng + i] = ay;
         e1[2 * ng + i] = az;
@@ -3628,13 +3632,13 @@ constexpr int kBatchMaxThreads = 512;
 // Particles per lane in the batched passes, loaded and computed on together: two (96 Landau
 // runs of 1e4 to 1e6 particles: four particles 183 us a step, three 181, two 180; 16 runs of
 // 3e5 particles with three components: one particle 208, two 160).  The electrostatic pass B
-// then needs a few registers more than its 128: 3 of them, with three components 5 to 14, are
+// then needs a few registers more than its 128: 1 of them, with three components 3 to 10, are
 // kept in scratch memory.
 constexpr int kBatchUnroll = 2;
 // Wavefronts per SIMD the batched passes are compiled for: two 512-thread workgroups per CU
 // (at most 128 VGPRs), so that one's prologue and flush overlap the other's particles.  The
-// electromagnetic pass B, 163 registers with two quadratic particles, is compiled for three:
-// kept within 128 it takes 414 us instead of 370 on 16 runs of 3e5 particles x 256 cells, 280
+// electromagnetic pass B, 161 registers with two quadratic particles, is compiled for three:
+// kept within 128 it took 414 us instead of 370 on 16 runs of 3e5 particles x 256 cells, 280
 // instead of 225 on 16 of 1e5 x 512 (one particle per lane at four wavefronts 424 and 290).
 template <bool EM> constexpr int kBatchWavesPerEU = EM ? 3 : 4;
 
